@@ -159,14 +159,13 @@ __global__ __launch_bounds__(NWV * 64, (NWV == 4 && KVB) ? 3 : 1) void k_attn(At
   bf16x8 qh[DS], ql[DS];
   if (KVB) {
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        uint16_t h, l2;
-        split_bf16(f8_get(qf[ds], e), h, l2);
-        qh[ds][e] = __builtin_bit_cast(__bf16, h);
-        ql[ds][e] = __builtin_bit_cast(__bf16, l2);
-      }
+    for (int ds = 0; ds < DS; ++ds) {
+      const float v[8] = {qf[ds].a.x, qf[ds].a.y, qf[ds].a.z, qf[ds].a.w, qf[ds].b.x, qf[ds].b.y, qf[ds].b.z, qf[ds].b.w};
+      u32x4 h, l;
+      split8(v, h, l);
+      qh[ds] = as_bf16x8(h);
+      ql[ds] = as_bf16x8(l);
+    }
   }
 
   float mrun = -INFINITY, lrun = 0.f;
@@ -269,14 +268,9 @@ __global__ __launch_bounds__(NWV * 64, (NWV == 4 && KVB) ? 3 : 1) void k_attn(At
       }
     }
     if (KVB) {
-      bf16x8 ph, pl;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        uint16_t h, l2;
-        split_bf16(pv[e], h, l2);
-        ph[e] = __builtin_bit_cast(__bf16, h);
-        pl[e] = __builtin_bit_cast(__bf16, l2);
-      }
+      u32x4 h, l;
+      split8(pv, h, l);
+      const bf16x8 ph = as_bf16x8(h), pl = as_bf16x8(l);
 #pragma unroll
       for (int t = 0; t < DT; ++t) {
         const bf16x8 vv = as_bf16x8(d16.v[t]);

@@ -13,12 +13,14 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// fp32 -> bf16 bits, round to nearest even (finite inputs)
-__device__ __forceinline__ uint16_t f2bf_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// two fp32 -> two bf16 bit patterns (a in the low half), round to nearest
+// even: one v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t f2bf_pair(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
+__device__ __forceinline__ uint16_t f2bf_bits(float f) { return (uint16_t)f2bf_pair(f, 0.f); }
 __device__ __forceinline__ float bf_bits2f(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
 }
@@ -27,6 +29,21 @@ __device__ __forceinline__ float bf_bits2f(uint16_t b) {
 __device__ __forceinline__ void split_bf16(float x, uint16_t& hi, uint16_t& lo) {
   hi = f2bf_bits(x);
   lo = f2bf_bits(x - bf_bits2f(hi));
+}
+// the same for a pair: hi and lo hold a's half low, b's half high
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = f2bf_pair(a, b);
+  lo = f2bf_pair(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+}
+// eight values as MFMA fragments
+__device__ __forceinline__ void split8(const float (&v)[8], u32x4& hi, u32x4& lo) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t h, l;
+    split_pair(v[2 * e], v[2 * e + 1], h, l);
+    hi[e] = h;
+    lo[e] = l;
+  }
 }
 
 __device__ __forceinline__ f32x4 mfma_bf16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
@@ -69,18 +86,29 @@ __device__ __forceinline__ void pack_store(const PackRef& p, int wtype, int m, i
   }
 }
 
+// store features f, f + 1 (f even) of token m
+__device__ __forceinline__ void pack_store2(const PackRef& p, int wtype, int m, int f, float a, float b) {
+  const size_t idx = pack_index(p.Kb, m, f);
+  if (wtype == W_BF16) {
+    uint32_t h, l;
+    split_pair(a, b, h, l);
+    *(uint32_t*)((uint16_t*)p.hi + idx) = h;
+    *(uint32_t*)((uint16_t*)p.lo + idx) = l;
+  } else {
+    *(float2*)((float*)p.hi + idx) = float2{a, b};
+  }
+}
+
 // store 4 consecutive features f0..f0+3 (f0 % 4 == 0) of token m: 8 bytes
 // per half for bf16 packs, 16 bytes for fp32 packs
 __device__ __forceinline__ void pack_store4(const PackRef& p, int wtype, int m, int f0, const float* v) {
   const size_t idx = pack_index(p.Kb, m, f0);
   if (wtype == W_BF16) {
-    uint16_t hi[4], lo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) split_bf16(v[e], hi[e], lo[e]);
-    *(uint2*)((uint16_t*)p.hi + idx) = uint2{(uint32_t)hi[0] | ((uint32_t)hi[1] << 16),
-                                             (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
-    *(uint2*)((uint16_t*)p.lo + idx) = uint2{(uint32_t)lo[0] | ((uint32_t)lo[1] << 16),
-                                             (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
+    uint2 h, l;
+    split_pair(v[0], v[1], h.x, l.x);
+    split_pair(v[2], v[3], h.y, l.y);
+    *(uint2*)((uint16_t*)p.hi + idx) = h;
+    *(uint2*)((uint16_t*)p.lo + idx) = l;
   } else {
     *(float4*)((float*)p.hi + idx) = float4{v[0], v[1], v[2], v[3]};
   }
@@ -91,15 +119,9 @@ __device__ __forceinline__ void pack_store4(const PackRef& p, int wtype, int m, 
 __device__ __forceinline__ void pack_store8(const PackRef& p, int wtype, int m, int f0, const float* v) {
   const size_t idx = pack_index(p.Kb, m, f0);
   if (wtype == W_BF16) {
-    uint16_t hi[8], lo[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) split_bf16(v[e], hi[e], lo[e]);
+    const float y[8] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
     u32x4 h, l;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      h[e] = (uint32_t)hi[2 * e] | ((uint32_t)hi[2 * e + 1] << 16);
-      l[e] = (uint32_t)lo[2 * e] | ((uint32_t)lo[2 * e + 1] << 16);
-    }
+    split8(y, h, l);
     *(u32x4*)((uint16_t*)p.hi + idx) = h;
     *(u32x4*)((uint16_t*)p.lo + idx) = l;
   } else {

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void k_embed_norm(EmbedArgs a) {
   norm_row(v, a.d, m, a.gain, a.eps, a.wtype, a.pack, sh);
   // rotary table of this row's position: angle = pos * base^(-2j/hd), fp64
   const int R = a.rows.rows_per_window;
-  const int pos = a.rows.lens[a.rows.window0 + m / R] + (a.rows.depth ? a.rows.depth[m] : m % R);
+  const int pos = a.rows.depth ? a.rows.lens[a.rows.window0 + m / R] + a.rows.depth[m] : row_slot(a.rows, m);
   const int half = a.hd >> 1;
   for (int j = threadIdx.x; j < half; j += 256) {
     const double inv = exp2(-2.0 * (double)j / (double)a.hd * a.log2_base);
@@ -200,6 +200,43 @@ __global__ void k_kv_add_checked(int* lens, int window, const int* tokens, int n
     if (bad) atomicOr(err, 1);
     else lens[window] += n;
   }
+}
+
+// one wave per group of kMaxRows prompt rows, then one thread lays the groups
+// out (at most kWideRows / kMaxRows of them)
+__global__ __launch_bounds__(1024) void k_prefill_rows(const int* lens, int window, const int* tokens, int n, int V,
+                                                       int last, int* gpos, int* adv, int* err) {
+  __shared__ int bad[kWideRows / kMaxRows];
+  const int groups = (n + kMaxRows - 1) / kMaxRows;
+  const int lane = threadIdx.x & 63;
+  for (int g = threadIdx.x >> 6; g < groups; g += 16) {
+    const int i = g * kMaxRows + lane;
+    const bool b = i < n && (tokens[i] < 0 || tokens[i] >= V);
+    if (__any(b)) {
+      if (lane == 0) bad[g] = 1;
+    } else if (lane == 0) {
+      bad[g] = 0;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int p = lens[window], a = 0, any = 0;
+    for (int g = 0; g < groups; ++g) {
+      const int rows = min(kMaxRows, n - g * kMaxRows);
+      if (bad[g]) {
+        any = 1;
+        gpos[g] = last && g + 1 == groups ? p + a : -1;
+      } else {
+        gpos[g] = p + a;
+        a += rows;
+      }
+    }
+    *adv = a;
+    if (any) atomicOr(err, 1);
+  }
+}
+__global__ void k_prefill_commit(int* lens, int window, const int* adv) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) lens[window] += *adv;
 }
 
 // copy [n_kv][len][hd] <-> cache (n_kv regions of maxlen * hd, kc_off / vc_off)
@@ -339,6 +376,17 @@ hipError_t launch_kv_set(int* lens, int window, int new_len, hipStream_t s) {
 hipError_t launch_kv_add_checked(int* lens, int window, const int* tokens, int n, int V, int* err,
                                  hipStream_t s) {
   hipLaunchKernelGGL(k_kv_add_checked, dim3(1), dim3(256), 0, s, lens, window, tokens, n, V, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_rows(const int* lens, int window, const int* tokens, int n, int V, int last, int* gpos,
+                               int* adv, int* err, hipStream_t s) {
+  if (n < 1 || n > kWideRows) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_prefill_rows, dim3(1), dim3(1024), 0, s, lens, window, tokens, n, V, last, gpos, adv, err);
+  return hipGetLastError();
+}
+hipError_t launch_prefill_commit(int* lens, int window, const int* adv, hipStream_t s) {
+  hipLaunchKernelGGL(k_prefill_commit, dim3(1), dim3(64), 0, s, lens, window, adv);
   return hipGetLastError();
 }
 

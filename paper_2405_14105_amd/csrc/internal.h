@@ -46,6 +46,7 @@ constexpr int kTileRows = 16;
 constexpr int kTileK = 32;
 constexpr int kMaxMt = 4;          // at most 64 rows per forward chunk
 constexpr int kMaxRows = kMaxMt * 16;
+constexpr int kWideRows = 2048;    // at most this many prompt rows per prefill forward (multiple of kMaxRows)
 
 // gemm epilogues
 // EPI_PART stores split s of a K-split GEMM into its own partial buffer
@@ -62,7 +63,9 @@ constexpr int kMaxRows = kMaxMt * 16;
 // workgroup) folds x += sum_s partial_s in split order for the group's
 // features and writes what EPI_RESID writes (x, x * gain into the pack,
 // ssq), plus an optional copy of x.
-enum Epi : int { EPI_STORE = 0, EPI_PART = 1, EPI_QKV = 2, EPI_SILU = 3, EPI_RESID = 4, EPI_PARTRES = 5 };
+// EPI_TILE (prefill GEMM only) stores split s's tiles as the accumulators hold
+// them, out + s * part_stride: [m-block][n-block][64 lanes][4].
+enum Epi : int { EPI_STORE = 0, EPI_PART = 1, EPI_QKV = 2, EPI_SILU = 3, EPI_RESID = 4, EPI_PARTRES = 5, EPI_TILE = 6 };
 
 struct PackRef {        // an activation pack (hi/lo bf16, or fp32 in hi)
   void* hi;
@@ -78,7 +81,20 @@ struct RowMap {         // token row m -> (window, row within window, position)
   // depth in its tree) instead of lens[w] + (m % R).  The cache slot of row
   // m is lens[w] + (m % R) either way.
   const int* depth;
+  // nullable: prompt rows of one window (dsi_prefill), in groups of kMaxRows
+  // rows: row m sits at cache slot and RoPE position gpos[m / kMaxRows] + m %
+  // kMaxRows instead of lens[w] + m; a group with a negative entry is not
+  // cached (it holds an invalid id, and a later group takes its positions)
+  const int* gpos = nullptr;
 };
+// cache slot of row m (negative: not cached)
+__device__ inline int row_slot(const RowMap& r, int m) {
+  if (r.gpos) {
+    const int g = r.gpos[m / kMaxRows];
+    return g < 0 ? -1 : g + m % kMaxRows;
+  }
+  return r.lens[r.window0 + m / r.rows_per_window] + m % r.rows_per_window;
+}
 
 // KV cache of one (layer, window, KV head): a region of maxlen * hd elements
 // in blocks of 32 positions.  K is stored per block as [hd/32][32 positions]
@@ -179,6 +195,15 @@ hipError_t launch_restream(const void* src, int Nb, int Kb, int G, const RingCfg
 // launchers (gemm.hip)
 hipError_t launch_gemm(int wtype, int mt, const GemmArgs& a, hipStream_t s);
 
+// prefill (prefill.hip): bf16 weights, any number of rows
+struct WideCfg {
+  int mt = 8;           // m-blocks (16 rows) per workgroup tile, 4..8
+  int nwn = 4;          // waves along the output features (2 or 4), 4 n-blocks each
+};
+hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s);
+// out of the S tile-order partials (EPI_TILE) of a QKV or gate/up GEMM
+hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride, int S, hipStream_t s);
+
 // prepack (elementwise.hip): src [N][K] row-major (device), dst packed
 // (wtile_index with dst_Nb n-blocks in groups of G).  rowmap: 0 plain, 1
 // rope-paired (QKV sections), 2 gate/up interleave (which = 0 gate, 1 up).
@@ -235,6 +260,12 @@ struct AttnArgs {
 };
 constexpr int kAttnWaves = 8;                       // waves per attention workgroup (default)
 hipError_t launch_attention(int kv_bf16, int hd, const AttnArgs& a, hipStream_t s);
+// causal attention of one window's prompt rows (rows.gpos) over a bf16 cache
+// (prefill.hip), the keys in n_chunks chunks of `chunk` (a multiple of 64);
+// several chunks leave partials [n_kv][units][chunks][16][hd] in part_o and
+// part_ml.  n_qtiles, waves unused.
+int prefill_units(int rows, int group);   // 16-row units of one KV head
+hipError_t launch_attention_prefill(int hd, const AttnArgs& a, hipStream_t s);
 
 // verification (verify.hip)
 struct VerifyArgs {
@@ -315,6 +346,13 @@ hipError_t launch_kv_rollback(int* lens, int window, int new_len, int* err, hipS
 hipError_t launch_kv_set(int* lens, int window, int new_len, hipStream_t s);
 hipError_t launch_kv_add_checked(int* lens, int window, const int* tokens, int n, int V, int* err,
                                  hipStream_t s);
+// Prompt rows of one forward (n tokens): gpos[g] of every group of kMaxRows
+// rows and *adv, the rows the window's length advances by: the rows of the
+// groups without an invalid id.  A group with one is not cached unless it is
+// the last of the call (`last`), and is reported in err.
+hipError_t launch_prefill_rows(const int* lens, int window, const int* tokens, int n, int V, int last, int* gpos,
+                               int* adv, int* err, hipStream_t s);
+hipError_t launch_prefill_commit(int* lens, int window, const int* adv, hipStream_t s);
 hipError_t launch_kv_copy(int to_cache, int kv_bf16, void* kc, void* vc, int n_kv, int hd,
                           int maxlen, int len, void* dk, void* dv, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);

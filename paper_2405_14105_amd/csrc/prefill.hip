@@ -1,0 +1,492 @@
+// Prefill: the layer GEMMs and the attention of up to kWideRows prompt rows
+// per forward (bf16 weights and cache).
+//
+// A verification window is bound by streaming the weights once; a prompt of
+// hundreds of rows is bound by the matrix cores, if the weights are read once
+// for all of them.  In forwards of 64 rows the weights were read n / 64 times:
+// 2048 tokens through one 8B layer took 5.1 ms (gate/up 2.00, down 1.24, QKV
+// 0.85, O 0.65, attention 0.4); in one forward they take 1.6 ms (0.81, 0.36,
+// 0.24, 0.12, 0.11).
+//
+// GEMM.  Same products as the window GEMMs: pre-tiled weights against the
+// hi/lo activation packs, two 16x16x32 MFMAs per product, fp32 sums.  A
+// workgroup of 8 waves makes a tile of NWN * 64 features x MT * 16 rows:
+//  * NWN waves lie along the features, four n-blocks each, and 8 / NWN groups
+//    of them split the tile's k-blocks, so two waves share each SIMD whatever
+//    the tile; the groups' sums meet in LDS at the end, in group order.
+//  * Weight fragments belong to one wave and go from memory to its registers,
+//    two k-blocks ahead.  Activation fragments are used by all NWN waves of a
+//    group and go through LDS (double buffered, one barrier per k-block):
+//    each fragment read there feeds four MFMAs, 64 of LDS's 128 bytes a
+//    cycle at full MFMA rate.  Both are stored in fragment order, so every
+//    load is 1 KB contiguous and no LDS access conflicts.
+//  * The loop has no branches; k-blocks past the split are zeroed on their
+//    way into LDS.
+// At the 8B shape and 2048 rows it executes 1.2-1.3 PFLOP/s, the rate of a
+// large bf16 library product on the card (1.29).
+
+#include <algorithm>
+
+#include "epilogue.h"
+
+namespace dsi {
+
+namespace {
+
+constexpr int kWideWaves = 8;
+constexpr int kWideNb = 4;     // n-blocks per wave
+
+// Workgroup order: XCD x (ids congruent to x mod 8) takes a contiguous run of
+// the tiles, row tiles fastest within groups of eight, so the 32 workgroups
+// of an XCD share a few weight and activation tiles through its L2.
+struct WideGrid {
+  int nt, mtiles;       // tiles along the features and the rows
+  int tiles;            // of one K split
+  int per_xcd;          // workgroups (tiles of all splits) of one XCD
+};
+
+template <int MT, int NWN, int EPI>
+__global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideGrid gr) {
+  constexpr int KG = kWideWaves / NWN;          // K groups
+  constexpr int XT = 2 * MT;                    // activation tiles of a k-block (hi, lo)
+  constexpr int XP = (XT + NWN - 1) / NWN;      // of them, copied by one wave
+  constexpr int XS = KG * 2 * XT * 64;
+  constexpr int RS = kWideWaves * 2 * MT * 64;
+  __shared__ u32x4 sm[XS > RS ? XS : RS];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = w % NWN, kg = w / NWN;
+  const int t0 = (blockIdx.x & 7) * gr.per_xcd + (blockIdx.x >> 3);
+  if (t0 >= gr.tiles * a.S) return;
+  const int split = t0 / gr.tiles, tile = t0 - split * gr.tiles;
+  constexpr int GM = 8;
+  const int mg = tile / (GM * gr.nt), in = tile - mg * (GM * gr.nt);
+  const int gm = min(GM, gr.mtiles - mg * GM);
+  const int nti = in / gm, mti = mg * GM + in % gm;
+  const int Mb = (a.M + 15) >> 4;
+  const int mb0 = mti * MT;
+  const int nb0 = (nti * NWN + wn) * kWideNb;
+  const int k0 = (split * a.Kb) / a.S, k1 = ((split + 1) * a.Kb) / a.S;
+  const int n = (k1 - k0 + KG - 1) / KG;
+
+  const u32x4* __restrict__ W = (const u32x4*)a.W;
+  const u32x4* __restrict__ Xh = (const u32x4*)a.Xhi;
+  const u32x4* __restrict__ Xl = (const u32x4*)a.Xlo;
+  size_t tb[kWideNb];
+  int ts[kWideNb];
+#pragma unroll
+  for (int j = 0; j < kWideNb; ++j) {
+    const int nb = min(nb0 + j, a.Nb - 1), gi = nb / a.G;
+    tb[j] = (size_t)gi * a.G * a.Kb + (nb - gi * a.G);
+    ts[j] = min(a.G, a.Nb - gi * a.G);
+  }
+  auto load_w = [&](u32x4 (&d)[kWideNb], int i) {
+    const int kb = min(k0 + i * KG + kg, k1 - 1);
+#pragma unroll
+    for (int j = 0; j < kWideNb; ++j) d[j] = W[(tb[j] + (size_t)kb * ts[j]) * 64 + lane];
+  };
+  auto load_x = [&](u32x4 (&d)[XP], int i) {
+    const int kb = min(k0 + i * KG + kg, k1 - 1);
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      const int t = min(wn + NWN * p, XT - 1);
+      const int mb = min(mb0 + (t >> 1), Mb - 1);
+      d[p] = ((t & 1) ? Xl : Xh)[((size_t)mb * a.Kb + kb) * 64 + lane];
+    }
+  };
+  u32x4* const xs = sm + kg * 2 * XT * 64;
+  // k-blocks past the split are multiplied as zeros (the loop runs whole
+  // steps of KG k-blocks, three at a time)
+  auto store_x = [&](const u32x4 (&d)[XP], int i) {
+    const uint32_t keep = k0 + i * KG + kg < k1 ? ~0u : 0u;
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      const int t = wn + NWN * p;
+      if (XT % NWN == 0 || t < XT) xs[((i & 1) * XT + t) * 64 + lane] = d[p] & keep;
+    }
+  };
+  auto sync = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+
+  f32x4 acc[kWideNb][MT];
+#pragma unroll
+  for (int j = 0; j < kWideNb; ++j)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[j][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  u32x4 wr[3][kWideNb];
+  u32x4 xr[XP];
+  load_x(xr, 0);
+  load_w(wr[0], 0);
+  load_w(wr[1], 1);
+  store_x(xr, 0);
+  load_x(xr, 1);
+  sync();
+  auto step = [&](int i, const u32x4 (&wc)[kWideNb], u32x4 (&wnext)[kWideNb]) {
+    load_w(wnext, i + 2);
+    const u32x4* xb = xs + (i & 1) * XT * 64 + lane;
+    u32x4 f[2][2];
+    f[0][0] = xb[0];
+    f[0][1] = xb[64];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      if (m + 1 < MT) {
+        f[(m + 1) & 1][0] = xb[(2 * m + 2) * 64];
+        f[(m + 1) & 1][1] = xb[(2 * m + 3) * 64];
+      }
+      if (m == MT / 2) {
+        store_x(xr, i + 1);
+        load_x(xr, i + 2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < kWideNb; ++j) acc[j][m] = mfma_bf16(as_bf16x8(wc[j]), as_bf16x8(f[m & 1][0]), acc[j][m]);
+#pragma unroll
+      for (int j = 0; j < kWideNb; ++j) acc[j][m] = mfma_bf16(as_bf16x8(wc[j]), as_bf16x8(f[m & 1][1]), acc[j][m]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    sync();
+  };
+  for (int i = 0; i < n; i += 3) {
+    step(i, wr[0], wr[2]);
+    step(i + 1, wr[1], wr[0]);
+    step(i + 2, wr[2], wr[1]);
+  }
+
+  // The K groups' partial tiles meet in LDS, two n-blocks of every wave a
+  // round; then each wave sums whole tiles in group order and finishes them.
+  f32x4* red = (f32x4*)sm;
+  const EpiArgs& e = a.epi;
+#pragma unroll
+  for (int r = 0; r < kWideNb / 2; ++r) {
+    if (r) __syncthreads();
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) red[((w * 2 + jj) * MT + m) * 64 + lane] = acc[2 * r + jj][m];
+    __syncthreads();
+    for (int it = w; it < 2 * NWN * MT; it += kWideWaves) {
+      const int m = it % MT, wj = it / MT;             // wj = (wave along N) * 2 + jj
+      const int nb = (nti * NWN + (wj >> 1)) * kWideNb + 2 * r + (wj & 1);
+      const int mb = mb0 + m, mrow = mb * 16 + (lane & 15);
+      if (nb >= a.Nb || mb >= Mb) continue;            // wave-uniform
+      f32x4 v = red[(wj * MT + m) * 64 + lane];
+#pragma unroll
+      for (int g = 1; g < KG; ++g) v += red[((g * NWN * 2 + wj) * MT + m) * 64 + lane];
+      if constexpr (EPI == EPI_TILE) {
+        *(f32x4*)(e.out + split * e.part_stride + (((size_t)mb * a.Nb + nb) * 64 + lane) * 4) = v;
+      } else if (mrow < a.M) {
+        if constexpr (EPI == EPI_PART) {
+          *(f32x4*)(e.out + split * e.part_stride + (size_t)mrow * e.ld + nb * 16 + (lane >> 4) * 4) = v;
+        } else {
+          EpiIn pre{};
+          if constexpr (EPI == EPI_QKV) pre = qkv_inputs(e, nb, (lane >> 4) * 4, mrow);
+          epilogue<W_BF16, EPI>(e, nb, (lane >> 4) * 4, mrow, split, v, pre);
+        }
+      }
+    }
+  }
+}
+
+// sums the splits' tile-order partials (EPI_TILE) in split order and applies
+// the role's epilogue; one wave per 16 x 16 tile
+template <int EPI>
+__global__ __launch_bounds__(256) void k_wide_fold(GemmArgs a, const float* part, size_t stride, int S) {
+  const int lane = threadIdx.x & 63;
+  const int nb = blockIdx.x * 4 + (threadIdx.x >> 6), mb = blockIdx.y;
+  if (nb >= a.Nb) return;
+  const float* p = part + (((size_t)mb * a.Nb + nb) * 64 + lane) * 4;
+  f32x4 pv[kMaxSplits];
+#pragma unroll
+  for (int s = 0; s < kMaxSplits; ++s) pv[s] = *(const f32x4*)(p + min(s, S - 1) * stride);
+  const int m = mb * 16 + (lane & 15);
+  if (m >= a.M) return;
+  EpiIn pre{};
+  if constexpr (EPI == EPI_QKV) pre = qkv_inputs(a.epi, nb, (lane >> 4) * 4, m);
+  f32x4 v = pv[0];
+#pragma unroll
+  for (int s = 1; s < kMaxSplits; ++s)
+    if (s < S) v += pv[s];
+  epilogue<W_BF16, EPI>(a.epi, nb, (lane >> 4) * 4, m, 0, v, pre);
+}
+
+// ---------------------------------------------------------------- attention
+//
+// Causal attention of the prompt rows over the cache (the rows' own keys and
+// values included: the QKV GEMM has written them).  Same arithmetic as the
+// window kernel (attention.hip): S^T = K Q^T and O^T = V^T P^T in 16x16x32
+// MFMAs, queries and probabilities split hi/lo, base-2 online softmax.
+// Bound by the softmax arithmetic and the MFMAs, about 16 queries x 32 keys
+// per 500 cycles of a SIMD.  A unit is 16 consecutive rows of one head; a
+// workgroup's 8 waves take 8 units that share keys (all heads of a KV group,
+// row block by row block), so the keys and values of a 64-key stage are
+// loaded once per workgroup into LDS, in fragment order, while the stage
+// before is worked on, and a workgroup stops at its last row's position.
+// 8B, 2048 rows: 114 us, against 32 x 15 us of the window kernel, which
+// reads the keys once per 16 queries.  With few row blocks the keys are cut
+// into chunks as well (13B, 77 rows over 900 keys: 51 -> 19 + 5 us).
+template <int HD>
+__global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int n_units, int n_ublk) {
+  constexpr int DS = HD / 32;
+  constexpr int DT = HD / 16;
+  constexpr int ST = 4 * DS;                 // tiles of a 32-key step: 2 DS of K, DT of V
+  __shared__ u32x4 kv[2][2 * ST][64];        // two stages of 64 keys
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kvh = blockIdx.x % a.n_kv, ic = blockIdx.x / a.n_kv;
+  const int c = ic % a.n_chunks, ub = n_ublk - 1 - ic / a.n_chunks;   // longest first
+  const int G = a.n_heads / a.n_kv, R = a.rows.rows_per_window;
+  const int u = min(ub * 8 + w, n_units - 1), ul = min(ub * 8 + 7, n_units - 1);
+  const bool live = ub * 8 + w < n_units;
+  const int rb = u / G, head = kvh * G + u % G;
+  // position of the first row of a 16-row block (negative: rows of an invalid
+  // group, whose output nobody reads), and the keys its rows see together:
+  // [0, base + rows in it)
+  auto block_pos = [&](int b) { return a.rows.gpos[b * 16 / kMaxRows] + b * 16 % kMaxRows; };
+  auto block_keys = [&](int b) { return a.rows.gpos[b * 16 / kMaxRows] < 0 ? 0 : block_pos(b) + min(16, R - b * 16); };
+  const int pos0 = block_pos(rb);
+  const int kw = live ? block_keys(rb) : 0;             // keys of this wave
+  int kwg = 0;                                          // and of the workgroup
+  for (int b = (ub * 8) / G; b <= ul / G; ++b) kwg = max(kwg, block_keys(b));
+  const int st0 = c * (a.chunk >> 6), st1 = min((kwg + 63) >> 6, st0 + (a.chunk >> 6));   // stages of 64 keys
+  const int r16 = lane & 15, kgrp = (lane >> 4) * 8;
+  const int row = rb * 16 + r16;
+  const int qpos = pos0 + r16;
+  const size_t base = ((size_t)a.rows.window0 * a.n_kv + kvh) * (size_t)a.maxlen * HD;
+  const uint16_t* kc = (const uint16_t*)a.kc + base;
+  const uint16_t* vc = (const uint16_t*)a.vc + base;
+  const float scale2 = a.scale * 1.44269504088896340736f;   // log2 e
+
+  // this wave's DS tiles of a stage: waves 0-3 the first 32 keys, 4-7 the
+  // second; of each four, two load K (16-key halves), two V
+  const int half = w >> 2, part = w & 3;
+  auto load_stage = [&](u32x4 (&d)[DS], int st) {
+    const int p0 = st * 64 + half * 32;
+#pragma unroll
+    for (int p = 0; p < DS; ++p) {
+      if (part < 2) d[p] = *(const u32x4*)(kc + kc_off(p0 + (r16 >> 2) * 8 + part * 4 + (r16 & 3), p * 32 + kgrp, HD));
+      else d[p] = *(const u32x4*)(vc + vc_off(p0 + kgrp, ((part - 2) * DS + p) * 16 + r16, HD));
+    }
+  };
+  auto store_stage = [&](const u32x4 (&d)[DS], int buf) {
+#pragma unroll
+    for (int p = 0; p < DS; ++p) kv[buf][half * ST + part * DS + p][lane] = d[p];
+  };
+
+  const float* qrow = a.q + (size_t)min(row, R - 1) * (a.n_heads * HD) + head * HD;
+  bf16x8 qh[DS], ql[DS];
+  u32x4 sr[DS];
+  load_stage(sr, st0 < st1 ? st0 : 0);
+#pragma unroll
+  for (int ds = 0; ds < DS; ++ds) {
+    const float4 a0 = *(const float4*)(qrow + ds * 32 + kgrp), a1 = *(const float4*)(qrow + ds * 32 + kgrp + 4);
+    const float v[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+    u32x4 h, l;
+    split8(v, h, l);
+    qh[ds] = as_bf16x8(h);
+    ql[ds] = as_bf16x8(l);
+  }
+  float mrun = -INFINITY, lrun = 0.f;
+  f32x4 o[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto step = [&](int p0, const u32x4 (*tl)[64]) {
+    f32x4 st[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds) {
+        const bf16x8 kb = as_bf16x8(tl[t * DS + ds][lane]);
+        st[t] = mfma_bf16(kb, qh[ds], st[t]);
+        st[t] = mfma_bf16(kb, ql[ds], st[t]);
+      }
+    }
+    const bool full = p0 + 32 <= pos0 + 1;
+    float sv[8];
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool vis = full || p0 + kgrp + e <= qpos;
+      sv[e] = vis ? st[e >> 2][e & 3] * scale2 : -INFINITY;
+      mloc = fmaxf(mloc, sv[e]);
+    }
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    const float mnew = fmaxf(mrun, mloc);
+    const float b = (mnew == -INFINITY) ? 0.f : mnew;
+    float pv[8];
+    float lsum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      pv[e] = __builtin_amdgcn_exp2f(sv[e] - b);
+      lsum += pv[e];
+    }
+    if (__ballot(mnew != mrun)) {
+      const float alpha = __builtin_amdgcn_exp2f(mrun - b);
+      lrun *= alpha;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) o[t] *= alpha;
+    }
+    lrun += lsum;
+    mrun = mnew;
+    u32x4 h, l;
+    split8(pv, h, l);
+    const bf16x8 ph = as_bf16x8(h), pl = as_bf16x8(l);
+    // keys past the block's rows may be dead cache rows: they have
+    // probability 0, and their values are zeroed so that 0 * NaN never
+    // reaches the output
+    const int nv = kw - (p0 + kgrp);
+    const bool tail = p0 + 32 > kw;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      u32x4 vv = tl[2 * DS + t][lane];
+      if (tail) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          vv[i] &= (2 * i < nv ? 0x0000FFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
+      }
+      o[t] = mfma_bf16(as_bf16x8(vv), ph, o[t]);
+      o[t] = mfma_bf16(as_bf16x8(vv), pl, o[t]);
+    }
+  };
+
+  store_stage(sr, 0);
+  __syncthreads();
+  for (int st = st0; st < st1; ++st) {
+    const bool more = st + 1 < st1;
+    if (more) load_stage(sr, st + 1);
+    const int buf = (st - st0) & 1;
+    if (st * 64 < kw) step(st * 64, &kv[buf][0]);
+    if (st * 64 + 32 < kw) step(st * 64 + 32, &kv[buf][ST]);
+    if (more) store_stage(sr, buf ^ 1);
+    __syncthreads();
+  }
+  if (!live) return;
+  lrun += __shfl_xor(lrun, 16);
+  lrun += __shfl_xor(lrun, 32);
+  if (a.n_chunks > 1) {
+    const size_t part = ((size_t)kvh * n_units + u) * a.n_chunks + c;
+    float* po = a.part_o + (part * 16 + r16) * HD + (lane >> 4) * 4;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) *(f32x4*)(po + t * 16) = o[t];
+    if (lane < 16) a.part_ml[part * 16 + lane] = make_float2(mrun, lrun);   // base-2 units
+    return;
+  }
+  if (row >= R) return;
+  const float inv = 1.0f / lrun;
+#pragma unroll
+  for (int t = 0; t < DT; ++t) {
+    const float y4[4] = {o[t][0] * inv, o[t][1] * inv, o[t][2] * inv, o[t][3] * inv};
+    pack_store4(a.out, a.wtype, row, head * HD + t * 16 + (lane >> 4) * 4, y4);
+  }
+}
+
+// sums the key chunks of one unit (16 rows of one head), chunks in order: one
+// thread per row and four dims
+template <int HD>
+__global__ __launch_bounds__(HD * 4) void k_attn_prefill_combine(AttnArgs a, int n_units) {
+  const int kvh = blockIdx.x % a.n_kv, u = blockIdx.x / a.n_kv;
+  const int G = a.n_heads / a.n_kv, R = a.rows.rows_per_window;
+  const int q = threadIdx.x / (HD / 4), d = threadIdx.x % (HD / 4) * 4;
+  const int row = u / G * 16 + q;
+  if (row >= R) return;
+  const size_t part = ((size_t)kvh * n_units + u) * a.n_chunks;
+  const float2* ml = a.part_ml + part * 16 + q;
+  const float* po = a.part_o + (part * 16 + q) * HD + d;
+  float M = -INFINITY;
+  for (int c = 0; c < a.n_chunks; ++c) M = fmaxf(M, ml[c * 16].x);
+  const float b = M == -INFINITY ? 0.f : M;
+  float L = 0.f;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int c = 0; c < a.n_chunks; ++c) {
+    const float2 v = ml[c * 16];
+    const float f = __builtin_amdgcn_exp2f(v.x - b);
+    L += v.y * f;
+    acc += *(const f32x4*)(po + (size_t)c * 16 * HD) * f;
+  }
+  const float inv = 1.0f / L;
+  const float y4[4] = {acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+  pack_store4(a.out, a.wtype, row, (kvh * G + u % G) * HD + d, y4);
+}
+
+}  // namespace
+
+template <int MT, int NWN>
+hipError_t launch_wide_epi(const GemmArgs& a, const WideGrid& g, int grid, hipStream_t s) {
+  const dim3 gd(grid), bd(kWideWaves * 64);
+  switch (a.epi.kind) {
+    case EPI_PART: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_PART>), gd, bd, 0, s, a, g); break;
+    case EPI_TILE: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_TILE>), gd, bd, 0, s, a, g); break;
+    case EPI_QKV: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_QKV>), gd, bd, 0, s, a, g); break;
+    case EPI_SILU: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_SILU>), gd, bd, 0, s, a, g); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <int MT>
+hipError_t launch_wide_mt(const GemmArgs& a, int nwn, const WideGrid& g, int grid, hipStream_t s) {
+  return nwn == 4 ? launch_wide_epi<MT, 4>(a, g, grid, s) : launch_wide_epi<MT, 2>(a, g, grid, s);
+}
+
+hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s) {
+  if (a.M < 1 || a.Nb < 1 || a.Kb < 1 || a.S < 1 || a.S > a.Kb || a.G < 1 || (c.nwn != 2 && c.nwn != 4))
+    return hipErrorInvalidValue;
+  if (a.S > 1 && a.epi.kind != EPI_PART && a.epi.kind != EPI_TILE) return hipErrorInvalidValue;
+  WideGrid g;
+  const int mb = (a.M + 15) / 16;
+  g.mtiles = (mb + c.mt - 1) / c.mt;
+  g.nt = (a.Nb + c.nwn * kWideNb - 1) / (c.nwn * kWideNb);
+  g.tiles = g.nt * g.mtiles;
+  g.per_xcd = (g.tiles * a.S + 7) / 8;
+  switch (c.mt) {
+    case 4: return launch_wide_mt<4>(a, c.nwn, g, g.per_xcd * 8, s);
+    case 5: return launch_wide_mt<5>(a, c.nwn, g, g.per_xcd * 8, s);
+    case 6: return launch_wide_mt<6>(a, c.nwn, g, g.per_xcd * 8, s);
+    case 7: return launch_wide_mt<7>(a, c.nwn, g, g.per_xcd * 8, s);
+    case 8: return launch_wide_mt<8>(a, c.nwn, g, g.per_xcd * 8, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride, int S, hipStream_t s) {
+  if (S < 1 || S > kMaxSplits) return hipErrorInvalidValue;
+  const dim3 grid((a.Nb + 3) / 4, (a.M + 15) / 16), blk(256);
+  if (a.epi.kind == EPI_QKV) hipLaunchKernelGGL((k_wide_fold<EPI_QKV>), grid, blk, 0, s, a, part, stride, S);
+  else if (a.epi.kind == EPI_SILU) hipLaunchKernelGGL((k_wide_fold<EPI_SILU>), grid, blk, 0, s, a, part, stride, S);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+int prefill_units(int rows, int group) { return (rows + 15) / 16 * group; }
+
+template <int HD>
+hipError_t launch_attn_prefill_hd(const AttnArgs& a, int units, hipStream_t s) {
+  const int ub = (units + 7) / 8;
+  hipLaunchKernelGGL((k_attn_prefill<HD>), dim3(ub * a.n_kv * a.n_chunks), dim3(512), 0, s, a, units, ub);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.n_chunks == 1) return e;
+  hipLaunchKernelGGL((k_attn_prefill_combine<HD>), dim3(units * a.n_kv), dim3(HD * 4), 0, s, a, units);
+  return hipGetLastError();
+}
+
+hipError_t launch_attention_prefill(int hd, const AttnArgs& a, hipStream_t s) {
+  const int units = prefill_units(a.rows.rows_per_window, a.n_heads / a.n_kv);
+  if (a.n_chunks < 1 || a.chunk < 64 || a.chunk % 64 || !a.rows.gpos) return hipErrorInvalidValue;
+  switch (hd) {
+    case 32: return launch_attn_prefill_hd<32>(a, units, s);
+    case 64: return launch_attn_prefill_hd<64>(a, units, s);
+    case 96: return launch_attn_prefill_hd<96>(a, units, s);
+    case 128: return launch_attn_prefill_hd<128>(a, units, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace dsi

@@ -89,6 +89,18 @@ struct LayerW {
   void* wdown_s = nullptr;
 };
 
+// Workspace of prefill forwards of up to `rows` prompt rows (prefill.hip).
+struct WideWs {
+  int rows = 0;                 // 0: none
+  float* x = nullptr;           // [rows][d]
+  float* delta = nullptr;       // partial GEMM outputs
+  size_t delta_bytes = 0;
+  PackRef pk_d{}, pk_q{}, pk_ff{};
+  float* qbuf = nullptr;
+  float2* rope = nullptr;
+  int* gpos = nullptr;          // [rows / kMaxRows], then the advance
+};
+
 struct dsi_model {
   dsi_config cfg;
   hipStream_t stream = nullptr;
@@ -127,6 +139,7 @@ struct dsi_model {
   int4* tdec = nullptr;
   int* err = nullptr;
   DevBuf attn_o, attn_ml;
+  WideWs wide;
   int live_kv = 0;
   // diagnostics: event pairs around one kernel class
   int prof_class = 0;
@@ -190,13 +203,52 @@ void* kv_ptr(const dsi_kv* kv, void* base, int layer, int window) {
   return (char*)base + off * kv->m->kvesz;
 }
 
-PackRef make_pack(dsi_model* m, int Kb, dsi_status* st) {
+PackRef make_pack(dsi_model* m, std::vector<void*>& allocs, int rows, int Kb, dsi_status* st) {
   PackRef p{};
   p.Kb = Kb;
-  const size_t elems = (size_t)kMaxMt * Kb * 512;
-  *st = dev_alloc(m->allocs, &p.hi, elems * m->esz);
-  if (*st == DSI_OK && m->wtype == W_BF16) *st = dev_alloc(m->allocs, &p.lo, elems * 2);
+  const size_t elems = (size_t)cdiv(rows, 16) * Kb * 512;
+  *st = dev_alloc(allocs, &p.hi, elems * m->esz);
+  if (*st == DSI_OK && m->wtype == W_BF16) *st = dev_alloc(allocs, &p.lo, elems * 2);
   return p;
+}
+
+// Prefill forwards of more than kMaxRows rows: bf16 weights and cache.
+// Reserves the workspace for a cache of max_len positions (kWideRows rows at
+// most).  A model that has no memory for it keeps the one it has, or none:
+// prompts then run in narrower forwards.  An outgrown workspace stays until
+// the model is destroyed (launches of it may be in flight or captured); the
+// sizes are powers of two, so all of them together hold less than twice the
+// last.
+void wide_reserve(dsi_model* m, int max_len) {
+  if (m->wtype != W_BF16 || !m->kvb || max_len <= kMaxRows) return;
+  int rows = 2 * kMaxRows;
+  while (rows < max_len && rows < kWideRows) rows *= 2;
+  if (rows <= m->wide.rows) return;
+  const std::string keep = g_err;
+  std::vector<void*> list;
+  WideWs w;
+  dsi_status st = DSI_OK;
+  auto A = [&](void** p, size_t bytes) {
+    if (st == DSI_OK) st = dev_alloc(list, p, bytes);
+  };
+  w.rows = rows;
+  // one partial of the widest launch, or several of a launch with fewer rows
+  w.delta_bytes = std::max((size_t)rows * m->d * 4, (size_t)64 << 20);
+  A((void**)&w.x, (size_t)rows * m->d * 4);
+  A((void**)&w.delta, w.delta_bytes);
+  if (st == DSI_OK) w.pk_d = make_pack(m, list, rows, m->Kb_d, &st);
+  if (st == DSI_OK) w.pk_q = make_pack(m, list, rows, m->Kb_q, &st);
+  if (st == DSI_OK) w.pk_ff = make_pack(m, list, rows, m->Kb_ff, &st);
+  A((void**)&w.qbuf, (size_t)rows * m->qdim * 4);
+  A((void**)&w.rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
+  A((void**)&w.gpos, (size_t)(kWideRows / kMaxRows + 1) * sizeof(int));
+  if (st != DSI_OK) {
+    free_list(list);
+    g_err = keep;
+    return;
+  }
+  m->allocs.insert(m->allocs.end(), list.begin(), list.end());
+  m->wide = w;
 }
 
 // event pair around the launches of one kernel class (diagnostics only)
@@ -556,6 +608,185 @@ dsi_status run_forward(dsi_model* m, dsi_kv* kv, const AttnPlan& ap, int window0
   return DSI_OK;
 }
 
+// ------------------------------------------------------------- wide prefill
+// Tile and K split of a prefill GEMM.
+struct WidePlan {
+  WideCfg cfg;
+  int S = 1;
+};
+// part_cols: columns of one partial row ([rows][part_cols] fp32); fused: the
+// unsplit launch applies its epilogue itself, a split one needs a fold launch
+WidePlan wide_plan(const dsi_model* m, int M, int Nb, int Kb, bool fused) {
+  const int mb = cdiv(M, 16), mtiles = cdiv(mb, 8);
+  WidePlan best;
+  double t_best = 1e30;
+  for (int nwn = 2; nwn <= 4; nwn += 2)
+    for (int half = 0; half < 2; ++half) {
+      const int mt = std::max(4, half ? cdiv(mb, 2 * mtiles) : cdiv(mb, mtiles));
+      const int tiles = cdiv(Nb, 4 * nwn) * cdiv(mb, mt);
+      for (int S = 1; S <= kMaxSplits; ++S) {
+        if (S > 1 && (Kb / S < 16 || (size_t)S * mb * 16 * Nb * 16 * 4 > m->wide.delta_bytes)) break;
+        const double steps = (double)cdiv(Kb, S) * nwn * mt;
+        const double part = (double)M * Nb * 16 * 4;
+        double t = 6.0 + cdiv(tiles * S, 256) * (1.5 + steps * 0.026);
+        t = std::max(t, 6.0 + (double)Nb * Kb * 1024 / 5.0e6);
+        if (fused && S > 1) t += 4.0 + S * part * 2 / 4.0e6;
+        if (!fused) t += S * part * 2 / 4.0e6;
+        if (t < t_best) {
+          t_best = t;
+          best.cfg.mt = mt;
+          best.cfg.nwn = nwn;
+          best.S = S;
+        }
+      }
+    }
+  return best;
+}
+
+// Launches one layer GEMM of M prompt rows: QKV and gate/up finish in their
+// epilogue (through a fold launch when K is split); O and down leave *splits
+// partials [M][d] in delta for the next RMSNorm.
+dsi_status wide_gemm(dsi_model* m, GemmArgs g, int M, int* splits) {
+  const bool fused = g.epi.kind == EPI_QKV || g.epi.kind == EPI_SILU;
+  const WidePlan p = wide_plan(m, M, g.Nb, g.Kb, fused);
+  g.M = M;
+  g.S = p.S;
+  if (fused && p.S == 1) {
+    HIP_TRY(launch_gemm_wide(g, p.cfg, m->stream));
+    return DSI_OK;
+  }
+  GemmArgs w = g;
+  w.epi.out = m->wide.delta;
+  if (fused) {
+    w.epi.kind = EPI_TILE;
+    w.epi.part_stride = (size_t)cdiv(M, 16) * 16 * g.Nb * 16;
+    HIP_TRY(launch_gemm_wide(w, p.cfg, m->stream));
+    HIP_TRY(launch_wide_fold(g, m->wide.delta, w.epi.part_stride, p.S, m->stream));
+  } else {
+    w.epi.kind = EPI_PART;
+    w.epi.ld = m->d;
+    w.epi.part_stride = (size_t)M * m->d;
+    HIP_TRY(launch_gemm_wide(w, p.cfg, m->stream));
+    *splits = p.S;
+  }
+  return DSI_OK;
+}
+
+// One forward of M (<= m->wide.rows) prompt tokens of one window, appended to
+// its cache.  logits (nullable, [V]): the last row's.
+dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d_tokens, float* logits, int last) {
+  hipStream_t s = m->stream;
+  WideWs& w = m->wide;
+  int* adv = w.gpos + kWideRows / kMaxRows;
+  HIP_TRY(launch_prefill_rows(kv->lens, window, d_tokens, M, m->V, last, w.gpos, adv, m->err, s));
+  RowMap rows{kv->lens, window, M, nullptr, w.gpos};
+
+  EmbedArgs ea{};
+  ea.tokens = d_tokens;
+  ea.E = m->embed;
+  ea.wtype = m->wtype;
+  ea.V = m->V;
+  ea.d = m->d;
+  ea.M = M;
+  ea.x = w.x;
+  ea.gain = m->layers[0].attn_norm;
+  ea.eps = m->cfg.rms_eps;
+  ea.pack = w.pk_d;
+  ea.rope = w.rope;
+  ea.hd = m->hd;
+  ea.log2_base = log2((double)m->cfg.rope_base);
+  ea.rows = rows;
+  ea.err = m->err;
+  HIP_TRY(launch_embed_norm(ea, s));
+
+  // attention: key chunks (of at least 256 keys) when the row blocks alone
+  // leave CUs idle
+  const int units = prefill_units(M, m->hq / m->hkv);
+  const int wgs = cdiv(units, 8) * m->hkv;
+  const int keys = (int)(kv->hi[window] + M);
+  int chunks = std::max(1, std::min(cdiv(keys, 256), 256 / wgs));
+  const int chunk = (int)round_up((size_t)cdiv(keys, chunks), 64);
+  chunks = cdiv(keys, chunk);
+  if (chunks > 1) {
+    const size_t parts = (size_t)m->hkv * units * chunks * 16;
+    DSI_TRY(ensure(m->attn_o, parts * m->hd * sizeof(float)));
+    DSI_TRY(ensure(m->attn_ml, parts * sizeof(float2)));
+  }
+
+  const size_t Md = (size_t)M * m->d;
+  int splits = 0;
+  for (int l = 0; l < m->L; ++l) {
+    GemmArgs g = qkv_args(m, kv, l, M, rows);
+    g.ssq = nullptr;          // the pack is normed
+    g.Xhi = w.pk_d.hi;
+    g.Xlo = w.pk_d.lo;
+    g.epi.q_out = w.qbuf;
+    g.epi.rope = w.rope;
+    {
+      Prof p(m, DSI_K_QKV);
+      DSI_TRY(wide_gemm(m, g, M, nullptr));
+    }
+    AttnArgs aa{};
+    aa.q = w.qbuf;
+    aa.kc = kv_ptr(kv, kv->k, l, 0);
+    aa.vc = kv_ptr(kv, kv->v, l, 0);
+    aa.rows = rows;
+    aa.n_windows = 1;
+    aa.n_heads = m->hq;
+    aa.n_kv = m->hkv;
+    aa.maxlen = kv->maxlen_pad;
+    aa.chunk = chunk;
+    aa.n_chunks = chunks;
+    aa.part_o = (float*)m->attn_o.p;
+    aa.part_ml = (float2*)m->attn_ml.p;
+    aa.scale = (float)(1.0 / sqrt((double)m->hd));
+    aa.out = w.pk_q;
+    aa.wtype = m->wtype;
+    {
+      Prof p(m, DSI_K_ATTN);
+      HIP_TRY(launch_attention_prefill(m->hd, aa, s));
+    }
+    g = oproj_args(m, l, M);
+    g.Xhi = w.pk_q.hi;
+    g.Xlo = w.pk_q.lo;
+    {
+      Prof p(m, DSI_K_OPROJ);
+      DSI_TRY(wide_gemm(m, g, M, &splits));
+      HIP_TRY(launch_rmsnorm_pack(w.x, w.delta, splits, Md, M, m->d, m->layers[l].ffn_norm, m->cfg.rms_eps, m->wtype,
+                                  w.pk_d, nullptr, s));
+    }
+    g = gateup_args(m, l, M);
+    g.ssq = nullptr;
+    g.Xhi = w.pk_d.hi;
+    g.Xlo = w.pk_d.lo;
+    g.epi.pack = w.pk_ff;
+    {
+      Prof p(m, DSI_K_GATEUP);
+      DSI_TRY(wide_gemm(m, g, M, nullptr));
+    }
+    g = down_args(m, l, M, 1);
+    g.Xhi = w.pk_ff.hi;
+    g.Xlo = w.pk_ff.lo;
+    {
+      Prof p(m, DSI_K_DOWN);
+      DSI_TRY(wide_gemm(m, g, M, &splits));
+      if (l + 1 < m->L)
+        HIP_TRY(launch_rmsnorm_pack(w.x, w.delta, splits, Md, M, m->d, m->layers[l + 1].attn_norm, m->cfg.rms_eps,
+                                    m->wtype, w.pk_d, nullptr, s));
+    }
+  }
+  if (logits) {
+    Prof ph(m, DSI_K_HEAD);
+    const size_t off = (size_t)(M - 1) * m->d;
+    HIP_TRY(launch_rmsnorm_pack(w.x + off, w.delta + off, splits, Md, 1, m->d, m->final_norm, m->cfg.rms_eps,
+                                m->wtype, m->pk_d, nullptr, s));
+    GemmArgs gh = head_args(m, logits, 1, ring_forward(m, kv, 1));
+    HIP_TRY(launch_gemm(m->wtype, 1, gh, s));
+  }
+  HIP_TRY(launch_prefill_commit(kv->lens, window, adv, s));
+  return DSI_OK;
+}
+
 // library workspace for dsi_accept, one per device
 struct AcceptWs {
   DevBuf ws;
@@ -756,9 +987,9 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
   A((void**)&m->ssq, (size_t)m->Nb_o * kMaxRows * 4);
   A((void**)&m->ssq2, (size_t)m->Nb_down * kMaxRows * 4);
   A((void**)&m->gcnt, (size_t)(m->Nb_down + 64) * sizeof(int));
-  if (st == DSI_OK) m->pk_d = make_pack(m, m->Kb_d, &st);
-  if (st == DSI_OK) m->pk_q = make_pack(m, m->Kb_q, &st);
-  if (st == DSI_OK) m->pk_ff = make_pack(m, m->Kb_ff, &st);
+  if (st == DSI_OK) m->pk_d = make_pack(m, m->allocs, kMaxRows, m->Kb_d, &st);
+  if (st == DSI_OK) m->pk_q = make_pack(m, m->allocs, kMaxRows, m->Kb_q, &st);
+  if (st == DSI_OK) m->pk_ff = make_pack(m, m->allocs, kMaxRows, m->Kb_ff, &st);
   A((void**)&m->qbuf, (size_t)kMaxRows * m->qdim * 4);
   A((void**)&m->rope, (size_t)kMaxRows * (m->hd / 2) * sizeof(float2));
   A((void**)&m->logits, (size_t)kMaxRows * m->V * 4);
@@ -934,6 +1165,7 @@ dsi_status dsi_kv_create(dsi_model* m, int32_t n_windows, int32_t max_len, dsi_k
     delete kv;
     return st;
   }
+  wide_reserve(m, max_len);
   m->live_kv++;
   *out = kv;
   return DSI_OK;
@@ -959,6 +1191,18 @@ dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* 
   if (kv->hi[window] + n > kv->max_len)
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window,
                 kv->hi[window], n, kv->max_len);
+  if (n > kMaxRows && m->wide.rows && m->kvb) {
+    // forwards of about equal size, whole groups of kMaxRows rows
+    const int parts = cdiv(n, m->wide.rows);
+    const int each = (int)round_up((size_t)cdiv(n, parts), kMaxRows);
+    for (int off = 0; off < n; off += each) {
+      const int rows = std::min(each, n - off);
+      const bool last = off + rows == n;
+      DSI_TRY(run_prefill(m, kv, window, rows, d_tokens + off, last ? d_last_logits : nullptr, last));
+      kv->hi[window] += rows;
+    }
+    return DSI_OK;
+  }
   for (int off = 0; off < n; off += kMaxRows) {
     const int rows = std::min(kMaxRows, n - off);
     const bool last = off + rows == n;

@@ -1,0 +1,100 @@
+"""Prompts longer than one 64-row chunk (many chunks in one forward) against
+the fp64 oracle and against the same prompt in 64-token calls."""
+import numpy as np
+import pytest
+
+import dsi_synth as S
+from oracle import forward64
+from paper_2405_14105_amd import dsi
+
+pytestmark = pytest.mark.gpu
+SEED = 5
+
+
+def _rig(*a):
+    from gpu_rig import Rig
+    return Rig(*a)
+
+
+def _weights(shape):
+    return lambda l, n: S.weight(shape, SEED, l, n).astype(np.float64)
+
+
+# one row past a chunk, row tiles of 4-8 blocks, one row past a tile, two and
+# three row tiles; prefixes that end off the 16-, 32- and 64-row grids; group
+# sizes 1, 3, 4 and 16; ragged FFN and K splits; several key chunks
+@pytest.mark.parametrize("name,prefix,n", [
+    ("ragged_bf16", 0, 65), ("ragged_bf16", 5, 129), ("gqa_hd64", 0, 97), ("gqa_hd64", 37, 257),
+    ("mha_hd128", 63, 112), ("mha_hd128", 700, 66), ("many_kv", 0, 200), ("o_ring_hd128", 64, 300),
+    ("ring_wide_ff", 31, 81)])
+def test_matches_oracle(name, prefix, n):
+    shape = S.SHAPES[name]
+    toks = S.prefix_tokens(shape, SEED, 0, prefix + n)
+    with _rig(shape, SEED, 2, prefix + n + 3) as rig:
+        if prefix:
+            rig.prefill(1, toks[:prefix])
+        z = rig.prefill(1, toks[prefix:], want_logits=True)
+        assert rig.length(1) == prefix + n
+        kv = [rig.export_kv(1, l, prefix + n) for l in range(shape.n_layers)]
+    zo, cache = forward64(shape, _weights(shape), toks)
+    err = float(np.abs(z - zo[-1]).max())
+    print(f"{name} {prefix}+{n}: max|dz| = {err:.3g}")
+    assert err <= 2e-3                      # tests/parity.py's gate for bf16 caches
+    for l, (k, v) in enumerate(kv):
+        for got, want in ((k, cache[l][0]), (v, cache[l][1])):
+            # equal up to one bf16 spacing of the largest entry of the row
+            want = np.asarray(want).reshape(got.shape)
+            top = np.abs(want).max(axis=-1, keepdims=True)
+            assert np.all(np.abs(got - want) <= 2.0 ** -7 * top + 1e-6)
+
+
+def test_more_than_one_forward():
+    """2100 rows: two forwards; the rows of the second attend to the first's."""
+    shape = S.SHAPES["gqa_hd64"]
+    toks = S.prefix_tokens(shape, SEED, 0, 2100)
+    with _rig(shape, SEED, 2, 2200) as rig:
+        z = rig.prefill(0, toks, want_logits=True)
+        for i in range(0, 2100, 64):        # one chunk a call
+            z64 = rig.prefill(1, toks[i:i + 64], want_logits=True)
+        assert rig.length(0) == rig.length(1) == 2100
+    assert np.abs(z - z64).max() <= 2e-3
+
+
+@pytest.mark.parametrize("bad", [(70,), (0, 199), (10, 140), (64, 70, 130, 210)])
+def test_invalid_ids_drop_their_chunks(bad):
+    """A chunk of 64 with an id outside the vocabulary is not cached, the others are, as in 64-token calls."""
+    shape = S.SHAPES["gqa_hd64"]
+    n = 211
+    toks = np.array(S.prefix_tokens(shape, SEED, 0, n))
+    for i in bad:
+        toks[i] = shape.vocab if i % 2 else -1
+    with _rig(shape, SEED, 2, 300) as rig:
+        rig.prefill(0, toks)
+        for i in range(0, n, 64):
+            rig.prefill(1, toks[i:i + 64])
+        lens = []
+        for w in (0, 1):
+            try:
+                rig.length(w)
+                seen = False
+            except dsi.DsiError as e:
+                seen = e.status == dsi.DSI_EINVAL
+            assert seen == (w == 0)          # one report for both windows' prompts
+            lens.append(rig.length(w))
+        chunks = {i // 64 for i in bad}
+        assert lens[0] == lens[1] == sum(min(64, n - 64 * c) for c in range(4) if c not in chunks)
+        for l in range(shape.n_layers):
+            for a, b in zip(rig.export_kv(0, l, lens[0]), rig.export_kv(1, l, lens[0])):
+                assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(b).max(axis=-1, keepdims=True) + 1e-6)
+
+
+def test_dead_rows_do_not_reach_the_logits():
+    """Rows past the length hold NaN: a long prompt over them is not touched by it."""
+    shape = S.SHAPES["mha_hd128"]
+    toks = S.prefix_tokens(shape, SEED, 0, 150)
+    with _rig(shape, SEED, 1, 400) as rig:
+        a = rig.prefill(0, toks, want_logits=True)
+        dsi.dsi_kv_rollback(rig.kv, 0, 0)
+        dsi.dsi_kv_poison(rig.kv, 0)
+        b = rig.prefill(0, toks, want_logits=True)
+    assert np.all(np.isfinite(b)) and np.array_equal(a, b)
