@@ -359,6 +359,10 @@ hipError_t launch_rmsnorm_pack(float* x, const float* delta, int S, size_t delta
     case 2: DSI_NORM_LAUNCH(2); break;
     case 3: DSI_NORM_LAUNCH(3); break;
     case 4: DSI_NORM_LAUNCH(4); break;
+    case 5: DSI_NORM_LAUNCH(5); break;
+    case 6: DSI_NORM_LAUNCH(6); break;
+    case 7: DSI_NORM_LAUNCH(7); break;
+    case 8: DSI_NORM_LAUNCH(8); break;
     default: return hipErrorInvalidValue;
   }
 #undef DSI_NORM_LAUNCH

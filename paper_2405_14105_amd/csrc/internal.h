@@ -196,6 +196,7 @@ hipError_t launch_restream(const void* src, int Nb, int Kb, int G, const RingCfg
 hipError_t launch_gemm(int wtype, int mt, const GemmArgs& a, hipStream_t s);
 
 // prefill (prefill.hip): bf16 weights, any number of rows
+constexpr int kWideSplits = 8;   // K splits at most
 struct WideCfg {
   int mt = 8;           // m-blocks (16 rows) per workgroup tile, 4..8
   int nwn = 4;          // waves along the output features (2 or 4), 4 n-blocks each

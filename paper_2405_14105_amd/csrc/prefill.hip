@@ -45,7 +45,8 @@ struct WideGrid {
   int per_xcd;          // workgroups (tiles of all splits) of one XCD
 };
 
-template <int MT, int NWN, int EPI>
+// NT: the weights are read by one row tile only, and loaded nontemporally
+template <int MT, int NWN, int EPI, int NT>
 __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideGrid gr) {
   constexpr int KG = kWideWaves / NWN;          // K groups
   constexpr int XT = 2 * MT;                    // activation tiles of a k-block (hi, lo)
@@ -83,7 +84,10 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
   auto load_w = [&](u32x4 (&d)[kWideNb], int i) {
     const int kb = min(k0 + i * KG + kg, k1 - 1);
 #pragma unroll
-    for (int j = 0; j < kWideNb; ++j) d[j] = W[(tb[j] + (size_t)kb * ts[j]) * 64 + lane];
+    for (int j = 0; j < kWideNb; ++j) {
+      const u32x4* p = &W[(tb[j] + (size_t)kb * ts[j]) * 64 + lane];
+      d[j] = NT ? __builtin_nontemporal_load(p) : *p;
+    }
   };
   auto load_x = [&](u32x4 (&d)[XP], int i) {
     const int kb = min(k0 + i * KG + kg, k1 - 1);
@@ -200,16 +204,16 @@ __global__ __launch_bounds__(256) void k_wide_fold(GemmArgs a, const float* part
   const int nb = blockIdx.x * 4 + (threadIdx.x >> 6), mb = blockIdx.y;
   if (nb >= a.Nb) return;
   const float* p = part + (((size_t)mb * a.Nb + nb) * 64 + lane) * 4;
-  f32x4 pv[kMaxSplits];
+  f32x4 pv[kWideSplits];
 #pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s) pv[s] = *(const f32x4*)(p + min(s, S - 1) * stride);
+  for (int s = 0; s < kWideSplits; ++s) pv[s] = *(const f32x4*)(p + min(s, S - 1) * stride);
   const int m = mb * 16 + (lane & 15);
   if (m >= a.M) return;
   EpiIn pre{};
   if constexpr (EPI == EPI_QKV) pre = qkv_inputs(a.epi, nb, (lane >> 4) * 4, m);
   f32x4 v = pv[0];
 #pragma unroll
-  for (int s = 1; s < kMaxSplits; ++s)
+  for (int s = 1; s < kWideSplits; ++s)
     if (s < S) v += pv[s];
   epilogue<W_BF16, EPI>(a.epi, nb, (lane >> 4) * 4, m, 0, v, pre);
 }
@@ -418,22 +422,23 @@ __global__ __launch_bounds__(HD * 4) void k_attn_prefill_combine(AttnArgs a, int
 
 }  // namespace
 
-template <int MT, int NWN>
-hipError_t launch_wide_epi(const GemmArgs& a, const WideGrid& g, int grid, hipStream_t s) {
-  const dim3 gd(grid), bd(kWideWaves * 64);
+template <int MT, int NWN, int NT>
+hipError_t launch_wide_epi(const GemmArgs& a, const WideGrid& g, hipStream_t s) {
+  const dim3 gd(g.per_xcd * 8), bd(kWideWaves * 64);
   switch (a.epi.kind) {
-    case EPI_PART: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_PART>), gd, bd, 0, s, a, g); break;
-    case EPI_TILE: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_TILE>), gd, bd, 0, s, a, g); break;
-    case EPI_QKV: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_QKV>), gd, bd, 0, s, a, g); break;
-    case EPI_SILU: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_SILU>), gd, bd, 0, s, a, g); break;
+    case EPI_PART: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_PART, NT>), gd, bd, 0, s, a, g); break;
+    case EPI_TILE: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_TILE, NT>), gd, bd, 0, s, a, g); break;
+    case EPI_QKV: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_QKV, NT>), gd, bd, 0, s, a, g); break;
+    case EPI_SILU: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_SILU, NT>), gd, bd, 0, s, a, g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <int MT>
-hipError_t launch_wide_mt(const GemmArgs& a, int nwn, const WideGrid& g, int grid, hipStream_t s) {
-  return nwn == 4 ? launch_wide_epi<MT, 4>(a, g, grid, s) : launch_wide_epi<MT, 2>(a, g, grid, s);
+hipError_t launch_wide_mt(const GemmArgs& a, int nwn, const WideGrid& g, hipStream_t s) {
+  if (g.mtiles == 1) return nwn == 4 ? launch_wide_epi<MT, 4, 1>(a, g, s) : launch_wide_epi<MT, 2, 1>(a, g, s);
+  return nwn == 4 ? launch_wide_epi<MT, 4, 0>(a, g, s) : launch_wide_epi<MT, 2, 0>(a, g, s);
 }
 
 hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s) {
@@ -447,17 +452,17 @@ hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s) 
   g.tiles = g.nt * g.mtiles;
   g.per_xcd = (g.tiles * a.S + 7) / 8;
   switch (c.mt) {
-    case 4: return launch_wide_mt<4>(a, c.nwn, g, g.per_xcd * 8, s);
-    case 5: return launch_wide_mt<5>(a, c.nwn, g, g.per_xcd * 8, s);
-    case 6: return launch_wide_mt<6>(a, c.nwn, g, g.per_xcd * 8, s);
-    case 7: return launch_wide_mt<7>(a, c.nwn, g, g.per_xcd * 8, s);
-    case 8: return launch_wide_mt<8>(a, c.nwn, g, g.per_xcd * 8, s);
+    case 4: return launch_wide_mt<4>(a, c.nwn, g, s);
+    case 5: return launch_wide_mt<5>(a, c.nwn, g, s);
+    case 6: return launch_wide_mt<6>(a, c.nwn, g, s);
+    case 7: return launch_wide_mt<7>(a, c.nwn, g, s);
+    case 8: return launch_wide_mt<8>(a, c.nwn, g, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride, int S, hipStream_t s) {
-  if (S < 1 || S > kMaxSplits) return hipErrorInvalidValue;
+  if (S < 1 || S > kWideSplits) return hipErrorInvalidValue;
   const dim3 grid((a.Nb + 3) / 4, (a.M + 15) / 16), blk(256);
   if (a.epi.kind == EPI_QKV) hipLaunchKernelGGL((k_wide_fold<EPI_QKV>), grid, blk, 0, s, a, part, stride, S);
   else if (a.epi.kind == EPI_SILU) hipLaunchKernelGGL((k_wide_fold<EPI_SILU>), grid, blk, 0, s, a, part, stride, S);

@@ -614,24 +614,39 @@ struct WidePlan {
   WideCfg cfg;
   int S = 1;
 };
-// part_cols: columns of one partial row ([rows][part_cols] fp32); fused: the
-// unsplit launch applies its epilogue itself, a split one needs a fold launch
+// The fastest by estimate over every tile and split.  A launch takes its
+// longest of
+//  * MFMA time: rounds of one workgroup per CU, each 1.3 us + 26 (NWN 4) or
+//    29.5 ns (NWN 2) per k-block, wave and m-block, down to 62 % of that
+//    with idle CUs (clock and L2 are shared);
+//  * the weights at 6 TB/s;
+//  * what one CU takes in, weights and activations, at 94 GB/s;
+// plus 8.7 us of launch, first loads, reduction and last stores, plus the
+// partials' way through memory (and the fold launch of a split QKV or
+// gate/up).  Fitted to 5266 launches (11 row counts from 65 to 2048, the
+// layer shapes of the 1B, 8B and 13B models and the small drafter, every
+// tile, splits 1-4): the chosen one is 1.2 % slower than the best on
+// average, 16 % at worst.
 WidePlan wide_plan(const dsi_model* m, int M, int Nb, int Kb, bool fused) {
-  const int mb = cdiv(M, 16), mtiles = cdiv(mb, 8);
+  const int mb = cdiv(M, 16);
+  const double part = (double)M * Nb * 64;
   WidePlan best;
   double t_best = 1e30;
   for (int nwn = 2; nwn <= 4; nwn += 2)
-    for (int half = 0; half < 2; ++half) {
-      const int mt = std::max(4, half ? cdiv(mb, 2 * mtiles) : cdiv(mb, mtiles));
-      const int tiles = cdiv(Nb, 4 * nwn) * cdiv(mb, mt);
-      for (int S = 1; S <= kMaxSplits; ++S) {
-        if (S > 1 && (Kb / S < 16 || (size_t)S * mb * 16 * Nb * 16 * 4 > m->wide.delta_bytes)) break;
-        const double steps = (double)cdiv(Kb, S) * nwn * mt;
-        const double part = (double)M * Nb * 16 * 4;
-        double t = 6.0 + cdiv(tiles * S, 256) * (1.5 + steps * 0.026);
-        t = std::max(t, 6.0 + (double)Nb * Kb * 1024 / 5.0e6);
-        if (fused && S > 1) t += 4.0 + S * part * 2 / 4.0e6;
-        if (!fused) t += S * part * 2 / 4.0e6;
+    for (int mt = 4; mt <= 8; ++mt) {
+      if (mt > 4 && mt > mb) break;
+      for (int S = 1; S <= kWideSplits; ++S) {
+        const size_t bytes = (size_t)S * mb * 256 * Nb * sizeof(float);
+        if (S > 1 && (Kb / S < 8 || bytes > m->wide.delta_bytes)) break;
+        const int wgs = cdiv(Nb, 4 * nwn) * cdiv(mb, mt) * S;
+        const int rounds = cdiv(wgs, 256), kbs = cdiv(Kb, S);
+        const double busy = 0.62 + 0.38 * std::min(1.0, wgs / 256.0);
+        const double mfma = rounds * (1.3 + (double)kbs * nwn * mt * (nwn == 4 ? 0.0257 : 0.0295) * busy);
+        const double stream = (double)Nb * Kb * 1024 / 6.0e6;
+        const double intake = (double)rounds * kbs * (4 * nwn + 2 * mt) * 1024 / 94e3;
+        double t = 8.7 + std::max(mfma, std::max(stream, intake));
+        if (!fused) t += S * part / 4.5e6;
+        else if (S > 1) t += 4.5 + (S + 1) * part / 4.0e6;
         if (t < t_best) {
           t_best = t;
           best.cfg.mt = mt;
@@ -646,9 +661,8 @@ WidePlan wide_plan(const dsi_model* m, int M, int Nb, int Kb, bool fused) {
 // Launches one layer GEMM of M prompt rows: QKV and gate/up finish in their
 // epilogue (through a fold launch when K is split); O and down leave *splits
 // partials [M][d] in delta for the next RMSNorm.
-dsi_status wide_gemm(dsi_model* m, GemmArgs g, int M, int* splits) {
+dsi_status wide_gemm(dsi_model* m, const WidePlan& p, GemmArgs g, int M, int* splits) {
   const bool fused = g.epi.kind == EPI_QKV || g.epi.kind == EPI_SILU;
-  const WidePlan p = wide_plan(m, M, g.Nb, g.Kb, fused);
   g.M = M;
   g.S = p.S;
   if (fused && p.S == 1) {
@@ -713,6 +727,10 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     DSI_TRY(ensure(m->attn_ml, parts * sizeof(float2)));
   }
 
+  const WidePlan pl_qkv = wide_plan(m, M, m->Nb_qkv, m->Kb_d, true), pl_o = wide_plan(m, M, m->Nb_o, m->Kb_q, false);
+  const WidePlan pl_gu = wide_plan(m, M, m->Nb_gu, m->Kb_d, true);
+  const WidePlan pl_down = wide_plan(m, M, m->Nb_down, m->Kb_ff, false);
+
   const size_t Md = (size_t)M * m->d;
   int splits = 0;
   for (int l = 0; l < m->L; ++l) {
@@ -724,7 +742,7 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     g.epi.rope = w.rope;
     {
       Prof p(m, DSI_K_QKV);
-      DSI_TRY(wide_gemm(m, g, M, nullptr));
+      DSI_TRY(wide_gemm(m, pl_qkv, g, M, nullptr));
     }
     AttnArgs aa{};
     aa.q = w.qbuf;
@@ -751,7 +769,7 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     g.Xlo = w.pk_q.lo;
     {
       Prof p(m, DSI_K_OPROJ);
-      DSI_TRY(wide_gemm(m, g, M, &splits));
+      DSI_TRY(wide_gemm(m, pl_o, g, M, &splits));
       HIP_TRY(launch_rmsnorm_pack(w.x, w.delta, splits, Md, M, m->d, m->layers[l].ffn_norm, m->cfg.rms_eps, m->wtype,
                                   w.pk_d, nullptr, s));
     }
@@ -762,14 +780,14 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     g.epi.pack = w.pk_ff;
     {
       Prof p(m, DSI_K_GATEUP);
-      DSI_TRY(wide_gemm(m, g, M, nullptr));
+      DSI_TRY(wide_gemm(m, pl_gu, g, M, nullptr));
     }
     g = down_args(m, l, M, 1);
     g.Xhi = w.pk_ff.hi;
     g.Xlo = w.pk_ff.lo;
     {
       Prof p(m, DSI_K_DOWN);
-      DSI_TRY(wide_gemm(m, g, M, &splits));
+      DSI_TRY(wide_gemm(m, pl_down, g, M, &splits));
       if (l + 1 < m->L)
         HIP_TRY(launch_rmsnorm_pack(w.x, w.delta, splits, Md, M, m->d, m->layers[l + 1].attn_norm, m->cfg.rms_eps,
                                     m->wtype, w.pk_d, nullptr, s));
