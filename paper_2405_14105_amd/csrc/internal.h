@@ -264,9 +264,10 @@ hipError_t launch_attention(int kv_bf16, int hd, const AttnArgs& a, hipStream_t 
 // causal attention of one window's prompt rows (rows.gpos) over a bf16 cache
 // (prefill.hip), the keys in n_chunks chunks of `chunk` (a multiple of 64);
 // several chunks leave partials [n_kv][units][chunks][16][hd] in part_o and
-// part_ml.  n_qtiles, waves unused.
+// part_ml.  Rows from 16 * rb0 on only (part_o's units count from there).
+// n_qtiles, waves unused.
 int prefill_units(int rows, int group);   // 16-row units of one KV head
-hipError_t launch_attention_prefill(int hd, const AttnArgs& a, hipStream_t s);
+hipError_t launch_attention_prefill(int hd, const AttnArgs& a, int rb0, hipStream_t s);
 
 // verification (verify.hip)
 struct VerifyArgs {

@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void k_wide_fold(GemmArgs a, const float* part
 // reads the keys once per 16 queries.  With few row blocks the keys are cut
 // into chunks as well (13B, 77 rows over 900 keys: 51 -> 19 + 5 us).
 template <int HD>
-__global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int n_units, int n_ublk) {
+__global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n_units, int n_ublk) {
   constexpr int DS = HD / 32;
   constexpr int DT = HD / 16;
   constexpr int ST = 4 * DS;                 // tiles of a 32-key step: 2 DS of K, DT of V
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int n_units, i
   const int G = a.n_heads / a.n_kv, R = a.rows.rows_per_window;
   const int u = min(ub * 8 + w, n_units - 1), ul = min(ub * 8 + 7, n_units - 1);
   const bool live = ub * 8 + w < n_units;
-  const int rb = u / G, head = kvh * G + u % G;
+  const int rb = rb0 + u / G, head = kvh * G + u % G;
   // position of the first row of a 16-row block (negative: rows of an invalid
   // group, whose output nobody reads), and the keys its rows see together:
   // [0, base + rows in it)
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int n_units, i
   const int pos0 = block_pos(rb);
   const int kw = live ? block_keys(rb) : 0;             // keys of this wave
   int kwg = 0;                                          // and of the workgroup
-  for (int b = (ub * 8) / G; b <= ul / G; ++b) kwg = max(kwg, block_keys(b));
+  for (int b = rb0 + (ub * 8) / G; b <= rb0 + ul / G; ++b) kwg = max(kwg, block_keys(b));
   const int st0 = c * (a.chunk >> 6), st1 = min((kwg + 63) >> 6, st0 + (a.chunk >> 6));   // stages of 64 keys
   const int r16 = lane & 15, kgrp = (lane >> 4) * 8;
   const int row = rb * 16 + r16;
@@ -394,11 +394,11 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int n_units, i
 // sums the key chunks of one unit (16 rows of one head), chunks in order: one
 // thread per row and four dims
 template <int HD>
-__global__ __launch_bounds__(HD * 4) void k_attn_prefill_combine(AttnArgs a, int n_units) {
+__global__ __launch_bounds__(HD * 4) void k_attn_prefill_combine(AttnArgs a, int rb0, int n_units) {
   const int kvh = blockIdx.x % a.n_kv, u = blockIdx.x / a.n_kv;
   const int G = a.n_heads / a.n_kv, R = a.rows.rows_per_window;
   const int q = threadIdx.x / (HD / 4), d = threadIdx.x % (HD / 4) * 4;
-  const int row = u / G * 16 + q;
+  const int row = (rb0 + u / G) * 16 + q;
   if (row >= R) return;
   const size_t part = ((size_t)kvh * n_units + u) * a.n_chunks;
   const float2* ml = a.part_ml + part * 16 + q;
@@ -473,23 +473,24 @@ hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride,
 int prefill_units(int rows, int group) { return (rows + 15) / 16 * group; }
 
 template <int HD>
-hipError_t launch_attn_prefill_hd(const AttnArgs& a, int units, hipStream_t s) {
+hipError_t launch_attn_prefill_hd(const AttnArgs& a, int rb0, int units, hipStream_t s) {
   const int ub = (units + 7) / 8;
-  hipLaunchKernelGGL((k_attn_prefill<HD>), dim3(ub * a.n_kv * a.n_chunks), dim3(512), 0, s, a, units, ub);
+  hipLaunchKernelGGL((k_attn_prefill<HD>), dim3(ub * a.n_kv * a.n_chunks), dim3(512), 0, s, a, rb0, units, ub);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_chunks == 1) return e;
-  hipLaunchKernelGGL((k_attn_prefill_combine<HD>), dim3(units * a.n_kv), dim3(HD * 4), 0, s, a, units);
+  hipLaunchKernelGGL((k_attn_prefill_combine<HD>), dim3(units * a.n_kv), dim3(HD * 4), 0, s, a, rb0, units);
   return hipGetLastError();
 }
 
-hipError_t launch_attention_prefill(int hd, const AttnArgs& a, hipStream_t s) {
-  const int units = prefill_units(a.rows.rows_per_window, a.n_heads / a.n_kv);
+hipError_t launch_attention_prefill(int hd, const AttnArgs& a, int rb0, hipStream_t s) {
+  const int units = prefill_units(a.rows.rows_per_window - 16 * rb0, a.n_heads / a.n_kv);
+  if (rb0 < 0 || units < 1) return hipErrorInvalidValue;
   if (a.n_chunks < 1 || a.chunk < 64 || a.chunk % 64 || !a.rows.gpos) return hipErrorInvalidValue;
   switch (hd) {
-    case 32: return launch_attn_prefill_hd<32>(a, units, s);
-    case 64: return launch_attn_prefill_hd<64>(a, units, s);
-    case 96: return launch_attn_prefill_hd<96>(a, units, s);
-    case 128: return launch_attn_prefill_hd<128>(a, units, s);
+    case 32: return launch_attn_prefill_hd<32>(a, rb0, units, s);
+    case 64: return launch_attn_prefill_hd<64>(a, rb0, units, s);
+    case 96: return launch_attn_prefill_hd<96>(a, rb0, units, s);
+    case 128: return launch_attn_prefill_hd<128>(a, rb0, units, s);
   }
   return hipErrorInvalidValue;
 }
