@@ -11,7 +11,7 @@
 //   1. per 4096-entry chunk: max of z / T and sum of exp(z / T - max) (fp64);
 //   2. per chunk: combine all chunk statistics (same order in every block),
 //      write the chunk's q = (float) exp(z / T - M) / S, and the fp64 sum of
-//      those fp32 values (per-thread runs of 16, then a workgroup scan);
+//      those fp32 values (per-thread runs of four, then a workgroup scan);
 //   3. one workgroup: a wave prefix over the chunk sums locates the chunk
 //      holding u * total, the chunk is rescanned in the same order, and the
 //      token is written to its slot of the verification window.
@@ -24,42 +24,44 @@ namespace dsi {
 
 namespace {
 
-constexpr int ST = 256;                  // threads per workgroup
-constexpr int SPER = kVerifyChunk / ST;  // 16 entries per thread
+constexpr int ST = 1024;                 // threads per workgroup
+constexpr int SW = ST / 64;              // waves
+constexpr int SPER = kVerifyChunk / ST;  // consecutive entries per thread: four keep the chains short (see verify.hip)
+static_assert(SPER == 4, "load_row4");
 
 __global__ __launch_bounds__(ST) void k_dstat(DraftArgs a) {
-  __shared__ double shd[4];
-  __shared__ float shv[4];
+  __shared__ double shd[SW];
+  __shared__ float shv[SW];
   const int c = blockIdx.x;
-  const int v0 = c * kVerifyChunk;
-  const int v1 = min(a.V, v0 + kVerifyChunk);
+  const int v0 = c * kVerifyChunk + threadIdx.x * SPER;
   float vals[SPER];
+  load_row4(a.logits, v0, a.V, rows_aligned4(a.logits, a.V), vals);
   float zmax = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < SPER; ++i) vals[i] = a.logits[min(v0 + (int)threadIdx.x + ST * i, v1 - 1)];
-#pragma unroll
   for (int i = 0; i < SPER; ++i) {
-    if (v0 + (int)threadIdx.x + ST * i >= v1) vals[i] = -INFINITY;
+    if (v0 + i >= a.V) vals[i] = -INFINITY;
     zmax = fmaxf(zmax, vals[i]);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, o));
+  zmax = wave_max(zmax);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) shv[w] = zmax;
   __syncthreads();
-  zmax = fmaxf(fmaxf(shv[0], shv[1]), fmaxf(shv[2], shv[3]));
-  const double m = (double)zmax / a.temperature;
+#pragma unroll
+  for (int i = 0; i < SW; ++i) zmax = fmaxf(zmax, shv[i]);
+  const double m = over_t((double)zmax, a.temperature, a.inv_temperature);
   double sum = 0.0;
 #pragma unroll
-  for (int i = 0; i < SPER; ++i) {
-    const int v = v0 + threadIdx.x + ST * i;
-    if (v < v1) sum += exp((double)vals[i] / a.temperature - m);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  for (int i = 0; i < SPER; ++i)
+    if (v0 + i < a.V) sum += exp(over_t((double)vals[i], a.temperature, a.inv_temperature) - m);
+  sum = wave_sum(sum);
   if ((threadIdx.x & 63) == 0) shd[w] = sum;
   __syncthreads();
-  if (threadIdx.x == 0) a.part[c] = make_double2(m, (shd[0] + shd[1]) + (shd[2] + shd[3]));
+  if (threadIdx.x == 0) {
+    sum = shd[0];
+#pragma unroll
+    for (int i = 1; i < SW; ++i) sum += shd[i];
+    a.part[c] = make_double2(m, sum);
+  }
 }
 
 // the row's max and normaliser from the chunk statistics: wave 0, chunks
@@ -69,12 +71,10 @@ __device__ __forceinline__ void row_stats(const DraftArgs& a, double* sM, double
     const int lane = threadIdx.x;
     double m = -INFINITY;
     for (int c = lane; c < a.C; c += 64) m = fmax(m, a.part[c].x);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+    m = wave_max(m);
     double s = 0.0;
     for (int c = lane; c < a.C; c += 64) s += a.part[c].y * exp(a.part[c].x - m);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = wave_sum(s);
     if (lane == 0) {
       *sM = m;
       *sS = s;
@@ -85,66 +85,63 @@ __device__ __forceinline__ void row_stats(const DraftArgs& a, double* sM, double
 
 __global__ __launch_bounds__(ST) void k_dq(DraftArgs a) {
   __shared__ double sM, sS;
-  __shared__ double sh[ST / 64];
-  row_stats(a, &sM, &sS);
+  __shared__ double sh[SW];
   const int c = blockIdx.x;
-  const double M = sM, S = sS;
-  // thread t: entries c*4096 + 16 t .. +15 in order (the rescan's order)
+  // thread t: entries c*4096 + 4 t .. +3 in order (the rescan's order)
   const int v0 = c * kVerifyChunk + threadIdx.x * SPER;
-  double own = 0.0;
   float zv[SPER];
-#pragma unroll
-  for (int i = 0; i < SPER; ++i) zv[i] = a.logits[min(v0 + i, a.V - 1)];
+  load_row4(a.logits, v0, a.V, rows_aligned4(a.logits, a.V), zv);
+  row_stats(a, &sM, &sS);
+  const double M = sM, S = sS;
+  double own = 0.0;
 #pragma unroll
   for (int i = 0; i < SPER; ++i) {
     const int v = v0 + i;
     if (v < a.V) {
-      const float q = (float)(exp((double)zv[i] / a.temperature - M) / S);
+      const float q = (float)(exp(over_t((double)zv[i], a.temperature, a.inv_temperature) - M) / S);
       a.q_out[v] = q;
       own += (double)q;
     }
   }
-  const double incl = block_scan_incl<ST / 64>(own, sh);
+  const double incl = block_scan_incl<SW>(own, sh);
   if (threadIdx.x == ST - 1) a.csum[c] = incl;
 }
 
 __global__ __launch_bounds__(ST) void k_ddraw(DraftArgs a) {
-  __shared__ double sh[ST / 64];
+  __shared__ double sh[SW];
   __shared__ double sincl[ST];
   __shared__ double s_base, s_target;
-  __shared__ int s_chunk, s_first, s_last;
+  __shared__ int s_chunk;
+  __shared__ int s_first[SW], s_last[SW];
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     // inclusive prefix over the chunk sums, 64 chunks at a time
+    const double un = (double)a.u[0];
     auto prefix = [&](int g, double carry) {
       const int c = g * 64 + lane;
       double x = c < a.C ? a.csum[c] : 0.0;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const double t = __shfl_up(x, o);
-        if (lane >= o) x += t;
-      }
-      return carry + x;
+      return carry + wave_scan_incl(x);
     };
-    double carry = 0.0;
     const int groups = (a.C + 63) / 64;
-    for (int g = 0; g < groups; ++g) carry = __shfl(prefix(g, carry), 63);
-    const double target = (double)a.u[0] * carry;
+    const double incl0 = prefix(0, 0.0);
+    double carry = lane_value(incl0, 63);
+    for (int g = 1; g < groups; ++g) carry = lane_value(prefix(g, carry), 63);
+    const double target = un * carry;
     int chunk = -1;
     double base = 0.0;
     carry = 0.0;
     for (int g = 0; g < groups; ++g) {
-      const double incl = prefix(g, carry);
+      const double incl = g == 0 ? incl0 : prefix(g, carry);
       const double prev = __shfl_up(incl, 1);
       const double excl = lane ? prev : carry;   // exact prefix before chunk g*64+lane
       const unsigned long long hit = __ballot(g * 64 + lane < a.C && incl > target);
       if (hit) {   // uniform across the wave
         const int l = __ffsll((long long)hit) - 1;
         chunk = g * 64 + l;
-        base = __shfl(excl, l);
+        base = lane_value(excl, l);
         break;
       }
-      carry = __shfl(incl, 63);
+      carry = lane_value(incl, 63);
     }
     if (chunk < 0) {
       // rounding left no crossing: the last chunk with mass (drawn from its
@@ -161,9 +158,18 @@ __global__ __launch_bounds__(ST) void k_ddraw(DraftArgs a) {
       s_chunk = chunk;
       s_base = base;
       s_target = target;
-      s_first = INT_MAX;
-      s_last = -1;
     }
+  } else if (threadIdx.x < 128 && a.lens) {
+    // wave 1: the forwarded rows (at most 64) enter the drafter's cache if
+    // every id is valid; the first step's last one is w0
+    const int lane = threadIdx.x - 64;
+    const int t = lane < a.n_rows ? a.rows[lane] : 0;
+    const bool bad = __any(t < 0 || t >= a.V);
+    if (lane == 0) {
+      if (bad) atomicOr(a.err, 1);
+      else a.lens[a.window] += a.n_rows;
+    }
+    if (a.w0_out && lane == a.n_rows - 1) *a.w0_out = t;
   }
   __syncthreads();
   const int v0 = s_chunk * kVerifyChunk + threadIdx.x * SPER;
@@ -173,8 +179,7 @@ __global__ __launch_bounds__(ST) void k_ddraw(DraftArgs a) {
   // all loads first (clamped index, masked after): a wait behind a
   // conditional load is a wait for every load issued before it
   float qv[SPER];
-#pragma unroll
-  for (int i = 0; i < SPER; ++i) qv[i] = a.q_out[min(v0 + i, a.V - 1)];
+  load_row4(a.q_out, v0, a.V, rows_aligned4(a.q_out, a.V), qv);
 #pragma unroll
   for (int i = 0; i < SPER; ++i) {
     const int v = v0 + i;
@@ -182,25 +187,20 @@ __global__ __launch_bounds__(ST) void k_ddraw(DraftArgs a) {
     own += vals[i];
     if (vals[i] > 0.0) lastpos = v;
   }
-  const double incl = block_scan_incl<ST / 64>(own, sh);
+  const double incl = block_scan_incl<SW>(own, sh);
   sincl[threadIdx.x] = incl;
   __syncthreads();
   int first = INT_MAX;
   if (s_base != INFINITY) {
     double cw = threadIdx.x > 0 ? sincl[threadIdx.x - 1] : 0.0;
+#pragma unroll
     for (int i = 0; i < SPER; ++i) {
       cw += vals[i];
-      if (s_base + cw > s_target && vals[i] > 0.0) {
-        first = v0 + i;
-        break;
-      }
+      if (first == INT_MAX && s_base + cw > s_target && vals[i] > 0.0) first = v0 + i;
     }
   }
-  if (first != INT_MAX) atomicMin(&s_first, first);
-  if (lastpos >= 0) atomicMax(&s_last, lastpos);
-  __syncthreads();
+  int tok = block_first_or_last<SW>(first, lastpos, s_first, s_last);
   if (threadIdx.x == 0) {
-    int tok = s_first != INT_MAX ? s_first : s_last;
     if (tok < 0) tok = 0;
     *a.tok_out = tok;
   }
@@ -214,7 +214,9 @@ size_t draft_workspace_bytes(int V) {
 }
 
 hipError_t launch_draft_sample(DraftArgs a, void* ws, hipStream_t s) {
+  if (a.lens && (a.n_rows < 1 || a.n_rows > kMaxRows)) return hipErrorInvalidValue;
   a.C = (a.V + kVerifyChunk - 1) / kVerifyChunk;
+  a.inv_temperature = 1.0 / a.temperature;
   a.part = (double2*)ws;
   a.csum = (double*)((char*)ws + (((size_t)a.C * sizeof(double2) + 15) & ~(size_t)15));
   hipLaunchKernelGGL(k_dstat, dim3(a.C), dim3(ST), 0, s, a);

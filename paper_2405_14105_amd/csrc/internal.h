@@ -277,6 +277,7 @@ struct VerifyArgs {
   const float* q;       // [B][k][V]
   const float* u;       // [B][k+1]
   double temperature;
+  double inv_temperature;   // set by verify_bind_workspace
   int greedy;
   int commit;
   int* lens;            // nullable: window lengths (commit)
@@ -304,6 +305,15 @@ struct DraftArgs {
   const float* u;       // [1] the uniform of this draft
   float* q_out;         // [V] the stored distribution
   int* tok_out;         // [1] the draft
+  // the forward this draft ends: its n_rows token ids are checked and, if
+  // valid, added to the window's length (nullable lens); the last one goes to
+  // w0_out (nullable)
+  int* lens;
+  int window, n_rows;
+  const int* rows;
+  int* err;
+  int* w0_out;
+  double inv_temperature;   // set by launch_draft_sample
   double2* part;        // workspace [C]: chunk (max z/T, sum exp)
   double* csum;         // workspace [C]: chunk sums of the stored q
 };

@@ -1429,8 +1429,6 @@ dsi_status dsi_draft(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* d_
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window, kv->hi[window],
                 n_feed + k - 1, kv->max_len);
   hipStream_t s = m->stream;
-  // w0, the last fed token, opens the verification window
-  HIP_TRY(hipMemcpyAsync(d_tokens, d_feed + n_feed - 1, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
   for (int i = 0; i < k; ++i) {
     // step i forwards the unseen feed (i = 0) or the previous draft, whose
     // last row's logits give q_{i+1} and d_{i+1}
@@ -1439,9 +1437,14 @@ dsi_status dsi_draft(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* d_
     AttnPlan ap;
     DSI_TRY(plan_attention(m, kv, window, 1, R, &ap));
     DSI_TRY(run_forward(m, kv, ap, window, 1, R, rows, m->logits, 1, nullptr));
-    HIP_TRY(launch_kv_add_checked(kv->lens, window, rows, R, m->V, m->err, s));
     kv->hi[window] += R;
     DraftArgs da{};
+    da.lens = kv->lens;
+    da.window = window;
+    da.n_rows = R;
+    da.rows = rows;
+    da.err = m->err;
+    if (i == 0) da.w0_out = d_tokens;   // w0, the last fed token, opens the verification window
     da.logits = m->logits;
     da.V = m->V;
     da.temperature = (double)temperature;
