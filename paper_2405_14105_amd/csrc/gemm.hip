@@ -546,13 +546,20 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(GemmArgs a) {
 // reduced across the waves through LDS in wave order and handed to the same
 // epilogues as the packed kernel.
 constexpr int kRingDepth = 8;
+// Shortest run of a wave: below it the k-range is padded with zero tiles
+// (d = 1024, four k-blocks a wave, one n-block: QKV 5.4 -> 4.4 us and O 5.2 ->
+// 4.0 us against runs padded to eight)
+constexpr int kRingMinTiles = 4;
 
 // Weight tiles in flight per wave for MT row tiles: 8, or 4 where the
 // registers would not hold 8 -- the narrow roles (one or two n-blocks per
 // workgroup) with several row tiles, whose activation slots (hi and lo of MT
 // tiles per k-block in flight) grow with MT, and gate/up's 7 x 4 accumulator
 // tiles at four row tiles.  The depth does not change any sum.
-constexpr int ring_depth(int nbw, int mt) { return ((mt > 1 && nbw <= 2) || (mt >= 4 && nbw >= 7)) ? 4 : kRingDepth; }
+constexpr int ring_depth(int nbw, int mt, int tiles) {
+  const int d = ((mt > 1 && nbw <= 2) || (mt >= 4 && nbw >= 7)) ? 4 : kRingDepth;
+  return tiles < d ? tiles : d;
+}
 // n-blocks per LDS reduction round: kRingWaves x NBR x MT tiles of 1 KB
 // within 128 KB
 constexpr int ring_red_nb(int nbw, int mt) { return 16 / mt < nbw ? 16 / mt : nbw; }
@@ -631,14 +638,13 @@ __device__ __forceinline__ void ring_row_scales(const GemmArgs& a, const RingSsq
 // how many rows share the launch.
 template <int NK, int NBW, int EPI, int MT>
 __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
-  constexpr int NW = kRingWaves, D = ring_depth(NBW, MT), N = NK * NBW;
+  constexpr int NW = kRingWaves, N = NK * NBW, D = ring_depth(NBW, MT, N);
   // activation slots: k-block i's fragments are requested together with its
   // first weight tile (D tiles ahead of use) and live until its last tile;
   // when one is requested, tile u has just been consumed and tiles
   // u+1 .. u+D-1 still need ceil((D-1)/NBW) k-blocks
   constexpr int A = (D - 1 + NBW - 1) / NBW + 1;
   constexpr int NBR = ring_red_nb(NBW, MT);
-  static_assert(N >= D, "a wave's run must fill the ring");
   __shared__ f32x4 red[NW * NBR * MT * 64];
   __shared__ float rs[MT * 16];
   const int lane = threadIdx.x & 63;
@@ -721,36 +727,39 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
 // 1B shape: 0.826 -> 0.811 ms per step, where two would leave 96
 // workgroups; at the 8B shape one is far slower, 18.4 vs 13.7 us, as every
 // CU then takes in twice the activation bytes), gate/up seven (one
-// workgroup per CU for 1792 n-blocks), the down projection four with its K
-// split (as the packed launch), the LM head eight
+// workgroup per CU for 1792 n-blocks; two where seven would leave half the
+// CUs idle: 8.7 -> 5.7 us at 352 n-blocks, d = 1024), the down projection
+// four with its K split (as the packed launch; two where four leave half the
+// CUs idle: 11.1 -> 10.1 us at the 1B shape, 7.5 -> 6.3 at d = 1024, d_ff
+// 2816), the LM head eight.  The choice changes no summation order.
 template <int EPI>
 struct RingRole;
 template <>
 struct RingRole<EPI_QKV> {
   static constexpr int NBW = 2;
-  static int nbw(int Nb) { return Nb <= 256 ? 1 : 2; }
+  static int nbw(int Nb, int) { return Nb <= 256 ? 1 : 2; }
 };
 template <>
 struct RingRole<EPI_RESID> {
   static constexpr int NBW = 1;
-  static int nbw(int) { return NBW; }
+  static int nbw(int, int) { return NBW; }
 };
 template <>
 struct RingRole<EPI_SILU> {
   static constexpr int NBW = 7;
-  static int nbw(int) { return NBW; }
+  static int nbw(int Nb, int) { return Nb < 7 * 128 ? 2 : NBW; }
 };
 template <>
 struct RingRole<EPI_PART> {
   static constexpr int NBW = 4;
-  static int nbw(int) { return NBW; }
+  static int nbw(int Nb, int S) { return (Nb + 3) / 4 * S <= 128 ? 2 : NBW; }
 };
 template <>
 struct RingRole<EPI_PARTRES> : RingRole<EPI_PART> {};
 template <>
 struct RingRole<EPI_STORE> {   // the LM head: many rounds of workgroups
   static constexpr int NBW = 8;
-  static int nbw(int) { return NBW; }
+  static int nbw(int, int) { return NBW; }
 };
 
 // k-blocks per wave the ring kernel is built for (a shape's k-range per wave
@@ -759,7 +768,7 @@ constexpr int kRingNk[] = {1, 2, 4, 8, 14, 16};
 
 template <int EPI, int NBW, int NK, int MT>
 hipError_t launch_ring_nk(const GemmArgs& a, hipStream_t s) {
-  if constexpr (NK * NBW < kRingDepth) {
+  if constexpr (NK * NBW < kRingMinTiles) {
     return hipErrorInvalidValue;
   } else {
     const int grid = ((a.Nb + NBW - 1) / NBW) * a.S;
@@ -797,6 +806,9 @@ template <int EPI>
 hipError_t launch_ring(const GemmArgs& a, int mt, hipStream_t s) {
   if constexpr (EPI == EPI_QKV) {
     if (a.ring_nbw == 1) return launch_ring_nbw<EPI, 1>(a, mt, s);
+  }
+  if constexpr (EPI == EPI_SILU || EPI == EPI_PART || EPI == EPI_PARTRES) {
+    if (a.ring_nbw == 2) return launch_ring_nbw<EPI, 2>(a, mt, s);
   }
   if (a.ring_nbw != RingRole<EPI>::NBW) return hipErrorInvalidValue;
   return launch_ring_nbw<EPI, RingRole<EPI>::NBW>(a, mt, s);
@@ -954,19 +966,19 @@ bool ring_config(int wtype, int epi_kind, int Nb, int Kb, int S, RingCfg* out) {
   if (wtype != W_BF16 || Nb < 1 || Kb < 1 || S < 1) return false;
   int nbw = 0;
   switch (epi_kind) {
-    case EPI_QKV: nbw = RingRole<EPI_QKV>::nbw(Nb); break;
-    case EPI_RESID: nbw = RingRole<EPI_RESID>::nbw(Nb); break;
-    case EPI_SILU: nbw = RingRole<EPI_SILU>::nbw(Nb); break;
+    case EPI_QKV: nbw = RingRole<EPI_QKV>::nbw(Nb, S); break;
+    case EPI_RESID: nbw = RingRole<EPI_RESID>::nbw(Nb, S); break;
+    case EPI_SILU: nbw = RingRole<EPI_SILU>::nbw(Nb, S); break;
     case EPI_PART:
-    case EPI_PARTRES: nbw = RingRole<EPI_PART>::nbw(Nb); break;
-    case EPI_STORE: nbw = RingRole<EPI_STORE>::nbw(Nb); break;
+    case EPI_PARTRES: nbw = RingRole<EPI_PART>::nbw(Nb, S); break;
+    case EPI_STORE: nbw = RingRole<EPI_STORE>::nbw(Nb, S); break;
     default: return false;
   }
   if (S > 1 && epi_kind != EPI_PART && epi_kind != EPI_PARTRES) return false;
   const int need = (Kb + S * kRingWaves - 1) / (S * kRingWaves);   // k-blocks per wave
   int nk = 0;
   for (int v : kRingNk)
-    if (v >= need && v * nbw >= kRingDepth) {
+    if (v >= need && v * nbw >= kRingMinTiles) {
       nk = v;
       break;
     }

@@ -98,3 +98,33 @@ def test_dead_rows_do_not_reach_the_logits():
         dsi.dsi_kv_poison(rig.kv, 0)
         b = rig.prefill(0, toks, want_logits=True)
     assert np.all(np.isfinite(b)) and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("name", ["gqa_hd64", "hd96_kvf32", "tiny"])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 100])
+@pytest.mark.parametrize("off", [0, 1])
+def test_cache_import_export_round_trip(name, n, off):
+    """Every element comes back, from buffers at any element offset, and the rows past the imported ones stay."""
+    import torch
+    shape = S.SHAPES[name]
+    dt = torch.bfloat16 if shape.kvdtype == "bf16" else torch.float32
+    size = shape.n_kv_heads * n * shape.head_dim
+
+    def buf():
+        t = torch.randn(size + 8, device="cuda").to(dt)
+        return t, t.data_ptr() + off * t.element_size()
+
+    with _rig(shape, SEED, 2, 128) as rig:
+        whole = [torch.randn((shape.n_kv_heads, 128, shape.head_dim), device="cuda").to(dt) for _ in range(2)]
+        (k, kp), (v, vp) = buf(), buf()
+        l = shape.n_layers - 1
+        dsi.dsi_kv_import(rig.kv, 1, l, 128, *whole)
+        dsi.dsi_kv_import(rig.kv, 1, l, n, kp, vp)
+        (k2, k2p), (v2, v2p) = buf(), buf()
+        dsi.dsi_kv_export(rig.kv, 1, l, n, k2p, v2p)
+        got = [torch.empty_like(t) for t in whole]
+        dsi.dsi_kv_export(rig.kv, 1, l, 128, *got)
+        torch.cuda.synchronize()
+        for a, b, full, back in ((k, k2, whole[0], got[0]), (v, v2, whole[1], got[1])):
+            assert torch.equal(a[off:off + size], b[off:off + size])
+            assert torch.equal(back[:, :n].reshape(-1), a[off:off + size]) and torch.equal(back[:, n:], full[:, n:])
