@@ -564,68 +564,43 @@ constexpr int ring_depth(int nbw, int mt, int tiles) {
 // within 128 KB
 constexpr int ring_red_nb(int nbw, int mt) { return 16 / mt < nbw ? 16 / mt : nbw; }
 
-// RMSNorm sums of rows w and w + kRingWaves (the first 16 rows), requested
-// before the weights and reduced after the main loop; rows beyond 16 (wave
-// w: rows w + 8h) are loaded after it, all at once (42-row batch: step 4.65
-// -> 4.62 ms against one conditional load after another)
+// RMSNorm sums of the MT*16 rows, wave w rows w + 8h: requested before the
+// weights and reduced right after the first weight tiles have been requested,
+// while those are on their way.  Every load is unconditional (indices clamped
+// into the buffer, entries past it zeroed after), so the waits count exactly.
+// (Reduced after the main loop, with rows past the first 16 requested there,
+// gate/up took 38.1 instead of 37.1 us at one row tile and 46.4 instead of 43.8
+// at three, QKV 13.6 instead of 13.4 and 23.2 instead of 22.0; 8B shape.)
+template <int MT>
 struct RingSsq {
-  float v[2][kSsqPer];
+  float v[2 * MT][kSsqPer];
 };
-template <int EPI>
-__device__ __forceinline__ RingSsq ring_ssq_prefetch(const GemmArgs& a) {
-  RingSsq r;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int c = 0; c < kSsqPer; ++c) r.v[h][c] = 0.f;
+template <int EPI, int MT>
+__device__ __forceinline__ void ring_ssq_prefetch(const GemmArgs& a, RingSsq<MT>& r) {
   if constexpr (EPI == EPI_QKV || EPI == EPI_SILU) {
     if (a.ssq) {
+      const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int m = w + h * kRingWaves;
-        if (m < a.M) {
-          const float* p = a.ssq + (size_t)m * a.ssq_n;
+      for (int h = 0; h < 2 * MT; ++h) {
+        const float* p = a.ssq + (size_t)min(w + h * kRingWaves, a.M - 1) * a.ssq_n;
 #pragma unroll
-          for (int c = 0; c < kSsqPer; ++c)
-            if (lane + 64 * c < a.ssq_n) r.v[h][c] = p[lane + 64 * c];
-        }
+        for (int c = 0; c < kSsqPer; ++c) r.v[h][c] = p[min(lane + 64 * c, a.ssq_n - 1)];
       }
     }
   }
-  return r;
 }
 
 // rs[m] = 1/sqrt(sum / d + eps) for the MT*16 rows; row m is reduced by wave
 // m % 8 in the same order for every MT (lane entries, then a butterfly)
 template <int MT>
-__device__ __forceinline__ void ring_row_scales(const GemmArgs& a, const RingSsq& pre, float* rs) {
+__device__ __forceinline__ void ring_row_scales(const GemmArgs& a, const RingSsq<MT>& pre, float* rs) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // rows past the first 16: every load issued at once (indices clamped into
-  // the buffer, invalid entries zeroed after), one wait for all of them
-  constexpr int HL = 2 * MT - 2 > 0 ? 2 * MT - 2 : 1;
-  float late[HL][kSsqPer];
-#pragma unroll
-  for (int h = 2; h < 2 * MT; ++h) {
-    const int m = min(w + h * kRingWaves, a.M - 1);
-#pragma unroll
-    for (int c = 0; c < kSsqPer; ++c) late[h - 2][c] = a.ssq[(size_t)m * a.ssq_n + min(lane + 64 * c, a.ssq_n - 1)];
-  }
 #pragma unroll
   for (int h = 0; h < 2 * MT; ++h) {
     const int m = w + h * kRingWaves;
-    float v[kSsqPer];
-#pragma unroll
-    for (int c = 0; c < kSsqPer; ++c) {
-      if (h < 2) {
-        v[c] = pre.v[h < 2 ? h : 0][c];
-      } else {
-        v[c] = (m < a.M && lane + 64 * c < a.ssq_n) ? late[h < 2 ? 0 : h - 2][c] : 0.f;
-      }
-    }
     float sum = 0.f;
 #pragma unroll
-    for (int c = 0; c < kSsqPer; ++c) sum += v[c];
+    for (int c = 0; c < kSsqPer; ++c) sum += lane + 64 * c < a.ssq_n ? pre.v[h][c] : 0.f;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
     if (lane == 0 && m < a.M) rs[m] = 1.0f / sqrtf(sum / (float)a.norm_d + a.eps);
@@ -667,7 +642,8 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
   const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
   FoldIn fpre{};
   if constexpr (EPI == EPI_PARTRES) fpre = fold_prefetch(a, nb0, nbv);
-  const RingSsq spre = ring_ssq_prefetch<EPI>(a);
+  RingSsq<MT> spre;
+  ring_ssq_prefetch<EPI, MT>(a, spre);
   __builtin_amdgcn_sched_barrier(0);
   u32x4 ring[D];
   u32x4 xh[A][MT], xl[A][MT];
@@ -689,6 +665,10 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
     issue(r);
     __builtin_amdgcn_sched_barrier(0);   // issue order = ring order
   }
+  if constexpr (EPI == EPI_QKV || EPI == EPI_SILU) {
+    if (a.ssq) ring_row_scales<MT>(a, spre, rs);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   f32x4 acc[NBW][MT];
 #pragma unroll
   for (int j = 0; j < NBW; ++j)
@@ -706,7 +686,6 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
     if (u + D < N) issue(u + D);
     __builtin_amdgcn_sched_barrier(0);   // consume tile u, then refill its slot
   }
-  if (a.ssq) ring_row_scales<MT>(a, spre, rs);
 #pragma unroll
   for (int j0 = 0; j0 < NBW; j0 += NBR) {
     if (j0 > 0) __syncthreads();   // the previous round's tiles have been read

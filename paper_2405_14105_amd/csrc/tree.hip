@@ -23,7 +23,7 @@
 #include <limits.h>
 #include <math.h>
 
-#include "internal.h"
+#include "scan.h"
 
 namespace dsi {
 
@@ -61,13 +61,16 @@ __global__ __launch_bounds__(64) void k_tprep(TreeArgs a) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_tdecide(TreeArgs a) {
+// a wave per row at a time, 16 waves: 31 rows in two rounds (with 4 waves,
+// eight dependent rounds, 10.5 us)
+constexpr int kDecideThreads = 1024;
+__global__ __launch_bounds__(kDecideThreads) void k_tdecide(TreeArgs a) {
   __shared__ int sArg[kMaxRows];
   const int b = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int R = a.R;
   // each wave: the argmax of a row from its chunk (max, argmax) pairs;
   // larger value wins, ties to the smaller token id
-  for (int i = w; i < R; i += 4) {
+  for (int i = w; i < R; i += kDecideThreads / 64) {
     const size_t r = (size_t)b * R + i;
     float bv = -INFINITY;
     int bi = INT_MAX;
@@ -79,15 +82,7 @@ __global__ __launch_bounds__(256) void k_tdecide(TreeArgs a) {
         bi = ia;
       }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o);
-      const int oi = __shfl_xor(bi, o);
-      if (ov > bv || (ov == bv && oi < bi)) {
-        bv = ov;
-        bi = oi;
-      }
-    }
+    wave_argmax(bv, bi);
     if (lane == 0) sArg[i] = bi;
   }
   __syncthreads();
@@ -181,7 +176,7 @@ hipError_t launch_tree_prep(const TreeArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_tree_decide(const TreeArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_tdecide, dim3(a.B), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_tdecide, dim3(a.B), dim3(kDecideThreads), 0, s, a);
   return hipGetLastError();
 }
 
