@@ -131,6 +131,9 @@ __device__ __forceinline__ void pack_store8(const PackRef& p, int wtype, int m, 
   }
 }
 
+// cache policy of a buffer load: device scope (sc1)
+constexpr int kSc1 = 16;
+
 // Device-scope (sc1) 16-byte store: written through to the device's
 // coherence point, for partial results that another workgroup of the same
 // kernel reads with device-scope loads after an arrival counter says they

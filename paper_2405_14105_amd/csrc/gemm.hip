@@ -146,25 +146,39 @@ __device__ __forceinline__ void row_scales(const GemmArgs& a, const SsqIn& pre, 
 // them), taken by the threads in rounds of the workgroup size; the four
 // lanes of one (row, n-block) are adjacent, so the n-block's sum of squares
 // is a two-step butterfly.  The residual and gain values of each thread's
-// first item are loaded at the start of the kernel (fold_prefetch), off the
+// items are loaded at the start of the kernel (fold_prefetch), off the
 // critical path.
+template <int MT, int NBW, int NW>
 struct FoldIn {
-  float4 x, g;
+  // rounds of the workgroup over its rows x n-blocks x 4 items
+  static constexpr int R = (MT * 16 * NBW * 4 + NW * 64 - 1) / (NW * 64);
+  float4 x[R], g[R];
 };
-__device__ __forceinline__ FoldIn fold_prefetch(const GemmArgs& a, int nb0, int nbv) {
-  FoldIn f{};
-  const int it = threadIdx.x;
-  if (it < a.M * nbv * 4) {
-    const int q = it & 3, jm = it >> 2;
-    const int m = jm / nbv, n0 = (nb0 + jm % nbv) * 16 + q * 4;
-    f.x = *(const float4*)(a.epi.x + (size_t)m * a.epi.ld + n0);
-    f.g = *(const float4*)(a.epi.gain + n0);
+// item -> row, first feature; a whole group divides by a constant
+template <int NBW>
+__device__ __forceinline__ void fold_item(int it, int nb0, int nbv, int& m, int& nb) {
+  const int jm = it >> 2;
+  m = nbv == NBW ? jm / NBW : jm / nbv;
+  nb = nb0 + (nbv == NBW ? jm % NBW : jm % nbv);
+}
+template <int MT, int NBW, int NW>
+__device__ __forceinline__ void fold_prefetch(const GemmArgs& a, int nb0, int nbv, FoldIn<MT, NBW, NW>& f) {
+#pragma unroll
+  for (int r = 0; r < FoldIn<MT, NBW, NW>::R; ++r) {
+    const int it = r * NW * 64 + threadIdx.x;
+    if (it < a.M * nbv * 4) {
+      int m, nb;
+      fold_item<NBW>(it, nb0, nbv, m, nb);
+      const int n0 = nb * 16 + (it & 3) * 4;
+      f.x[r] = *(const float4*)(a.epi.x + (size_t)m * a.epi.ld + n0);
+      f.g[r] = *(const float4*)(a.epi.gain + n0);
+    }
   }
-  return f;
 }
 
-template <int WT, int NW>
-__device__ __forceinline__ void part_fold(const GemmArgs& a, int nb0, int nbv, const FoldIn& pre) {
+template <int WT, int MT, int NBW, int NW>
+__device__ __forceinline__ void part_fold(const GemmArgs& a, int nb0, int nbv, const FoldIn<MT, NBW, NW>& pre) {
+  constexpr int R = FoldIn<MT, NBW, NW>::R;
   __shared__ int s_last;
   const EpiArgs& e = a.epi;
   const int g = blockIdx.x / a.S;
@@ -174,37 +188,43 @@ __device__ __forceinline__ void part_fold(const GemmArgs& a, int nb0, int nbv, c
     s_last = __hip_atomic_fetch_add(e.cnt + g, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.S - 1;
   __syncthreads();
   if (!s_last) return;
+  // every split's values of every round are requested before the first add
+  // (split index clamped; the extra loads are never added), 16 bytes a load,
+  // then added in split order.  Device-scope (sc1) buffer loads; items past
+  // the rows read out of range, which returns zeros without an access.
   const int total = a.M * nbv * 4;
-  for (int base = 0; base < total; base += NW * 64) {   // uniform trip count
-    const int it = base + threadIdx.x;
+  const int bytes = (int)(a.S * e.part_stride * sizeof(float));
+  const __amdgpu_buffer_rsrc_t P = __builtin_amdgcn_make_buffer_rsrc(e.out, (short)0, bytes, 0x00020000);
+  u32x4 pv[R][kMaxSplits];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int it = r * NW * 64 + threadIdx.x;
+    int m, nb;
+    fold_item<NBW>(it, nb0, nbv, m, nb);
+    const int off = (m * e.ld + nb * 16 + (it & 3) * 4) * 4;
+#pragma unroll
+    for (int sp = 0; sp < kMaxSplits; ++sp)
+      pv[r][sp] = __builtin_amdgcn_raw_buffer_load_b128(
+          P, it < total ? off + min(sp, a.S - 1) * (int)(e.part_stride * 4) : 0x7ffffff0, 0, kSc1);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int it = r * NW * 64 + threadIdx.x;
     const bool ok = it < total;
-    const int q = it & 3, jm = it >> 2;
-    const int m = ok ? jm / nbv : 0, nb = nb0 + (ok ? jm % nbv : 0);
-    const int n0 = nb * 16 + q * 4;
+    int m, nb;
+    fold_item<NBW>(it, nb0, nbv, m, nb);
+    const int n0 = nb * 16 + (it & 3) * 4;
     float sq = 0.f;
     if (ok) {
-      // every split's values are requested before the first add (split
-      // index clamped; the extra loads are never added), then added in
-      // split order
-      float pv[kMaxSplits][4];
-#pragma unroll
-      for (int sp = 0; sp < kMaxSplits; ++sp) {
-        const float* pp = e.out + min(sp, a.S - 1) * e.part_stride + (size_t)m * e.ld + n0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) pv[sp][c] = __hip_atomic_load(pp + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      float4 xv = pre.x, gv = pre.g;
-      if (base > 0) {
-        xv = *(const float4*)(e.x + (size_t)m * e.ld + n0);
-        gv = *(const float4*)(e.gain + n0);
-      }
+      float4 xv = pre.x[r];
+      const float4 gv = pre.g[r];
 #pragma unroll
       for (int sp = 0; sp < kMaxSplits; ++sp) {
         if (sp < a.S) {
-          xv.x += pv[sp][0];
-          xv.y += pv[sp][1];
-          xv.z += pv[sp][2];
-          xv.w += pv[sp][3];
+          xv.x += __uint_as_float(pv[r][sp][0]);
+          xv.y += __uint_as_float(pv[r][sp][1]);
+          xv.z += __uint_as_float(pv[r][sp][2]);
+          xv.w += __uint_as_float(pv[r][sp][3]);
         }
       }
       *(float4*)(e.x + (size_t)m * e.ld + n0) = xv;
@@ -215,7 +235,7 @@ __device__ __forceinline__ void part_fold(const GemmArgs& a, int nb0, int nbv, c
     }
     sq += __shfl_xor(sq, 1);
     sq += __shfl_xor(sq, 2);
-    if (ok && q == 0) e.ssq[(size_t)m * a.Nb + nb] = sq;
+    if (ok && (it & 3) == 0) e.ssq[(size_t)m * a.Nb + nb] = sq;
   }
   if (threadIdx.x == 0) __hip_atomic_store(e.cnt + g, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -370,8 +390,8 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(GemmArgs a) {
   // waits for no weight load
   const SsqIn spre = ssq_prefetch<EPI>(a);
   const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
-  FoldIn fpre{};
-  if constexpr (EPI == EPI_PARTRES) fpre = fold_prefetch(a, nb0, nbv);
+  FoldIn<MT, NBW, NW> fpre;
+  if constexpr (EPI == EPI_PARTRES) fold_prefetch(a, nb0, nbv, fpre);
   if constexpr (kPipelined<MT, EPI>) {
     if (nk > 0) {
       // two weight register sets used in turn (a copy from one to the other
@@ -471,7 +491,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(GemmArgs a) {
     finish<W_BF16, EPI, MT, NBR, NW>(a, red, a.ssq ? rs : nullptr, nb0 + j0, min(NBR, NBW - j0),
                                      wk.split, pre);
   }
-  if constexpr (EPI == EPI_PARTRES) part_fold<W_BF16, NW>(a, nb0, nbv, fpre);
+  if constexpr (EPI == EPI_PARTRES) part_fold<W_BF16, MT, NBW, NW>(a, nb0, nbv, fpre);
 }
 
 template <int MT, int NBW, int NW, int EPI>
@@ -486,8 +506,8 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(GemmArgs a) {
   const float4* __restrict__ W = (const float4*)a.W;
   const float4* __restrict__ X = (const float4*)a.Xhi;
   const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
-  FoldIn fpre{};
-  if constexpr (EPI == EPI_PARTRES) fpre = fold_prefetch(a, nb0, nbv);
+  FoldIn<MT, NBW, NW> fpre;
+  if constexpr (EPI == EPI_PARTRES) fold_prefetch(a, nb0, nbv, fpre);
   if (a.ssq) row_scales<NW>(a, ssq_prefetch<EPI>(a), rs);
 
   f32x4 acc[NBW][MT];
@@ -527,7 +547,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(GemmArgs a) {
     for (int t = 0; t < MT; ++t) red[((w * NBW + j) * MT + t) * 64 + lane] = acc[j][t];
   __syncthreads();
   finish<W_F32, EPI, MT, NBW, NW>(a, red, a.ssq ? rs : nullptr, nb0, NBW, wk.split, pre);
-  if constexpr (EPI == EPI_PARTRES) part_fold<W_F32, NW>(a, nb0, nbv, fpre);
+  if constexpr (EPI == EPI_PARTRES) part_fold<W_F32, MT, NBW, NW>(a, nb0, nbv, fpre);
 }
 
 // ------------------------------------------------------------------ ring GEMM
@@ -640,8 +660,8 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
   };
 
   const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
-  FoldIn fpre{};
-  if constexpr (EPI == EPI_PARTRES) fpre = fold_prefetch(a, nb0, nbv);
+  FoldIn<MT, NBW, NW> fpre;
+  if constexpr (EPI == EPI_PARTRES) fold_prefetch(a, nb0, nbv, fpre);
   RingSsq<MT> spre;
   ring_ssq_prefetch<EPI, MT>(a, spre);
   __builtin_amdgcn_sched_barrier(0);
@@ -697,7 +717,7 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
     __syncthreads();
     finish<W_BF16, EPI, MT, NBR, NW>(a, red, a.ssq ? rs : nullptr, nb0 + j0, min(NBR, NBW - j0), split, pre);
   }
-  if constexpr (EPI == EPI_PARTRES) part_fold<W_BF16, NW>(a, nb0, nbv, fpre);
+  if constexpr (EPI == EPI_PARTRES) part_fold<W_BF16, MT, NBW, NW>(a, nb0, nbv, fpre);
 }
 
 // n-blocks per workgroup of each role's ring layout: the O projection one
