@@ -127,8 +127,8 @@ dsi_status dsi_kv_destroy(dsi_kv* kv);
  * drafts a task builds on).  d_last_logits (nullable, device [V] fp32)
  * receives the logits of the last token.  Fails with DSI_ECAPACITY if
  * length + n may exceed max_len, with no side effects.  The tokens run in
- * chunks of DSI_MAX_ROWS (many of them in one forward where the model and the
- * cache are bf16: dsi_kv_create reserves the workspace); a chunk holding an id outside [0, V) does not
+ * chunks of DSI_MAX_ROWS, many of them in one forward (the first prompt longer
+ * than one chunk reserves the model's workspace for it); a chunk holding an id outside [0, V) does not
  * advance the length and is reported by the next synchronising call
  * (DSI_EINVAL).  Stream-ordered; d_tokens is caller-owned and only read by
  * the call's stream work. */

@@ -195,13 +195,14 @@ hipError_t launch_restream(const void* src, int Nb, int Kb, int G, const RingCfg
 // launchers (gemm.hip)
 hipError_t launch_gemm(int wtype, int mt, const GemmArgs& a, hipStream_t s);
 
-// prefill (prefill.hip): bf16 weights, any number of rows
+// prefill (prefill.hip): any number of rows
 constexpr int kWideSplits = 8;   // K splits at most
 struct WideCfg {
   int mt = 8;           // m-blocks (16 rows) per workgroup tile, 4..8
   int nwn = 4;          // waves along the output features (2 or 4), 4 n-blocks each
 };
-hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s);
+hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s);   // bf16 weights
+hipError_t launch_gemm_wide_f32(const GemmArgs& a, hipStream_t s);                   // fp32, no K split
 // out of the S tile-order partials (EPI_TILE) of a QKV or gate/up GEMM
 hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride, int S, hipStream_t s);
 
@@ -261,13 +262,13 @@ struct AttnArgs {
 };
 constexpr int kAttnWaves = 8;                       // waves per attention workgroup (default)
 hipError_t launch_attention(int kv_bf16, int hd, const AttnArgs& a, hipStream_t s);
-// causal attention of one window's prompt rows (rows.gpos) over a bf16 cache
+// causal attention of one window's prompt rows (rows.gpos) over the cache
 // (prefill.hip), the keys in n_chunks chunks of `chunk` (a multiple of 64);
 // several chunks leave partials [n_kv][units][chunks][16][hd] in part_o and
 // part_ml.  Rows from 16 * rb0 on only (part_o's units count from there).
 // n_qtiles, waves unused.
 int prefill_units(int rows, int group);   // 16-row units of one KV head
-hipError_t launch_attention_prefill(int hd, const AttnArgs& a, int rb0, hipStream_t s);
+hipError_t launch_attention_prefill(int kv_bf16, int hd, const AttnArgs& a, int rb0, hipStream_t s);
 
 // verification (verify.hip)
 struct VerifyArgs {

@@ -1,5 +1,5 @@
 // Prefill: the layer GEMMs and the attention of up to kWideRows prompt rows
-// per forward (bf16 weights and cache).
+// per forward.
 //
 // A verification window is bound by streaming the weights once; a prompt of
 // hundreds of rows is bound by the matrix cores, if the weights are read once
@@ -8,7 +8,7 @@
 // 0.85, O 0.65, attention 0.4); in one forward they take 1.6 ms (0.81, 0.36,
 // 0.24, 0.12, 0.11).
 //
-// GEMM.  Same products as the window GEMMs: pre-tiled weights against the
+// GEMM (bf16 weights).  Same products as the window GEMMs: pre-tiled weights against the
 // hi/lo activation packs, two 16x16x32 MFMAs per product, fp32 sums.  A
 // workgroup of 8 waves makes a tile of NWN * 64 features x MT * 16 rows:
 //  * NWN waves lie along the features, four n-blocks each, and 8 / NWN groups
@@ -196,6 +196,46 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
   }
 }
 
+// fp32 weights and activations: the window kernel's tile (16 features x 64
+// rows, four waves splitting K as k_gemm_f32 does) over any number of row
+// tiles, for models small enough that launches are most of what they cost.
+template <int EPI>
+__global__ __launch_bounds__(256) void k_gemm_wide_f32(GemmArgs a) {
+  constexpr int NW = 4, MT = 4;
+  __shared__ f32x4 red[NW * MT * 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int nb = blockIdx.x, mb0 = blockIdx.y * MT, Mb = (a.M + 15) >> 4;
+  const int per = (a.Kb + NW - 1) / NW, kb0 = min(a.Kb, w * per), kb1 = min(a.Kb, kb0 + per);
+  const float4* __restrict__ W = (const float4*)a.W;
+  const float4* __restrict__ X = (const float4*)a.Xhi;
+  f32x4 acc[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb = kb0; kb < kb1; ++kb) {
+    const size_t wi = (((size_t)nb * a.Kb + kb) * 64 + lane) * 2;
+    const F8 wf{W[wi], W[wi + 1]};
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const size_t xi = (((size_t)min(mb0 + t, Mb - 1) * a.Kb + kb) * 64 + lane) * 2;
+      const F8 xf{X[xi], X[xi + 1]};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[t] = mfma_f32(f8_get(wf, e), f8_get(xf, e), acc[t]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) red[(w * MT + t) * 64 + lane] = acc[t];
+  __syncthreads();
+  // wave w finishes row tile w
+  f32x4 v = red[w * 64 + lane];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) v += red[(i * MT + w) * 64 + lane];
+  const int m = (mb0 + w) * 16 + (lane & 15);
+  if (m >= a.M) return;
+  EpiIn pre{};
+  if constexpr (EPI == EPI_QKV) pre = qkv_inputs(a.epi, nb, (lane >> 4) * 4, m);
+  epilogue<W_F32, EPI>(a.epi, nb, (lane >> 4) * 4, m, 0, v, pre);
+}
+
 // sums the splits' tile-order partials (EPI_TILE) in split order and applies
 // the role's epilogue; one wave per 16 x 16 tile
 template <int EPI>
@@ -233,12 +273,17 @@ __global__ __launch_bounds__(256) void k_wide_fold(GemmArgs a, const float* part
 // 8B, 2048 rows: 114 us, against 32 x 15 us of the window kernel, which
 // reads the keys once per 16 queries.  With few row blocks the keys are cut
 // into chunks as well (13B, 77 rows over 900 keys: 51 -> 19 + 5 us).
-template <int HD>
+template <int KVB, int HD>
 __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n_units, int n_ublk) {
   constexpr int DS = HD / 32;
   constexpr int DT = HD / 16;
   constexpr int ST = 4 * DS;                 // tiles of a 32-key step: 2 DS of K, DT of V
-  __shared__ u32x4 kv[2][2 * ST][64];        // two stages of 64 keys
+  // a lane's eight elements of a tile: one 16-byte piece of a bf16 cache, two
+  // of an fp32 cache
+  struct Frag {
+    u32x4 p[KVB ? 1 : 2];
+  };
+  __shared__ u32x4 kv[2][2 * ST][KVB ? 1 : 2][64];   // two stages of 64 keys
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kvh = blockIdx.x % a.n_kv, ic = blockIdx.x / a.n_kv;
@@ -261,54 +306,72 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
   const int row = rb * 16 + r16;
   const int qpos = pos0 + r16;
   const size_t base = ((size_t)a.rows.window0 * a.n_kv + kvh) * (size_t)a.maxlen * HD;
-  const uint16_t* kc = (const uint16_t*)a.kc + base;
-  const uint16_t* vc = (const uint16_t*)a.vc + base;
+  constexpr int ESZ = KVB ? 2 : 4;
+  const char* kc = (const char*)a.kc + base * ESZ;
+  const char* vc = (const char*)a.vc + base * ESZ;
   const float scale2 = a.scale * 1.44269504088896340736f;   // log2 e
 
   // this wave's DS tiles of a stage: waves 0-3 the first 32 keys, 4-7 the
   // second; of each four, two load K (16-key halves), two V
   const int half = w >> 2, part = w & 3;
-  auto load_stage = [&](u32x4 (&d)[DS], int st) {
+  auto load_stage = [&](Frag (&d)[DS], int st) {
     const int p0 = st * 64 + half * 32;
 #pragma unroll
     for (int p = 0; p < DS; ++p) {
-      if (part < 2) d[p] = *(const u32x4*)(kc + kc_off(p0 + (r16 >> 2) * 8 + part * 4 + (r16 & 3), p * 32 + kgrp, HD));
-      else d[p] = *(const u32x4*)(vc + vc_off(p0 + kgrp, ((part - 2) * DS + p) * 16 + r16, HD));
+      const char* src = part < 2 ? kc + kc_off(p0 + (r16 >> 2) * 8 + part * 4 + (r16 & 3), p * 32 + kgrp, HD) * ESZ
+                                 : vc + vc_off(p0 + kgrp, ((part - 2) * DS + p) * 16 + r16, HD) * ESZ;
+      d[p] = *(const Frag*)src;
     }
   };
-  auto store_stage = [&](const u32x4 (&d)[DS], int buf) {
+  auto store_stage = [&](const Frag (&d)[DS], int buf) {
 #pragma unroll
-    for (int p = 0; p < DS; ++p) kv[buf][half * ST + part * DS + p][lane] = d[p];
+    for (int p = 0; p < DS; ++p)
+#pragma unroll
+      for (int i = 0; i < (KVB ? 1 : 2); ++i) kv[buf][half * ST + part * DS + p][i][lane] = d[p].p[i];
   };
 
   const float* qrow = a.q + (size_t)min(row, R - 1) * (a.n_heads * HD) + head * HD;
   bf16x8 qh[DS], ql[DS];
-  u32x4 sr[DS];
+  float qf[DS][8];
+  Frag sr[DS];
   load_stage(sr, st0 < st1 ? st0 : 0);
 #pragma unroll
   for (int ds = 0; ds < DS; ++ds) {
     const float4 a0 = *(const float4*)(qrow + ds * 32 + kgrp), a1 = *(const float4*)(qrow + ds * 32 + kgrp + 4);
     const float v[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-    u32x4 h, l;
-    split8(v, h, l);
-    qh[ds] = as_bf16x8(h);
-    ql[ds] = as_bf16x8(l);
+    if constexpr (KVB) {
+      u32x4 h, l;
+      split8(v, h, l);
+      qh[ds] = as_bf16x8(h);
+      ql[ds] = as_bf16x8(l);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qf[ds][e] = v[e];
+    }
   }
   float mrun = -INFINITY, lrun = 0.f;
   f32x4 o[DT];
 #pragma unroll
   for (int t = 0; t < DT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto step = [&](int p0, const u32x4 (*tl)[64]) {
+  auto f32_at = [](const u32x4 (&x)[KVB ? 1 : 2][64], int lane, int e) {
+    return __uint_as_float(x[KVB ? 0 : e >> 2][lane][e & 3]);
+  };
+  auto step = [&](int p0, const u32x4 (*tl)[KVB ? 1 : 2][64]) {
     f32x4 st[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ds = 0; ds < DS; ++ds) {
-        const bf16x8 kb = as_bf16x8(tl[t * DS + ds][lane]);
-        st[t] = mfma_bf16(kb, qh[ds], st[t]);
-        st[t] = mfma_bf16(kb, ql[ds], st[t]);
+        if constexpr (KVB) {
+          const bf16x8 kb = as_bf16x8(tl[t * DS + ds][0][lane]);
+          st[t] = mfma_bf16(kb, qh[ds], st[t]);
+          st[t] = mfma_bf16(kb, ql[ds], st[t]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) st[t] = mfma_f32(f32_at(tl[t * DS + ds], lane, e), qf[ds][e], st[t]);
+        }
       }
     }
     const bool full = p0 + 32 <= pos0 + 1;
@@ -339,9 +402,13 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
     }
     lrun += lsum;
     mrun = mnew;
-    u32x4 h, l;
-    split8(pv, h, l);
-    const bf16x8 ph = as_bf16x8(h), pl = as_bf16x8(l);
+    bf16x8 ph, pl;
+    if constexpr (KVB) {
+      u32x4 h, l;
+      split8(pv, h, l);
+      ph = as_bf16x8(h);
+      pl = as_bf16x8(l);
+    }
     // keys past the block's rows may be dead cache rows: they have
     // probability 0, and their values are zeroed so that 0 * NaN never
     // reaches the output
@@ -349,14 +416,22 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
     const bool tail = p0 + 32 > kw;
 #pragma unroll
     for (int t = 0; t < DT; ++t) {
-      u32x4 vv = tl[2 * DS + t][lane];
-      if (tail) {
+      if constexpr (KVB) {
+        u32x4 vv = tl[2 * DS + t][0][lane];
+        if (tail) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          vv[i] &= (2 * i < nv ? 0x0000FFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
+          for (int i = 0; i < 4; ++i)
+            vv[i] &= (2 * i < nv ? 0x0000FFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
+        }
+        o[t] = mfma_bf16(as_bf16x8(vv), ph, o[t]);
+        o[t] = mfma_bf16(as_bf16x8(vv), pl, o[t]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float vv = f32_at(tl[2 * DS + t], lane, e);
+          o[t] = mfma_f32(e < nv ? vv : 0.f, pv[e], o[t]);
+        }
       }
-      o[t] = mfma_bf16(as_bf16x8(vv), ph, o[t]);
-      o[t] = mfma_bf16(as_bf16x8(vv), pl, o[t]);
     }
   };
 
@@ -461,6 +536,18 @@ hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s) 
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_gemm_wide_f32(const GemmArgs& a, hipStream_t s) {
+  if (a.M < 1 || a.Nb < 1 || a.Kb < 1 || a.S != 1 || a.G != 1) return hipErrorInvalidValue;
+  const dim3 grid(a.Nb, (a.M + 63) / 64), blk(256);
+  switch (a.epi.kind) {
+    case EPI_PART: hipLaunchKernelGGL((k_gemm_wide_f32<EPI_PART>), grid, blk, 0, s, a); break;
+    case EPI_QKV: hipLaunchKernelGGL((k_gemm_wide_f32<EPI_QKV>), grid, blk, 0, s, a); break;
+    case EPI_SILU: hipLaunchKernelGGL((k_gemm_wide_f32<EPI_SILU>), grid, blk, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride, int S, hipStream_t s) {
   if (S < 1 || S > kWideSplits) return hipErrorInvalidValue;
   const dim3 grid((a.Nb + 3) / 4, (a.M + 15) / 16), blk(256);
@@ -472,25 +559,34 @@ hipError_t launch_wide_fold(const GemmArgs& a, const float* part, size_t stride,
 
 int prefill_units(int rows, int group) { return (rows + 15) / 16 * group; }
 
-template <int HD>
+template <int KVB, int HD>
 hipError_t launch_attn_prefill_hd(const AttnArgs& a, int rb0, int units, hipStream_t s) {
   const int ub = (units + 7) / 8;
-  hipLaunchKernelGGL((k_attn_prefill<HD>), dim3(ub * a.n_kv * a.n_chunks), dim3(512), 0, s, a, rb0, units, ub);
+  hipLaunchKernelGGL((k_attn_prefill<KVB, HD>), dim3(ub * a.n_kv * a.n_chunks), dim3(512), 0, s, a, rb0, units, ub);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_chunks == 1) return e;
   hipLaunchKernelGGL((k_attn_prefill_combine<HD>), dim3(units * a.n_kv), dim3(HD * 4), 0, s, a, rb0, units);
   return hipGetLastError();
 }
 
-hipError_t launch_attention_prefill(int hd, const AttnArgs& a, int rb0, hipStream_t s) {
+hipError_t launch_attention_prefill(int kv_bf16, int hd, const AttnArgs& a, int rb0, hipStream_t s) {
   const int units = prefill_units(a.rows.rows_per_window - 16 * rb0, a.n_heads / a.n_kv);
   if (rb0 < 0 || units < 1) return hipErrorInvalidValue;
   if (a.n_chunks < 1 || a.chunk < 64 || a.chunk % 64 || !a.rows.gpos) return hipErrorInvalidValue;
-  switch (hd) {
-    case 32: return launch_attn_prefill_hd<32>(a, rb0, units, s);
-    case 64: return launch_attn_prefill_hd<64>(a, rb0, units, s);
-    case 96: return launch_attn_prefill_hd<96>(a, rb0, units, s);
-    case 128: return launch_attn_prefill_hd<128>(a, rb0, units, s);
+  if (kv_bf16) {
+    switch (hd) {
+      case 32: return launch_attn_prefill_hd<1, 32>(a, rb0, units, s);
+      case 64: return launch_attn_prefill_hd<1, 64>(a, rb0, units, s);
+      case 96: return launch_attn_prefill_hd<1, 96>(a, rb0, units, s);
+      case 128: return launch_attn_prefill_hd<1, 128>(a, rb0, units, s);
+    }
+  } else {
+    switch (hd) {
+      case 32: return launch_attn_prefill_hd<0, 32>(a, rb0, units, s);
+      case 64: return launch_attn_prefill_hd<0, 64>(a, rb0, units, s);
+      case 96: return launch_attn_prefill_hd<0, 96>(a, rb0, units, s);
+      case 128: return launch_attn_prefill_hd<0, 128>(a, rb0, units, s);
+    }
   }
   return hipErrorInvalidValue;
 }

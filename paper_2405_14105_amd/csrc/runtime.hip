@@ -140,6 +140,7 @@ struct dsi_model {
   int* err = nullptr;
   DevBuf attn_o, attn_ml;
   WideWs wide;
+  int wide_refused = 0;         // rows there was no memory for
   int live_kv = 0;
   // diagnostics: event pairs around one kernel class
   int prof_class = 0;
@@ -203,51 +204,68 @@ void* kv_ptr(const dsi_kv* kv, void* base, int layer, int window) {
   return (char*)base + off * kv->m->kvesz;
 }
 
-PackRef make_pack(dsi_model* m, std::vector<void*>& allocs, int rows, int Kb, dsi_status* st) {
+PackRef make_pack(dsi_model* m, int Kb, dsi_status* st) {
   PackRef p{};
   p.Kb = Kb;
-  const size_t elems = (size_t)cdiv(rows, 16) * Kb * 512;
-  *st = dev_alloc(allocs, &p.hi, elems * m->esz);
-  if (*st == DSI_OK && m->wtype == W_BF16) *st = dev_alloc(allocs, &p.lo, elems * 2);
+  const size_t elems = (size_t)kMaxMt * Kb * 512;
+  *st = dev_alloc(m->allocs, &p.hi, elems * m->esz);
+  if (*st == DSI_OK && m->wtype == W_BF16) *st = dev_alloc(m->allocs, &p.lo, elems * 2);
   return p;
 }
 
-// Prefill forwards of more than kMaxRows rows: bf16 weights and cache.
-// Reserves the workspace for a cache of max_len positions (kWideRows rows at
-// most).  A model that has no memory for it keeps the one it has, or none:
-// prompts then run in narrower forwards.  An outgrown workspace stays until
-// the model is destroyed (launches of it may be in flight or captured); the
-// sizes are powers of two, so all of them together hold less than twice the
-// last.
+// The workspace of prefill forwards of more than kMaxRows rows, reserved by
+// the first prompt that needs it, for the cache's max_len (kWideRows rows at
+// most), in one allocation.  A model that has no memory for it keeps the one
+// it has, or none: prompts then run in narrower forwards.  An outgrown
+// workspace stays until the model is destroyed (launches of it may be in
+// flight or captured); the sizes are powers of two, so all of them together
+// hold less than twice the last.
 void wide_reserve(dsi_model* m, int max_len) {
-  if (m->wtype != W_BF16 || !m->kvb || max_len <= kMaxRows) return;
   int rows = 2 * kMaxRows;
   while (rows < max_len && rows < kWideRows) rows *= 2;
-  if (rows <= m->wide.rows) return;
-  const std::string keep = g_err;
-  std::vector<void*> list;
+  if (rows <= m->wide.rows || rows <= m->wide_refused) return;
   WideWs w;
-  dsi_status st = DSI_OK;
-  auto A = [&](void** p, size_t bytes) {
-    if (st == DSI_OK) st = dev_alloc(list, p, bytes);
-  };
   w.rows = rows;
   // one partial of the widest launch, or several of a launch with fewer rows
   w.delta_bytes = std::max((size_t)rows * m->d * 4, (size_t)64 << 20);
-  A((void**)&w.x, (size_t)rows * m->d * 4);
-  A((void**)&w.delta, w.delta_bytes);
-  if (st == DSI_OK) w.pk_d = make_pack(m, list, rows, m->Kb_d, &st);
-  if (st == DSI_OK) w.pk_q = make_pack(m, list, rows, m->Kb_q, &st);
-  if (st == DSI_OK) w.pk_ff = make_pack(m, list, rows, m->Kb_ff, &st);
-  A((void**)&w.qbuf, (size_t)rows * m->qdim * 4);
-  A((void**)&w.rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
-  A((void**)&w.gpos, (size_t)(kWideRows / kMaxRows + 1) * sizeof(int));
-  if (st != DSI_OK) {
-    free_list(list);
-    g_err = keep;
+  if (m->wtype != W_BF16) w.delta_bytes = (size_t)rows * m->d * 4;   // fp32 GEMMs do not split
+  size_t total = 0;
+  std::vector<std::pair<void**, size_t>> parts;
+  auto part = [&](void** p, size_t bytes) {
+    parts.push_back({p, total});
+    total += round_up(bytes, 256);
+  };
+  auto pack = [&](PackRef& p, int Kb) {
+    p.Kb = Kb;
+    const size_t elems = (size_t)rows * Kb * 32;
+    part(&p.hi, elems * m->esz);
+    if (m->wtype == W_BF16) part(&p.lo, elems * 2);
+  };
+  part((void**)&w.x, (size_t)rows * m->d * 4);
+  part((void**)&w.delta, w.delta_bytes);
+  pack(w.pk_d, m->Kb_d);
+  pack(w.pk_q, m->Kb_q);
+  const size_t ff0 = total;
+  pack(w.pk_ff, m->Kb_ff);
+  const size_t ff1 = total;
+  part((void**)&w.qbuf, (size_t)rows * m->qdim * 4);
+  part((void**)&w.rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
+  part((void**)&w.gpos, (size_t)(kWideRows / kMaxRows + 1) * sizeof(int));
+  char* slab = nullptr;
+  if (hipMalloc((void**)&slab, total) != hipSuccess) {
+    hipGetLastError();
+    m->wide_refused = rows;
     return;
   }
-  m->allocs.insert(m->allocs.end(), list.begin(), list.end());
+  for (auto& p : parts) *p.first = slab + p.second;
+  // the FFN pack's columns past d_ff are multiplied (by zero weights) and
+  // never written
+  if (m->ff % 32 && launch_fill_zero(slab + ff0, ff1 - ff0, m->stream) != hipSuccess) {
+    hipFree(slab);
+    m->wide_refused = rows;
+    return;
+  }
+  m->allocs.push_back(slab);
   m->wide = w;
 }
 
@@ -666,7 +684,18 @@ WidePlan wide_plan(const dsi_model* m, int M, int Nb, int Kb, bool fused) {
 dsi_status wide_gemm(dsi_model* m, const WidePlan& p, GemmArgs g, int M, int* splits) {
   const bool fused = g.epi.kind == EPI_QKV || g.epi.kind == EPI_SILU;
   g.M = M;
-  g.S = p.S;
+  g.S = m->wtype == W_BF16 ? p.S : 1;
+  if (m->wtype != W_BF16) {
+    if (!fused) {
+      g.epi.kind = EPI_PART;
+      g.epi.out = m->wide.delta;
+      g.epi.ld = m->d;
+      g.epi.part_stride = (size_t)M * m->d;
+      *splits = 1;
+    }
+    HIP_TRY(launch_gemm_wide_f32(g, m->stream));
+    return DSI_OK;
+  }
   if (fused && p.S == 1) {
     HIP_TRY(launch_gemm_wide(g, p.cfg, m->stream));
     return DSI_OK;
@@ -686,6 +715,55 @@ dsi_status wide_gemm(dsi_model* m, const WidePlan& p, GemmArgs g, int M, int* sp
     *splits = p.S;
   }
   return DSI_OK;
+}
+
+// Key chunks of the attention of rows 16 rb0 .. M - 1 over `keys` keys (see
+// run_prefill), and the most row partials they leave over that many keys or
+// fewer.
+struct Chunks {
+  int n, size;
+  size_t parts;
+};
+Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
+  const int units = prefill_units(M - 16 * rb0, m->hq / m->hkv);
+  const int want = std::max(1, std::min(cdiv(keys, 256), 256 / (cdiv(units, 8) * m->hkv)));
+  Chunks c;
+  c.size = (int)round_up((size_t)cdiv(keys, want), 64);
+  c.n = cdiv(keys, c.size);
+  c.parts = want == 1 ? 0 : (size_t)m->hkv * units * want * 16;
+  return c;
+}
+
+// Rows per wide forward of a prompt of n tokens: forwards of about equal size,
+// whole groups of kMaxRows rows; 0 when the prompt runs in 64-row forwards
+// instead.  Reserves what the forwards need, so that they allocate nothing;
+// a capturing stream cannot, and takes wide forwards only where earlier
+// prompts have reserved enough.
+int wide_rows(dsi_model* m, const dsi_kv* kv, int window, int n) {
+  if (n <= kMaxRows) return 0;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (m->stream && hipStreamIsCapturing(m->stream, &cap) != hipSuccess) {
+    hipGetLastError();
+    return 0;
+  }
+  const bool may = cap == hipStreamCaptureStatusNone;
+  if (may) wide_reserve(m, kv->max_len);
+  if (!m->wide.rows) return 0;
+  const int forwards = cdiv(n, m->wide.rows);
+  const int each = (int)round_up((size_t)cdiv(n, forwards), kMaxRows);
+  const int keys = (int)(kv->hi[window] + n);
+  size_t parts = 0;
+  for (int M : {std::min(n, each), (n - 1) % each + 1})
+    parts = std::max(parts, std::max(key_chunks(m, M, 0, keys).parts, key_chunks(m, M, (M - 1) / 16, keys).parts));
+  const size_t ob = parts * m->hd * sizeof(float), mb = parts * sizeof(float2);
+  if (may) {
+    const std::string keep = g_err;
+    if (ensure(m->attn_o, ob) != DSI_OK || ensure(m->attn_ml, mb) != DSI_OK) {
+      g_err = keep;
+      return 0;
+    }
+  }
+  return m->attn_o.bytes >= ob && m->attn_ml.bytes >= mb ? each : 0;
 }
 
 // One forward of M (<= m->wide.rows) prompt tokens of one window, appended to
@@ -719,22 +797,7 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
   // leave CUs idle; of the last layer the last row block only
   const int keys = (int)(kv->hi[window] + M);
   const int rb_last = (M - 1) / 16;
-  struct Chunks {
-    int n, size;
-  };
-  auto key_chunks = [&](int rb0, Chunks* c) -> dsi_status {
-    const int units = prefill_units(M - 16 * rb0, m->hq / m->hkv);
-    const int want = std::max(1, std::min(cdiv(keys, 256), 256 / (cdiv(units, 8) * m->hkv)));
-    c->size = (int)round_up((size_t)cdiv(keys, want), 64);
-    c->n = cdiv(keys, c->size);
-    if (c->n == 1) return DSI_OK;
-    const size_t parts = (size_t)m->hkv * units * c->n * 16;
-    DSI_TRY(ensure(m->attn_o, parts * m->hd * sizeof(float)));
-    return ensure(m->attn_ml, parts * sizeof(float2));
-  };
-  Chunks ch_all, ch_last;
-  DSI_TRY(key_chunks(0, &ch_all));
-  DSI_TRY(key_chunks(rb_last, &ch_last));
+  const Chunks ch_all = key_chunks(m, M, 0, keys), ch_last = key_chunks(m, M, rb_last, keys);
   const WidePlan pl_qkv = wide_plan(m, M, m->Nb_qkv, m->Kb_d, true), pl_o = wide_plan(m, M, m->Nb_o, m->Kb_q, false);
   const WidePlan pl_gu = wide_plan(m, M, m->Nb_gu, m->Kb_d, true);
   const WidePlan pl_down = wide_plan(m, M, m->Nb_down, m->Kb_ff, false);
@@ -776,15 +839,16 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     aa.wtype = m->wtype;
     {
       Prof p(m, DSI_K_ATTN);
-      HIP_TRY(launch_attention_prefill(m->hd, aa, tail ? rb_last : 0, s));
+      HIP_TRY(launch_attention_prefill(m->kvb, m->hd, aa, tail ? rb_last : 0, s));
     }
     if (tail) {
       const int Mt = M - 16 * rb_last;
       const bool ring = ring_forward(m, kv, 1);
       const size_t xo = (size_t)rb_last * 16 * m->d;
       g = oproj_args(m, l, Mt, ring);
-      g.Xhi = (uint16_t*)w.pk_q.hi + (size_t)rb_last * m->Kb_q * 512;
-      g.Xlo = (uint16_t*)w.pk_q.lo + (size_t)rb_last * m->Kb_q * 512;
+      const size_t po = (size_t)rb_last * m->Kb_q * 512 * m->esz;
+      g.Xhi = (char*)w.pk_q.hi + po;
+      g.Xlo = w.pk_q.lo ? (char*)w.pk_q.lo + po : nullptr;
       g.epi.x = w.x + xo;
       {
         Prof p(m, DSI_K_OPROJ);
@@ -1038,9 +1102,9 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
   A((void**)&m->ssq, (size_t)m->Nb_o * kMaxRows * 4);
   A((void**)&m->ssq2, (size_t)m->Nb_down * kMaxRows * 4);
   A((void**)&m->gcnt, (size_t)(m->Nb_down + 64) * sizeof(int));
-  if (st == DSI_OK) m->pk_d = make_pack(m, m->allocs, kMaxRows, m->Kb_d, &st);
-  if (st == DSI_OK) m->pk_q = make_pack(m, m->allocs, kMaxRows, m->Kb_q, &st);
-  if (st == DSI_OK) m->pk_ff = make_pack(m, m->allocs, kMaxRows, m->Kb_ff, &st);
+  if (st == DSI_OK) m->pk_d = make_pack(m, m->Kb_d, &st);
+  if (st == DSI_OK) m->pk_q = make_pack(m, m->Kb_q, &st);
+  if (st == DSI_OK) m->pk_ff = make_pack(m, m->Kb_ff, &st);
   A((void**)&m->qbuf, (size_t)kMaxRows * m->qdim * 4);
   A((void**)&m->rope, (size_t)kMaxRows * (m->hd / 2) * sizeof(float2));
   A((void**)&m->logits, (size_t)kMaxRows * m->V * 4);
@@ -1216,7 +1280,6 @@ dsi_status dsi_kv_create(dsi_model* m, int32_t n_windows, int32_t max_len, dsi_k
     delete kv;
     return st;
   }
-  wide_reserve(m, max_len);
   m->live_kv++;
   *out = kv;
   return DSI_OK;
@@ -1242,10 +1305,7 @@ dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* 
   if (kv->hi[window] + n > kv->max_len)
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window,
                 kv->hi[window], n, kv->max_len);
-  if (n > kMaxRows && m->wide.rows && m->kvb) {
-    // forwards of about equal size, whole groups of kMaxRows rows
-    const int parts = cdiv(n, m->wide.rows);
-    const int each = (int)round_up((size_t)cdiv(n, parts), kMaxRows);
+  if (const int each = wide_rows(m, kv, window, n)) {
     for (int off = 0; off < n; off += each) {
       const int rows = std::min(each, n - off);
       const bool last = off + rows == n;

@@ -6,6 +6,7 @@ import pytest
 import dsi_synth as S
 from oracle import forward64
 from paper_2405_14105_amd import dsi
+from parity import reg_of
 
 pytestmark = pytest.mark.gpu
 SEED = 5
@@ -26,7 +27,9 @@ def _weights(shape):
 @pytest.mark.parametrize("name,prefix,n", [
     ("ragged_bf16", 0, 65), ("ragged_bf16", 5, 129), ("gqa_hd64", 0, 97), ("gqa_hd64", 37, 257),
     ("mha_hd128", 63, 112), ("mha_hd128", 700, 66), ("many_kv", 0, 200), ("o_ring_hd128", 64, 300),
-    ("ring_wide_ff", 31, 81)])
+    ("ring_wide_ff", 31, 81),
+    # fp32 weights and / or cache
+    ("tiny", 0, 65), ("tiny", 40, 300), ("ragged_f32", 7, 130), ("hd96_kvf32", 33, 129), ("f32w_bf16kv", 0, 200)])
 def test_matches_oracle(name, prefix, n):
     shape = S.SHAPES[name]
     toks = S.prefix_tokens(shape, SEED, 0, prefix + n)
@@ -39,13 +42,15 @@ def test_matches_oracle(name, prefix, n):
     zo, cache = forward64(shape, _weights(shape), toks)
     err = float(np.abs(z - zo[-1]).max())
     print(f"{name} {prefix}+{n}: max|dz| = {err:.3g}")
-    assert err <= 2e-3                      # tests/parity.py's gate for bf16 caches
+    assert err <= reg_of(shape)
+    # keys and values: one bf16 spacing of the row's largest entry, or the
+    # activations' own error (bf16 hi + lo, or fp32) in an fp32 cache
+    rel = 2.0 ** -7 if shape.kvdtype == "bf16" else 1e-4 if shape.wdtype == "bf16" else 1e-5
     for l, (k, v) in enumerate(kv):
         for got, want in ((k, cache[l][0]), (v, cache[l][1])):
-            # equal up to one bf16 spacing of the largest entry of the row
             want = np.asarray(want).reshape(got.shape)
             top = np.abs(want).max(axis=-1, keepdims=True)
-            assert np.all(np.abs(got - want) <= 2.0 ** -7 * top + 1e-6)
+            assert np.all(np.abs(got - want) <= rel * top + 1e-6)
 
 
 def test_more_than_one_forward():
@@ -61,9 +66,10 @@ def test_more_than_one_forward():
 
 
 @pytest.mark.parametrize("bad", [(70,), (0, 199), (10, 140), (64, 70, 130, 210)])
-def test_invalid_ids_drop_their_chunks(bad):
+@pytest.mark.parametrize("name", ["gqa_hd64", "tiny"])
+def test_invalid_ids_drop_their_chunks(name, bad):
     """A chunk of 64 with an id outside the vocabulary is not cached, the others are, as in 64-token calls."""
-    shape = S.SHAPES["gqa_hd64"]
+    shape = S.SHAPES[name]
     n = 211
     toks = np.array(S.prefix_tokens(shape, SEED, 0, n))
     for i in bad:
@@ -88,9 +94,10 @@ def test_invalid_ids_drop_their_chunks(bad):
                 assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(b).max(axis=-1, keepdims=True) + 1e-6)
 
 
-def test_dead_rows_do_not_reach_the_logits():
+@pytest.mark.parametrize("name", ["mha_hd128", "tiny"])
+def test_dead_rows_do_not_reach_the_logits(name):
     """Rows past the length hold NaN: a long prompt over them is not touched by it."""
-    shape = S.SHAPES["mha_hd128"]
+    shape = S.SHAPES[name]
     toks = S.prefix_tokens(shape, SEED, 0, 150)
     with _rig(shape, SEED, 1, 400) as rig:
         a = rig.prefill(0, toks, want_logits=True)
@@ -128,3 +135,33 @@ def test_cache_import_export_round_trip(name, n, off):
         for a, b, full, back in ((k, k2, whole[0], got[0]), (v, v2, whole[1], got[1])):
             assert torch.equal(a[off:off + size], b[off:off + size])
             assert torch.equal(back[:, :n].reshape(-1), a[off:off + size]) and torch.equal(back[:, n:], full[:, n:])
+
+
+def test_captured_prompt():
+    """A prompt captured before any ran on the model (64-row forwards) and one captured after (wide), replayed."""
+    import torch
+    from gpu_rig import Rig
+    shape = S.SHAPES["gqa_hd64"]
+    toks = S.prefix_tokens(shape, SEED, 0, 150)
+    with torch.cuda.stream(torch.cuda.Stream()), Rig(shape, SEED, 2, 200) as rig:
+        t = rig.dev_i32(toks)
+        rig.prefill(1, toks[:64])                    # the 64-row forwards' buffers
+        out = []
+        for after in (False, True):
+            z = torch.zeros(shape.vocab, device="cuda")
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=torch.cuda.current_stream()):
+                dsi.dsi_kv_rollback(rig.kv, 0, 0)
+                dsi.dsi_prefill(rig.model, rig.kv, 0, t, len(toks), z)
+            for _ in range(3):
+                z.zero_()
+                g.replay()
+                torch.cuda.synchronize()
+                out.append(z.cpu().numpy())
+            dsi.dsi_kv_rollback(rig.kv, 0, 0)
+            out.append(rig.prefill(0, toks, want_logits=True))
+            dsi.dsi_kv_rollback(rig.kv, 0, 0)
+    narrow, wide = out[0], out[3]
+    assert all(np.array_equal(x, narrow) for x in out[:3]) and all(np.array_equal(x, wide) for x in out[3:])
+    assert np.abs(narrow - wide).max() <= 2e-3
