@@ -213,7 +213,7 @@ PackRef make_pack(dsi_model* m, int Kb, dsi_status* st) {
   return p;
 }
 
-// The workspace of prefill forwards of more than kMaxRows rows, reserved by
+// The workspace of wide prefill forwards (see wide_above), reserved by
 // the first prompt that needs it, for the cache's max_len (kWideRows rows at
 // most), in one allocation.  A model that has no memory for it keeps the one
 // it has, or none: prompts then run in narrower forwards.  An outgrown
@@ -734,13 +734,24 @@ Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
   return c;
 }
 
+// Prompts of more rows than this run in wide forwards.  A model whose layer
+// GEMMs have ring layouts gains from 65 rows on, where 64-row forwards read
+// the weights twice (8B, 64 rows after 900: 770 us narrow, 791 wide; 65: 1201
+// and 815, 4 layers).  The packed kernels of the others are overtaken at three
+// row tiles (13B, 3 layers, 32 rows: 611 and 603; 33: 706 and 620), the fp32
+// ones at four (tiny, 48 rows after 900: 89 and 88; 64: 103 and 91).
+int wide_above(const dsi_model* m) {
+  if (m->wtype != W_BF16) return 48;
+  return m->use_ring && m->rc_qkv.nbw && m->rc_o.nbw && m->rc_gu.nbw && m->rc_down.nbw ? kMaxRows : 32;
+}
+
 // Rows per wide forward of a prompt of n tokens: forwards of about equal size,
 // whole groups of kMaxRows rows; 0 when the prompt runs in 64-row forwards
 // instead.  Reserves what the forwards need, so that they allocate nothing;
 // a capturing stream cannot, and takes wide forwards only where earlier
 // prompts have reserved enough.
 int wide_rows(dsi_model* m, const dsi_kv* kv, int window, int n) {
-  if (n <= kMaxRows) return 0;
+  if (n <= wide_above(m)) return 0;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (m->stream && hipStreamIsCapturing(m->stream, &cap) != hipSuccess) {
     hipGetLastError();
