@@ -219,8 +219,7 @@ __global__ __launch_bounds__(NWV * 64, (NWV == 4 && KVB) ? 3 : 1) void k_attn(At
         mloc = fmaxf(mloc, sv[e]);
       }
     }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    mloc = max_over_16_32(mloc);
     const float mnew = fmaxf(mrun, mloc);
     const float base = (mnew == -INFINITY) ? 0.f : mnew;
     float pv[8];
@@ -295,8 +294,7 @@ __global__ __launch_bounds__(NWV * 64, (NWV == 4 && KVB) ? 3 : 1) void k_attn(At
   }
 
   // combine the waves of this workgroup into one partial (m, l, O)
-  lrun += __shfl_xor(lrun, 16);
-  lrun += __shfl_xor(lrun, 32);
+  lrun = sum_over_16_32(lrun);
   if (lane < 16) {
     sm[w][lane] = mrun;
     sl[w][lane] = lrun;

@@ -264,15 +264,16 @@ __global__ __launch_bounds__(256) void k_wide_fold(GemmArgs a, const float* part
 // values included: the QKV GEMM has written them).  Same arithmetic as the
 // window kernel (attention.hip): S^T = K Q^T and O^T = V^T P^T in 16x16x32
 // MFMAs, queries and probabilities split hi/lo, base-2 online softmax.
-// Bound by the softmax arithmetic and the MFMAs, about 16 queries x 32 keys
-// per 500 cycles of a SIMD.  A unit is 16 consecutive rows of one head; a
+// Bound by the MFMAs, the fragment reads from LDS and the softmax arithmetic,
+// about 1 us each per 64-key stage of a CU and only partly overlapped.  A unit is 16 consecutive rows of one head; a
 // workgroup's 8 waves take 8 units that share keys (all heads of a KV group,
 // row block by row block), so the keys and values of a 64-key stage are
 // loaded once per workgroup into LDS, in fragment order, while the stage
 // before is worked on, and a workgroup stops at its last row's position.
-// 8B, 2048 rows: 114 us, against 32 x 15 us of the window kernel, which
-// reads the keys once per 16 queries.  With few row blocks the keys are cut
-// into chunks as well (13B, 77 rows over 900 keys: 51 -> 19 + 5 us).
+// 8B, 2048 rows: 108 us (114 with a maximum and a rescale per 32 keys), against
+// 32 x 15 us of the window kernel, which reads the keys once per 16 queries.
+// With few row blocks the keys are cut into chunks as well (13B, 77 rows over
+// 900 keys: 51 us whole, 19 + 5 in 256-key and 13 + 6 in 128-key chunks).
 template <int KVB, int HD>
 __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n_units, int n_ublk) {
   constexpr int DS = HD / 32;
@@ -357,43 +358,59 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
   auto f32_at = [](const u32x4 (&x)[KVB ? 1 : 2][64], int lane, int e) {
     return __uint_as_float(x[KVB ? 0 : e >> 2][lane][e & 3]);
   };
-  auto step = [&](int p0, const u32x4 (*tl)[KVB ? 1 : 2][64]) {
-    f32x4 st[2];
+  // one 64-key stage: both halves' scores, one maximum and one rescale, then
+  // both halves' values.  Lane: keys p0 + 32 h + kgrp + e of query r16.
+  auto stage = [&](int p0, const u32x4 (*tl)[KVB ? 1 : 2][64]) {
+    f32x4 st[2][2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      st[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int ds = 0; ds < DS; ++ds) {
-        if constexpr (KVB) {
-          const bf16x8 kb = as_bf16x8(tl[t * DS + ds][0][lane]);
-          st[t] = mfma_bf16(kb, qh[ds], st[t]);
-          st[t] = mfma_bf16(kb, ql[ds], st[t]);
-        } else {
+      for (int t = 0; t < 2; ++t) {
+        st[h][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int e = 0; e < 8; ++e) st[t] = mfma_f32(f32_at(tl[t * DS + ds], lane, e), qf[ds][e], st[t]);
+        for (int ds = 0; ds < DS; ++ds) {
+          if constexpr (KVB) {
+            const bf16x8 kb = as_bf16x8(tl[h * ST + t * DS + ds][0][lane]);
+            st[h][t] = mfma_bf16(kb, qh[ds], st[h][t]);
+            st[h][t] = mfma_bf16(kb, ql[ds], st[h][t]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              st[h][t] = mfma_f32(f32_at(tl[h * ST + t * DS + ds], lane, e), qf[ds][e], st[h][t]);
+          }
         }
       }
-    }
-    const bool full = p0 + 32 <= pos0 + 1;
-    float sv[8];
+    const bool full = p0 + 64 <= pos0 + 1;
+    // the maximum over the unscaled scores; the scale goes into the exponent
+    float pv[2][8];
     float mloc = -INFINITY;
+    if (full) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool vis = full || p0 + kgrp + e <= qpos;
-      sv[e] = vis ? st[e >> 2][e & 3] * scale2 : -INFINITY;
-      mloc = fmaxf(mloc, sv[e]);
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          pv[h][e] = st[h][e >> 2][e & 3];
+          mloc = fmaxf(mloc, pv[h][e]);
+        }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          pv[h][e] = p0 + 32 * h + kgrp + e <= qpos ? st[h][e >> 2][e & 3] : -INFINITY;
+          mloc = fmaxf(mloc, pv[h][e]);
+        }
     }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-    const float mnew = fmaxf(mrun, mloc);
+    const float mnew = fmaxf(mrun, max_over_16_32(mloc) * scale2);
     const float b = (mnew == -INFINITY) ? 0.f : mnew;
-    float pv[8];
     float lsum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      pv[e] = __builtin_amdgcn_exp2f(sv[e] - b);
-      lsum += pv[e];
-    }
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        pv[h][e] = __builtin_amdgcn_exp2f(fmaf(pv[h][e], scale2, -b));
+        lsum += pv[h][e];
+      }
     if (__ballot(mnew != mrun)) {
       const float alpha = __builtin_amdgcn_exp2f(mrun - b);
       lrun *= alpha;
@@ -402,34 +419,37 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
     }
     lrun += lsum;
     mrun = mnew;
-    bf16x8 ph, pl;
-    if constexpr (KVB) {
-      u32x4 h, l;
-      split8(pv, h, l);
-      ph = as_bf16x8(h);
-      pl = as_bf16x8(l);
-    }
-    // keys past the block's rows may be dead cache rows: they have
-    // probability 0, and their values are zeroed so that 0 * NaN never
-    // reaches the output
-    const int nv = kw - (p0 + kgrp);
-    const bool tail = p0 + 32 > kw;
 #pragma unroll
-    for (int t = 0; t < DT; ++t) {
+    for (int h = 0; h < 2; ++h) {
+      bf16x8 ph, pl;
       if constexpr (KVB) {
-        u32x4 vv = tl[2 * DS + t][0][lane];
-        if (tail) {
+        u32x4 x, y;
+        split8(pv[h], x, y);
+        ph = as_bf16x8(x);
+        pl = as_bf16x8(y);
+      }
+      // keys past the block's rows may be dead cache rows: they have
+      // probability 0, and their values are zeroed so that 0 * NaN never
+      // reaches the output
+      const int nv = kw - (p0 + 32 * h + kgrp);
+      const bool tail = p0 + 32 * h + 32 > kw;
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            vv[i] &= (2 * i < nv ? 0x0000FFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
-        }
-        o[t] = mfma_bf16(as_bf16x8(vv), ph, o[t]);
-        o[t] = mfma_bf16(as_bf16x8(vv), pl, o[t]);
-      } else {
+      for (int t = 0; t < DT; ++t) {
+        if constexpr (KVB) {
+          u32x4 vv = tl[h * ST + 2 * DS + t][0][lane];
+          if (tail) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float vv = f32_at(tl[2 * DS + t], lane, e);
-          o[t] = mfma_f32(e < nv ? vv : 0.f, pv[e], o[t]);
+            for (int i = 0; i < 4; ++i)
+              vv[i] &= (2 * i < nv ? 0x0000FFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
+          }
+          o[t] = mfma_bf16(as_bf16x8(vv), ph, o[t]);
+          o[t] = mfma_bf16(as_bf16x8(vv), pl, o[t]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float vv = f32_at(tl[h * ST + 2 * DS + t], lane, e);
+            o[t] = mfma_f32(e < nv ? vv : 0.f, pv[h][e], o[t]);
+          }
         }
       }
     }
@@ -441,14 +461,12 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
     const bool more = st + 1 < st1;
     if (more) load_stage(sr, st + 1);
     const int buf = (st - st0) & 1;
-    if (st * 64 < kw) step(st * 64, &kv[buf][0]);
-    if (st * 64 + 32 < kw) step(st * 64 + 32, &kv[buf][ST]);
+    if (st * 64 < kw) stage(st * 64, &kv[buf][0]);
     if (more) store_stage(sr, buf ^ 1);
     __syncthreads();
   }
   if (!live) return;
-  lrun += __shfl_xor(lrun, 16);
-  lrun += __shfl_xor(lrun, 32);
+  lrun = sum_over_16_32(lrun);
   if (a.n_chunks > 1) {
     const size_t part = ((size_t)kvh * n_units + u) * a.n_chunks + c;
     float* po = a.part_o + (part * 16 + r16) * HD + (lane >> 4) * 4;

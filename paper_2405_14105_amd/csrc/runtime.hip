@@ -726,7 +726,7 @@ struct Chunks {
 };
 Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
   const int units = prefill_units(M - 16 * rb0, m->hq / m->hkv);
-  const int want = std::max(1, std::min(cdiv(keys, 256), 256 / (cdiv(units, 8) * m->hkv)));
+  const int want = std::max(1, std::min(cdiv(keys, 128), 256 / (cdiv(units, 8) * m->hkv)));
   Chunks c;
   c.size = (int)round_up((size_t)cdiv(keys, want), 64);
   c.n = cdiv(keys, c.size);
@@ -804,7 +804,7 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
   ea.err = m->err;
   HIP_TRY(launch_embed_norm(ea, s));
 
-  // attention: key chunks (of at least 256 keys) when the row blocks alone
+  // attention: key chunks (of at least 128 keys) when the row blocks alone
   // leave CUs idle; of the last layer the last row block only
   const int keys = (int)(kv->hi[window] + M);
   const int rb_last = (M - 1) / 16;
