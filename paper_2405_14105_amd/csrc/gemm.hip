@@ -17,6 +17,7 @@
 //  * weight loads for the next U k-blocks are issued before the MFMAs of the
 //    current ones so every wave keeps U*NBW KB in flight.
 #include <algorithm>
+#include <utility>
 
 #include "epilogue.h"
 
@@ -59,30 +60,38 @@ struct Role<EPI_RESID> {
   static constexpr bool RR = false;
 };
 
-// The EpiIn of the one epilogue item a thread owns, loaded before the main
-// loop so that its latency is hidden.
+// The EpiIn of the epilogue items a thread owns (item r: tile and lane r * NW *
+// 64 + threadIdx.x of the workgroup's), loaded before the main loop so that
+// its latency is hidden.
 template <int MT, int NBW, int NW, int EPI>
-__device__ __forceinline__ EpiIn epi_prefetch(const GemmArgs& a, int nb0) {
-  EpiIn r{};
+struct EpiPre {
+  static constexpr int R = EPI == EPI_RESID || EPI == EPI_QKV ? (NBW * MT + NW - 1) / NW : 1;
+  EpiIn in[R];
+};
+template <int MT, int NBW, int NW, int EPI>
+__device__ __forceinline__ EpiPre<MT, NBW, NW, EPI> epi_prefetch(const GemmArgs& a, int nb0) {
+  EpiPre<MT, NBW, NW, EPI> p{};
   if constexpr (EPI == EPI_RESID || EPI == EPI_QKV) {
-    static_assert(NBW * MT <= NW, "finish() must give each thread at most one item");
-    const int it = threadIdx.x;
-    if (it < NBW * MT * 64) {
-      const int l = it & 63, jm = it >> 6;
-      const int nb = nb0 + jm / MT, m = (jm % MT) * 16 + (l & 15);
-      if (nb < a.Nb && m < a.M) {
-        const EpiArgs& e = a.epi;
-        if constexpr (EPI == EPI_RESID) {
-          const int n0 = nb * 16 + (l >> 4) * 4;
-          r.x = *(const float4*)(e.x + (size_t)m * e.ld + n0);
-          r.g = *(const float4*)(e.gain + n0);
-        } else {
-          r = qkv_inputs(e, nb, (l >> 4) * 4, m);
+#pragma unroll
+    for (int r = 0; r < p.R; ++r) {
+      const int it = r * NW * 64 + threadIdx.x;
+      if (it < NBW * MT * 64) {
+        const int l = it & 63, jm = it >> 6;
+        const int nb = nb0 + jm / MT, m = (jm % MT) * 16 + (l & 15);
+        if (nb < a.Nb && m < a.M) {
+          const EpiArgs& e = a.epi;
+          if constexpr (EPI == EPI_RESID) {
+            const int n0 = nb * 16 + (l >> 4) * 4;
+            p.in[r].x = *(const float4*)(e.x + (size_t)m * e.ld + n0);
+            p.in[r].g = *(const float4*)(e.gain + n0);
+          } else {
+            p.in[r] = qkv_inputs(e, nb, (l >> 4) * 4, m);
+          }
         }
       }
     }
   }
-  return r;
+  return p;
 }
 
 // RMSNorm scale of each input row from the per-n-block sums of squares the
@@ -244,11 +253,11 @@ __device__ __forceinline__ void part_fold(const GemmArgs& a, int nb0, int nbv, c
 // is uniform across a wave, so the EPI_RESID lane reduction is safe.
 // NBW here is the number of n-blocks of one reduction round (red holds
 // NW x NBW x MT tiles); n-blocks j >= nvalid of the round are skipped.
-template <int WT, int EPI, int MT, int NBW, int NW>
+template <int WT, int EPI, int MT, int NBW, int NW, typename Pre>
 __device__ __forceinline__ void finish(const GemmArgs& a, const f32x4* red, const float* rs, int nb0,
-                                       int nvalid, int split, const EpiIn& pre) {
+                                       int nvalid, int split, const Pre& pre) {
   constexpr int ACC = NBW * MT;
-  for (int it = threadIdx.x; it < ACC * 64; it += NW * 64) {
+  auto item = [&](int it, const EpiIn& in) {
     const int l = it & 63, jm = it >> 6;
     const int j = jm / MT, t = jm % MT;
     f32x4 v = red[jm * 64 + l];
@@ -257,13 +266,22 @@ __device__ __forceinline__ void finish(const GemmArgs& a, const f32x4* red, cons
     const bool ok = j < nvalid && nb < a.Nb && m < a.M;
     if (ok && rs) v *= rs[m];
     float sq = 0.f;
-    if (ok) sq = epilogue<WT, EPI>(a.epi, nb, (l >> 4) * 4, m, split, v, pre);
+    if (ok) sq = epilogue<WT, EPI>(a.epi, nb, (l >> 4) * 4, m, split, v, in);
     if constexpr (EPI == EPI_RESID) {
       // lanes l, l+16, l+32, l+48 hold the 16 features of row m
       sq += __shfl_xor(sq, 16);
       sq += __shfl_xor(sq, 32);
       if (ok && l < 16) a.epi.ssq[(size_t)m * a.Nb + nb] = sq;
     }
+  };
+  if constexpr (EPI == EPI_RESID || EPI == EPI_QKV) {
+#pragma unroll
+    for (int r = 0; r < Pre::R; ++r) {
+      const int it = r * NW * 64 + threadIdx.x;
+      if (it < ACC * 64) item(it, pre.in[r]);
+    }
+  } else {
+    for (int it = threadIdx.x; it < ACC * 64; it += NW * 64) item(it, pre.in[0]);
   }
 }
 
@@ -389,7 +407,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_bf16(GemmArgs a) {
   // epilogue inputs and the RMSNorm sums go first: waiting for them then
   // waits for no weight load
   const SsqIn spre = ssq_prefetch<EPI>(a);
-  const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
+  const auto pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
   FoldIn<MT, NBW, NW> fpre;
   if constexpr (EPI == EPI_PARTRES) fold_prefetch(a, nb0, nbv, fpre);
   if constexpr (kPipelined<MT, EPI>) {
@@ -505,7 +523,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32(GemmArgs a) {
   const int nb0 = wk.nb0, nbv = wk.nbv, kb_beg = wk.kb_beg, kb_end = wk.kb_beg + wk.nk;
   const float4* __restrict__ W = (const float4*)a.W;
   const float4* __restrict__ X = (const float4*)a.Xhi;
-  const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
+  const auto pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
   FoldIn<MT, NBW, NW> fpre;
   if constexpr (EPI == EPI_PARTRES) fold_prefetch(a, nb0, nbv, fpre);
   if (a.ssq) row_scales<NW>(a, ssq_prefetch<EPI>(a), rs);
@@ -627,6 +645,15 @@ __device__ __forceinline__ void ring_row_scales(const GemmArgs& a, const RingSsq
   }
 }
 
+// f(0), f(1), ... as compile-time constants: the unroll pragma gives up on the
+// longest runs (140 tiles at three row tiles), and a loop that is only partly
+// unrolled waits for every load (13B gate/up, 33 rows: 92 us against 53; the
+// 8B head and gate/up at four row tiles no longer spill)
+template <typename F, int... I>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
 // MT row tiles (1..4) of the activation pack; every row's sums are formed
 // in the same order for every MT -- each wave's k-blocks in order, hi then
 // lo, the waves reduced in order -- so a row's results do not depend on
@@ -659,7 +686,7 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
     return ((lane & 15) + 16 * t < a.M && kb0 + i < a.Kb) ? ((t * a.Kb + kb0 + i) * 64 + lane) * 16 : 0x7ffffff0;
   };
 
-  const EpiIn pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
+  const auto pre = epi_prefetch<MT, NBW, NW, EPI>(a, nb0);
   FoldIn<MT, NBW, NW> fpre;
   if constexpr (EPI == EPI_PARTRES) fold_prefetch(a, nb0, nbv, fpre);
   RingSsq<MT> spre;
@@ -694,18 +721,17 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
   for (int j = 0; j < NBW; ++j)
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int u = 0; u < N; ++u) {
+  static_for(std::make_integer_sequence<int, N>{}, [&](auto step) {
+    constexpr int u = decltype(step)::value, i = u / NBW;
     const bf16x8 wv = as_bf16x8(ring[u % D]);
-    const int i = u / NBW;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       acc[u % NBW][t] = mfma_bf16(wv, as_bf16x8(xh[i % A][t]), acc[u % NBW][t]);
       acc[u % NBW][t] = mfma_bf16(wv, as_bf16x8(xl[i % A][t]), acc[u % NBW][t]);
     }
-    if (u + D < N) issue(u + D);
+    if constexpr (u + D < N) issue(u + D);
     __builtin_amdgcn_sched_barrier(0);   // consume tile u, then refill its slot
-  }
+  });
 #pragma unroll
   for (int j0 = 0; j0 < NBW; j0 += NBR) {
     if (j0 > 0) __syncthreads();   // the previous round's tiles have been read
@@ -725,7 +751,9 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
 // round of single-n-block workgroups covers every n-block, e.g. 192 at the
 // 1B shape: 0.826 -> 0.811 ms per step, where two would leave 96
 // workgroups; at the 8B shape one is far slower, 18.4 vs 13.7 us, as every
-// CU then takes in twice the activation bytes), gate/up seven (one
+// CU then takes in twice the activation bytes; four where two would need a
+// second round, 960 n-blocks at the 13B shape; there the O projection takes
+// two), gate/up seven (one
 // workgroup per CU for 1792 n-blocks; two where seven would leave half the
 // CUs idle: 8.7 -> 5.7 us at 352 n-blocks, d = 1024), the down projection
 // four with its K split (as the packed launch; two where four leave half the
@@ -736,12 +764,12 @@ struct RingRole;
 template <>
 struct RingRole<EPI_QKV> {
   static constexpr int NBW = 2;
-  static int nbw(int Nb, int) { return Nb <= 256 ? 1 : 2; }
+  static int nbw(int Nb, int) { return Nb <= 256 ? 1 : Nb <= 512 ? 2 : 4; }
 };
 template <>
 struct RingRole<EPI_RESID> {
   static constexpr int NBW = 1;
-  static int nbw(int, int) { return NBW; }
+  static int nbw(int Nb, int) { return Nb <= 256 ? 1 : 2; }
 };
 template <>
 struct RingRole<EPI_SILU> {
@@ -762,8 +790,13 @@ struct RingRole<EPI_STORE> {   // the LM head: many rounds of workgroups
 };
 
 // k-blocks per wave the ring kernel is built for (a shape's k-range per wave
-// is rounded up to one of them; the extra tiles are zero)
-constexpr int kRingNk[] = {1, 2, 4, 8, 14, 16};
+// is rounded up to one of them; the extra tiles are zero).  18 and 20 are the
+// 13B shape's (d_ff 13824 split three ways, d 5120), against its packed
+// kernels per launch at 11 / 17 / 55 rows: QKV 28.3 / 30.7 / 45.0 against 29.8
+// / 44.4 / 54.7 us, O 18.5 / 19.9 / 28.6 against 18.5 / 28.2 / 34.6, gate/up
+// 47.2 / 49.0 / 61.7 against 47.1 / 64.2 / 82.7, down 26.4 / 28.6 / 41.6
+// against 27.3 / 31.5 / 42.1, head 53 / 54 / 65 against 58 / 60 / 73.
+constexpr int kRingNk[] = {1, 2, 4, 8, 14, 16, 18, 20};
 
 template <int EPI, int NBW, int NK, int MT>
 hipError_t launch_ring_nk(const GemmArgs& a, hipStream_t s) {
@@ -785,6 +818,8 @@ hipError_t launch_ring_mt(const GemmArgs& a, hipStream_t s) {
     case 8: return launch_ring_nk<EPI, NBW, 8, MT>(a, s);
     case 14: return launch_ring_nk<EPI, NBW, 14, MT>(a, s);
     case 16: return launch_ring_nk<EPI, NBW, 16, MT>(a, s);
+    case 18: return launch_ring_nk<EPI, NBW, 18, MT>(a, s);
+    case 20: return launch_ring_nk<EPI, NBW, 20, MT>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -805,6 +840,10 @@ template <int EPI>
 hipError_t launch_ring(const GemmArgs& a, int mt, hipStream_t s) {
   if constexpr (EPI == EPI_QKV) {
     if (a.ring_nbw == 1) return launch_ring_nbw<EPI, 1>(a, mt, s);
+    if (a.ring_nbw == 4) return launch_ring_nbw<EPI, 4>(a, mt, s);
+  }
+  if constexpr (EPI == EPI_RESID) {
+    if (a.ring_nbw == 2) return launch_ring_nbw<EPI, 2>(a, mt, s);
   }
   if constexpr (EPI == EPI_SILU || EPI == EPI_PART || EPI == EPI_PARTRES) {
     if (a.ring_nbw == 2) return launch_ring_nbw<EPI, 2>(a, mt, s);

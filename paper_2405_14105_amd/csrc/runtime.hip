@@ -738,7 +738,7 @@ Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
 // GEMMs have ring layouts gains from 65 rows on, where 64-row forwards read
 // the weights twice (8B, 64 rows after 900: 770 us narrow, 791 wide; 65: 1201
 // and 815, 4 layers).  The packed kernels of the others are overtaken at three
-// row tiles (13B, 3 layers, 32 rows: 611 and 603; 33: 706 and 620), the fp32
+// row tiles (the 13B shape on them, 3 layers, 32 rows: 611 and 603; 33: 706 and 620), the fp32
 // ones at four (tiny, 48 rows after 900: 89 and 88; 64: 103 and 91).
 int wide_above(const dsi_model* m) {
   if (m->wtype != W_BF16) return 48;
