@@ -108,6 +108,10 @@ SHAPES = {
     # a wide FFN on a small residual stream: 1125 gate/up n-blocks in 161
     # ring workgroups of seven, and a four-way K split of the down projection
     "ring_wide_ff": Shape("ring_wide_ff", 2, 256, 8, 2, 64, 9000, 1500, gains="random"),
+    # a residual stream and heads as wide as the 13B shape's, the rest small:
+    # ring runs of 20 (QKV, gate/up, head) and 18 (O) k-blocks per wave, four
+    # n-blocks per workgroup for QKV and two for O
+    "ring_wide_d": Shape("ring_wide_d", 1, 4640, 36, 36, 128, 600, 700, gains="random"),
     # drafters: small models sharing a target's vocabulary
     "tiny_draft": Shape("tiny_draft", 1, 64, 2, 2, 32, 128, 1024, wdtype="f32", kvdtype="f32"),
     "ragged_draft": Shape("ragged_draft", 1, 96, 3, 1, 32, 200, 1003, gains="random"),

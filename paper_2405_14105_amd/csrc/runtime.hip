@@ -89,6 +89,10 @@ struct LayerW {
   void* wdown_s = nullptr;
 };
 
+// Row partials that the attention of a prefill forward leaves at most: its
+// key chunks make no more than 256 workgroups (key_chunks) of 8 units of 16 rows.
+constexpr size_t kChunkParts = 256 * 8 * 16;
+
 // Workspace of prefill forwards of up to `rows` prompt rows (prefill.hip).
 struct WideWs {
   int rows = 0;                 // 0: none
@@ -97,6 +101,8 @@ struct WideWs {
   size_t delta_bytes = 0;
   PackRef pk_d{}, pk_q{}, pk_ff{};
   float* qbuf = nullptr;
+  float* attn_o = nullptr;      // [kChunkParts][hd] partials of chunked attention
+  float2* attn_ml = nullptr;
   float2* rope = nullptr;
   int* gpos = nullptr;          // [rows / kMaxRows], then the advance
 };
@@ -249,6 +255,8 @@ void wide_reserve(dsi_model* m, int max_len) {
   pack(w.pk_ff, m->Kb_ff);
   const size_t ff1 = total;
   part((void**)&w.qbuf, (size_t)rows * m->qdim * 4);
+  part((void**)&w.attn_o, kChunkParts * m->hd * sizeof(float));
+  part((void**)&w.attn_ml, kChunkParts * sizeof(float2));
   part((void**)&w.rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
   part((void**)&w.gpos, (size_t)(kWideRows / kMaxRows + 1) * sizeof(int));
   char* slab = nullptr;
@@ -718,11 +726,9 @@ dsi_status wide_gemm(dsi_model* m, const WidePlan& p, GemmArgs g, int M, int* sp
 }
 
 // Key chunks of the attention of rows 16 rb0 .. M - 1 over `keys` keys (see
-// run_prefill), and the most row partials they leave over that many keys or
-// fewer.
+// run_prefill).
 struct Chunks {
   int n, size;
-  size_t parts;
 };
 Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
   const int units = prefill_units(M - 16 * rb0, m->hq / m->hkv);
@@ -730,7 +736,6 @@ Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
   Chunks c;
   c.size = (int)round_up((size_t)cdiv(keys, want), 64);
   c.n = cdiv(keys, c.size);
-  c.parts = want == 1 ? 0 : (size_t)m->hkv * units * want * 16;
   return c;
 }
 
@@ -747,34 +752,20 @@ int wide_above(const dsi_model* m) {
 
 // Rows per wide forward of a prompt of n tokens: forwards of about equal size,
 // whole groups of kMaxRows rows; 0 when the prompt runs in 64-row forwards
-// instead.  Reserves what the forwards need, so that they allocate nothing;
-// a capturing stream cannot, and takes wide forwards only where earlier
-// prompts have reserved enough.
-int wide_rows(dsi_model* m, const dsi_kv* kv, int window, int n) {
+// instead.  Reserves what the forwards need, so that they allocate nothing and
+// free nothing that a captured launch may use; a capturing stream cannot
+// reserve, and takes wide forwards only where an earlier prompt has.
+int wide_rows(dsi_model* m, const dsi_kv* kv, int n) {
   if (n <= wide_above(m)) return 0;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (m->stream && hipStreamIsCapturing(m->stream, &cap) != hipSuccess) {
     hipGetLastError();
     return 0;
   }
-  const bool may = cap == hipStreamCaptureStatusNone;
-  if (may) wide_reserve(m, kv->max_len);
+  if (cap == hipStreamCaptureStatusNone) wide_reserve(m, kv->max_len);
   if (!m->wide.rows) return 0;
   const int forwards = cdiv(n, m->wide.rows);
-  const int each = (int)round_up((size_t)cdiv(n, forwards), kMaxRows);
-  const int keys = (int)(kv->hi[window] + n);
-  size_t parts = 0;
-  for (int M : {std::min(n, each), (n - 1) % each + 1})
-    parts = std::max(parts, std::max(key_chunks(m, M, 0, keys).parts, key_chunks(m, M, (M - 1) / 16, keys).parts));
-  const size_t ob = parts * m->hd * sizeof(float), mb = parts * sizeof(float2);
-  if (may) {
-    const std::string keep = g_err;
-    if (ensure(m->attn_o, ob) != DSI_OK || ensure(m->attn_ml, mb) != DSI_OK) {
-      g_err = keep;
-      return 0;
-    }
-  }
-  return m->attn_o.bytes >= ob && m->attn_ml.bytes >= mb ? each : 0;
+  return (int)round_up((size_t)cdiv(n, forwards), kMaxRows);
 }
 
 // One forward of M (<= m->wide.rows) prompt tokens of one window, appended to
@@ -843,8 +834,8 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     aa.maxlen = kv->maxlen_pad;
     aa.chunk = ch.size;
     aa.n_chunks = ch.n;
-    aa.part_o = (float*)m->attn_o.p;
-    aa.part_ml = (float2*)m->attn_ml.p;
+    aa.part_o = w.attn_o;
+    aa.part_ml = w.attn_ml;
     aa.scale = (float)(1.0 / sqrt((double)m->hd));
     aa.out = w.pk_q;
     aa.wtype = m->wtype;
@@ -1316,7 +1307,7 @@ dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* 
   if (kv->hi[window] + n > kv->max_len)
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window,
                 kv->hi[window], n, kv->max_len);
-  if (const int each = wide_rows(m, kv, window, n)) {
+  if (const int each = wide_rows(m, kv, n)) {
     for (int off = 0; off < n; off += each) {
       const int rows = std::min(each, n - off);
       const bool last = off + rows == n;

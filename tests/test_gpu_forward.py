@@ -167,6 +167,21 @@ def test_multichunk_attention(name, n_windows, max_len, win, L, k):
         assert rig.length(win) == L + out["n"][0] + 1
 
 
+# one to four row tiles on the longest ring runs
+@pytest.mark.parametrize("k", [10, 16, 36, 63])
+def test_wide_residual_ring(k):
+    shape = S.SHAPES["ring_wide_d"]
+    prefix = S.prefix_tokens(shape, SEED, 0, 20)
+    wi = S.window_inputs(shape, SEED, 1, k)
+    zo = oracle_logits(shape, prefix, wi["tokens"][0])
+    with Rig(shape, SEED, 1, 20 + k + 1) as rig:
+        rig.prefill(0, prefix)
+        out = rig.verify(0, wi["tokens"], wi["q"], wi["u"], commit=False)
+    delta = float(np.abs(out["logits"] - zo).max())
+    print(f"k {k}: max|dz| = {delta:.3g}")
+    assert delta <= tol_of(shape) and delta <= reg_of(shape)
+
+
 def test_empty_prefix_and_k0():
     shape = S.SHAPES["ragged_bf16"]
     with Rig(shape, SEED, 1, 16) as rig:

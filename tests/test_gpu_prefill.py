@@ -165,3 +165,30 @@ def test_captured_prompt():
     narrow, wide = out[0], out[3]
     assert all(np.array_equal(x, narrow) for x in out[:3]) and all(np.array_equal(x, wide) for x in out[3:])
     assert np.abs(narrow - wide).max() <= 2e-3
+
+
+def test_captured_launches_outlive_later_prompts():
+    """Launches captured before the first wide prompt, replayed after it: it frees nothing that they use."""
+    import torch
+    shape = S.SHAPES["gqa_hd64"]
+    toks = S.prefix_tokens(shape, SEED, 0, 900)
+    with torch.cuda.stream(torch.cuda.Stream()), _rig(shape, SEED, 2, 1000) as rig:
+        t = rig.dev_i32(toks)
+        z = torch.zeros(shape.vocab, device="cuda")
+        dsi.dsi_prefill(rig.model, rig.kv, 0, t, 40, z)
+        dsi.dsi_kv_rollback(rig.kv, 0, 0)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=torch.cuda.current_stream()):
+            dsi.dsi_kv_rollback(rig.kv, 0, 0)
+            dsi.dsi_prefill(rig.model, rig.kv, 0, t, 40, z)
+        want = None
+        for n in (0, 150, 900, 0):
+            if n:
+                rig.prefill(1, toks[:n])
+                dsi.dsi_kv_rollback(rig.kv, 1, 0)
+            z.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            want = z.clone() if want is None else want
+            assert torch.equal(z, want) and bool(z.any())
