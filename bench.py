@@ -32,16 +32,16 @@ METRIC = "verify-step latency (ms) + verified draft tokens/s, 8B-shape k=10; % H
 # profiles/verify_8b_k10_hbm_traffic.md (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0,
 # scales from a 512 MiB copy).  Reported only while the GEMM sources are the
 # ones the counters were taken with.
-TRAFFIC_MEASURED = {"workload": "llama8b_L2048_k10", "bytes": 237.88e6,
-                    "sources_sha256": "486b6b80d8952f9b4cb4feccb4ab91eadc7a79b28914573593fadf426c8a15e6"}
+TRAFFIC_MEASURED = {"workload": "llama8b_L2048_k10", "bytes": 237.90e6,
+                    "sources_sha256": "72f217d1c092606206afc6ed2e745ecf896408877acd391ffbda88f6b27ac3d2"}
 # Matrix-core work of the same kernel from the counter run in
 # profiles/verify_8b_mfma_counters.md: SQ_INSTS_VALU_MFMA_MOPS_BF16 x 512 flops
 # per launch (what the MFMAs execute: 16-row tiles, both hi/lo halves) and
 # SQ_VALU_MFMA_BUSY_CYCLES against all SIMD cycles.  Same source condition.
-MFMA_MEASURED = {"workload": "llama8b_L2048_k10", "gflop_per_launch": 7.52, "busy_pct": 6.8,
+MFMA_MEASURED = {"workload": "llama8b_L2048_k10", "gflop_per_launch": 7.52, "busy_pct": 7.1,
                  "sources_sha256": TRAFFIC_MEASURED["sources_sha256"]}
-GEMM_SOURCES = ("paper_2405_14105_amd/csrc/gemm.hip", "paper_2405_14105_amd/csrc/device_util.h",
-                "paper_2405_14105_amd/csrc/internal.h")
+GEMM_SOURCES = ("paper_2405_14105_amd/csrc/gemm.hip", "paper_2405_14105_amd/csrc/epilogue.h",
+                "paper_2405_14105_amd/csrc/device_util.h", "paper_2405_14105_amd/csrc/internal.h")
 HBM_PEAK_GBS = 8000.0
 SEED = 0
 
