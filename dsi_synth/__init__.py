@@ -112,6 +112,9 @@ SHAPES = {
     # ring runs of 20 (QKV, gate/up, head) and 18 (O) k-blocks per wave, four
     # n-blocks per workgroup for QKV and two for O
     "ring_wide_d": Shape("ring_wide_d", 1, 4640, 36, 36, 128, 600, 700, gains="random"),
+    # the 8B attention's projections with little behind them and an fp32
+    # cache, where long sums show that the cache's rounding would hide
+    "wide_sums": Shape("wide_sums", 1, 4096, 32, 8, 128, 64, 256, kvdtype="f32"),
     # drafters: small models sharing a target's vocabulary
     "tiny_draft": Shape("tiny_draft", 1, 64, 2, 2, 32, 128, 1024, wdtype="f32", kvdtype="f32"),
     "ragged_draft": Shape("ragged_draft", 1, 96, 3, 1, 32, 200, 1003, gains="random"),

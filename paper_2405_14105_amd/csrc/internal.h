@@ -198,8 +198,8 @@ hipError_t launch_gemm(int wtype, int mt, const GemmArgs& a, hipStream_t s);
 // prefill (prefill.hip): any number of rows
 constexpr int kWideSplits = 8;   // K splits at most
 struct WideCfg {
-  int mt = 8;           // m-blocks (16 rows) per workgroup tile, 4..8
-  int nwn = 4;          // waves along the output features (2 or 4), 4 n-blocks each
+  int mt = 4;           // m-blocks (16 rows) per workgroup tile, 4 or 5
+  int nwn = 4;          // waves along the output features (2, 4 or 8), 4 n-blocks each
 };
 hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s);   // bf16 weights
 hipError_t launch_gemm_wide_f32(const GemmArgs& a, hipStream_t s);                   // fp32, no K split

@@ -11,17 +11,27 @@
 // GEMM (bf16 weights).  Same products as the window GEMMs: pre-tiled weights against the
 // hi/lo activation packs, two 16x16x32 MFMAs per product, fp32 sums.  A
 // workgroup of 8 waves makes a tile of NWN * 64 features x MT * 16 rows:
-//  * NWN waves lie along the features, four n-blocks each, and 8 / NWN groups
-//    of them split the tile's k-blocks, so two waves share each SIMD whatever
-//    the tile; the groups' sums meet in LDS at the end, in group order.
+//  * NWN (2, 4 or 8) waves lie along the features, four n-blocks each, and 8 /
+//    NWN groups of them split the tile's k-blocks, so two waves share each
+//    SIMD whatever the tile; the groups' sums meet in LDS at the end, in group
+//    order.
 //  * Weight fragments belong to one wave and go from memory to its registers,
 //    two k-blocks ahead.  Activation fragments are used by all NWN waves of a
 //    group and go through LDS (double buffered, one barrier per k-block):
 //    each fragment read there feeds four MFMAs, 64 of LDS's 128 bytes a
 //    cycle at full MFMA rate.  Both are stored in fragment order, so every
 //    load is 1 KB contiguous and no LDS access conflicts.
-//  * The loop has no branches; k-blocks past the split are zeroed on their
-//    way into LDS.
+//  * A wave's running sum goes into a second set of accumulators every
+//    kWideRun k-blocks.  In one chain over all of a wave's k-blocks (up to
+//    224 at the 8B shape) the error against 64 bits was 0.9 % larger than in
+//    the window kernels, whose waves sum 14-20 (700 rows, d = 4096, fp32
+//    cache: 2.482e-6 against 2.461e-6; now 2.458e-6).  The second set is why
+//    a tile has at most five row blocks (totals of the fifth and fourth in LDS
+//    where the registers are full).  Tiles of 8 x 4 blocks a wave and two
+//    waves' K groups, which it replaces, were 1-4 % faster: 2048 rows of four
+//    8B layers 5.20 ms, now 5.30; 1000 rows 2.84 and 2.88; 509 rows of eight
+//    1B layers 1.28 and 1.30.
+//  * K-blocks past the split are zeroed on their way into LDS.
 // At the 8B shape and 2048 rows it executes 1.2-1.3 PFLOP/s, the rate of a
 // large bf16 library product on the card (1.29).
 
@@ -35,6 +45,7 @@ namespace {
 
 constexpr int kWideWaves = 8;
 constexpr int kWideNb = 4;     // n-blocks per wave
+constexpr int kWideRun = 9;    // k-blocks a wave adds up before they go into its total (a multiple of 3)
 
 // Workgroup order: XCD x (ids congruent to x mod 8) takes a contiguous run of
 // the tiles, row tiles fastest within groups of eight, so the 32 workgroups
@@ -53,7 +64,9 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
   constexpr int XP = (XT + NWN - 1) / NWN;      // of them, copied by one wave
   constexpr int XS = KG * 2 * XT * 64;
   constexpr int RS = kWideWaves * 2 * MT * 64;
+  constexpr int TR = MT < 5 || NWN == 8 ? MT : 3;   // row blocks whose totals are in registers
   __shared__ u32x4 sm[XS > RS ? XS : RS];
+  __shared__ f32x4 tot_sh[MT > TR ? kWideWaves * kWideNb * (MT - TR) * 64 : 1];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = w % NWN, kg = w / NWN;
@@ -99,6 +112,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
     }
   };
   u32x4* const xs = sm + kg * 2 * XT * 64;
+  f32x4* const tot_l = tot_sh + (MT > TR ? w * kWideNb * (MT - TR) * 64 + lane : 0);
   // k-blocks past the split are multiplied as zeros (the loop runs whole
   // steps of KG k-blocks, three at a time)
   auto store_x = [&](const u32x4 (&d)[XP], int i) {
@@ -129,6 +143,15 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
   store_x(xr, 0);
   load_x(xr, 1);
   sync();
+  // sums of the runs so far: of the first TR row blocks in registers
+  f32x4 tot_r[kWideNb][TR];
+  auto tot = [&](int j, int m) -> f32x4& {
+    return m < TR ? tot_r[j][m < TR ? m : 0] : tot_l[(j * (MT - TR) + m - TR) * 64];
+  };
+#pragma unroll
+  for (int j = 0; j < kWideNb; ++j)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) tot(j, m) = acc[j][m];
   auto step = [&](int i, const u32x4 (&wc)[kWideNb], u32x4 (&wnext)[kWideNb]) {
     load_w(wnext, i + 2);
     const u32x4* xb = xs + (i & 1) * XT * 64 + lane;
@@ -155,10 +178,21 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
     }
     sync();
   };
+  int trips = 0;
   for (int i = 0; i < n; i += 3) {
     step(i, wr[0], wr[2]);
     step(i + 1, wr[1], wr[0]);
     step(i + 2, wr[2], wr[1]);
+    if (++trips == kWideRun / 3 && i + 3 < n) {
+      trips = 0;
+#pragma unroll
+      for (int j = 0; j < kWideNb; ++j)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          tot(j, m) += acc[j][m];
+          acc[j][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
   }
 
   // The K groups' partial tiles meet in LDS, two n-blocks of every wave a
@@ -171,7 +205,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void k_gemm_wide(GemmArgs a, WideG
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-      for (int m = 0; m < MT; ++m) red[((w * 2 + jj) * MT + m) * 64 + lane] = acc[2 * r + jj][m];
+      for (int m = 0; m < MT; ++m) red[((w * 2 + jj) * MT + m) * 64 + lane] = tot(2 * r + jj, m) + acc[2 * r + jj][m];
     __syncthreads();
     for (int it = w; it < 2 * NWN * MT; it += kWideWaves) {
       const int m = it % MT, wj = it / MT;             // wj = (wave along N) * 2 + jj
@@ -218,8 +252,10 @@ __global__ __launch_bounds__(256) void k_gemm_wide_f32(GemmArgs a) {
     for (int t = 0; t < MT; ++t) {
       const size_t xi = (((size_t)min(mb0 + t, Mb - 1) * a.Kb + kb) * 64 + lane) * 2;
       const F8 xf{X[xi], X[xi + 1]};
+      f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};   // of this k-block
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[t] = mfma_f32(f8_get(wf, e), f8_get(xf, e), acc[t]);
+      for (int e = 0; e < 8; ++e) s = mfma_f32(f8_get(wf, e), f8_get(xf, e), s);
+      acc[t] += s;
     }
   }
 #pragma unroll
@@ -530,12 +566,14 @@ hipError_t launch_wide_epi(const GemmArgs& a, const WideGrid& g, hipStream_t s) 
 
 template <int MT>
 hipError_t launch_wide_mt(const GemmArgs& a, int nwn, const WideGrid& g, hipStream_t s) {
-  if (g.mtiles == 1) return nwn == 4 ? launch_wide_epi<MT, 4, 1>(a, g, s) : launch_wide_epi<MT, 2, 1>(a, g, s);
-  return nwn == 4 ? launch_wide_epi<MT, 4, 0>(a, g, s) : launch_wide_epi<MT, 2, 0>(a, g, s);
+  const bool one = g.mtiles == 1;
+  if (nwn == 2) return one ? launch_wide_epi<MT, 2, 1>(a, g, s) : launch_wide_epi<MT, 2, 0>(a, g, s);
+  if (nwn == 4) return one ? launch_wide_epi<MT, 4, 1>(a, g, s) : launch_wide_epi<MT, 4, 0>(a, g, s);
+  return one ? launch_wide_epi<MT, 8, 1>(a, g, s) : launch_wide_epi<MT, 8, 0>(a, g, s);
 }
 
 hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s) {
-  if (a.M < 1 || a.Nb < 1 || a.Kb < 1 || a.S < 1 || a.S > a.Kb || a.G < 1 || (c.nwn != 2 && c.nwn != 4))
+  if (a.M < 1 || a.Nb < 1 || a.Kb < 1 || a.S < 1 || a.S > a.Kb || a.G < 1 || (c.nwn != 2 && c.nwn != 4 && c.nwn != 8))
     return hipErrorInvalidValue;
   if (a.S > 1 && a.epi.kind != EPI_PART && a.epi.kind != EPI_TILE) return hipErrorInvalidValue;
   WideGrid g;
@@ -547,9 +585,6 @@ hipError_t launch_gemm_wide(const GemmArgs& a, const WideCfg& c, hipStream_t s) 
   switch (c.mt) {
     case 4: return launch_wide_mt<4>(a, c.nwn, g, s);
     case 5: return launch_wide_mt<5>(a, c.nwn, g, s);
-    case 6: return launch_wide_mt<6>(a, c.nwn, g, s);
-    case 7: return launch_wide_mt<7>(a, c.nwn, g, s);
-    case 8: return launch_wide_mt<8>(a, c.nwn, g, s);
   }
   return hipErrorInvalidValue;
 }

@@ -644,35 +644,36 @@ struct WidePlan {
 };
 // The fastest by estimate over every tile and split.  A launch takes its
 // longest of
-//  * MFMA time: rounds of one workgroup per CU, each 1.3 us + 26 (NWN 4) or
-//    29.5 ns (NWN 2) per k-block, wave and m-block, down to 62 % of that
-//    with idle CUs (clock and L2 are shared);
-//  * the weights at 6 TB/s;
-//  * what one CU takes in, weights and activations, at 94 GB/s;
-// plus 8.7 us of launch, first loads, reduction and last stores, plus the
+//  * MFMA time: rounds of one workgroup per CU, each 1.2 us + 20, 22 or 19.5 ns
+//    (NWN 2, 4, 8) per k-block, wave and m-block, down to 68 % of that with
+//    idle CUs (clock and L2 are shared);
+//  * the weights at 9.6 TB/s (some come from the last-level cache);
+//  * what one CU takes in, weights and activations, at 69 GB/s;
+// plus 7.4 us of launch, first loads, reduction and last stores, plus the
 // partials' way through memory (and the fold launch of a split QKV or
-// gate/up).  Fitted to 5266 launches (11 row counts from 65 to 2048, the
-// layer shapes of the 1B, 8B and 13B models and the small drafter, every
-// tile, splits 1-4): the chosen one is 1.2 % slower than the best on
-// average, 16 % at worst.
+// gate/up).  Fitted to 7582 launches: 15 row counts from 33 to 2048, the layer
+// shapes of the 1B, 8B and 13B models, the small drafter and a wide FFN on a
+// small residual stream, every tile, splits 1-8.  The chosen launch and the
+// reading of its partials are 1.0 % slower than the best on average, 11 % at
+// worst (33-64 rows: 1.4 %; where it splits more than four ways: 1.9 %).
 WidePlan wide_plan(const dsi_model* m, int M, int Nb, int Kb, bool fused) {
   const int mb = cdiv(M, 16);
   const double part = (double)M * Nb * 64;
   WidePlan best;
   double t_best = 1e30;
-  for (int nwn = 2; nwn <= 4; nwn += 2)
-    for (int mt = 4; mt <= 8; ++mt) {
+  for (int nwn = 2; nwn <= 8; nwn *= 2)
+    for (int mt = 4; mt <= 5; ++mt) {
       if (mt > 4 && mt > mb) break;
       for (int S = 1; S <= kWideSplits; ++S) {
         const size_t bytes = (size_t)S * mb * 256 * Nb * sizeof(float);
         if (S > 1 && (Kb / S < 8 || bytes > m->wide.delta_bytes)) break;
         const int wgs = cdiv(Nb, 4 * nwn) * cdiv(mb, mt) * S;
         const int rounds = cdiv(wgs, 256), kbs = cdiv(Kb, S);
-        const double busy = 0.62 + 0.38 * std::min(1.0, wgs / 256.0);
-        const double mfma = rounds * (1.3 + (double)kbs * nwn * mt * (nwn == 4 ? 0.0257 : 0.0295) * busy);
-        const double stream = (double)Nb * Kb * 1024 / 6.0e6;
-        const double intake = (double)rounds * kbs * (4 * nwn + 2 * mt) * 1024 / 94e3;
-        double t = 8.7 + std::max(mfma, std::max(stream, intake));
+        const double busy = 0.68 + 0.32 * std::min(1.0, wgs / 256.0);
+        const double mfma = rounds * (1.2 + (double)kbs * nwn * mt * (nwn == 2 ? 0.02 : nwn == 4 ? 0.022 : 0.0195) * busy);
+        const double stream = (double)Nb * Kb * 1024 / 9.6e6;
+        const double intake = (double)rounds * kbs * (4 * nwn + 2 * mt) * 1024 / 69e3;
+        double t = 7.4 + std::max(mfma, std::max(stream, intake));
         if (!fused) t += S * part / 4.5e6;
         else if (S > 1) t += 4.5 + (S + 1) * part / 4.0e6;
         if (t < t_best) {
