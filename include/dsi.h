@@ -130,8 +130,12 @@ dsi_status dsi_kv_destroy(dsi_kv* kv);
  * chunks of DSI_MAX_ROWS, many of them in one forward (the first prompt longer
  * than one chunk reserves the model's workspace for it); a chunk holding an id outside [0, V) does not
  * advance the length and is reported by the next synchronising call
- * (DSI_EINVAL).  Stream-ordered; d_tokens is caller-owned and only read by
- * the call's stream work. */
+ * (DSI_EINVAL).  The same prompt on the same cache gives the same bits,
+ * whatever ran before.  They differ in rounding between ways of cutting a
+ * prompt into calls, and between a call captured into a graph before the
+ * workspace was reserved (forwards of one chunk) and one captured after.
+ * Stream-ordered; d_tokens is caller-owned and only read by the call's stream
+ * work. */
 dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* d_tokens,
                        int32_t n, float* d_last_logits);
 

@@ -205,7 +205,7 @@ __global__ void k_kv_add_checked(int* lens, int window, const int* tokens, int n
 // one wave per group of kMaxRows prompt rows, then one thread lays the groups
 // out (at most kWideRows / kMaxRows of them)
 __global__ __launch_bounds__(1024) void k_prefill_rows(const int* lens, int window, const int* tokens, int n, int V,
-                                                       int last, int* gpos, int* adv, int* err) {
+                                                       int last, int* gpos, int* err) {
   __shared__ int bad[kWideRows / kMaxRows];
   const int groups = (n + kMaxRows - 1) / kMaxRows;
   const int lane = threadIdx.x & 63;
@@ -220,23 +220,26 @@ __global__ __launch_bounds__(1024) void k_prefill_rows(const int* lens, int wind
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int p = lens[window], a = 0, any = 0;
+    int p = lens[window], a = 0, seen = 0, any = 0;
     for (int g = 0; g < groups; ++g) {
       const int rows = min(kMaxRows, n - g * kMaxRows);
       if (bad[g]) {
         any = 1;
         gpos[g] = last && g + 1 == groups ? p + a : -1;
+        if (gpos[g] >= 0) seen = a + rows;
       } else {
         gpos[g] = p + a;
         a += rows;
+        seen = a;
       }
     }
-    *adv = a;
+    gpos[kGposAdv] = a;
+    gpos[kGposKeys] = p + seen;
     if (any) atomicOr(err, 1);
   }
 }
-__global__ void k_prefill_commit(int* lens, int window, const int* adv) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) lens[window] += *adv;
+__global__ void k_prefill_commit(int* lens, int window, const int* gpos) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) lens[window] += gpos[kGposAdv];
 }
 
 // copy [n_kv][len][hd] <-> cache (n_kv regions of maxlen * hd, kc_off /
@@ -423,13 +426,13 @@ hipError_t launch_kv_add_checked(int* lens, int window, const int* tokens, int n
 }
 
 hipError_t launch_prefill_rows(const int* lens, int window, const int* tokens, int n, int V, int last, int* gpos,
-                               int* adv, int* err, hipStream_t s) {
+                               int* err, hipStream_t s) {
   if (n < 1 || n > kWideRows) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_prefill_rows, dim3(1), dim3(1024), 0, s, lens, window, tokens, n, V, last, gpos, adv, err);
+  hipLaunchKernelGGL(k_prefill_rows, dim3(1), dim3(1024), 0, s, lens, window, tokens, n, V, last, gpos, err);
   return hipGetLastError();
 }
-hipError_t launch_prefill_commit(int* lens, int window, const int* adv, hipStream_t s) {
-  hipLaunchKernelGGL(k_prefill_commit, dim3(1), dim3(64), 0, s, lens, window, adv);
+hipError_t launch_prefill_commit(int* lens, int window, const int* gpos, hipStream_t s) {
+  hipLaunchKernelGGL(k_prefill_commit, dim3(1), dim3(64), 0, s, lens, window, gpos);
   return hipGetLastError();
 }
 

@@ -87,6 +87,10 @@ struct RowMap {         // token row m -> (window, row within window, position)
   // cached (it holds an invalid id, and a later group takes its positions)
   const int* gpos = nullptr;
 };
+// after the groups' entries, gpos holds the rows by which the window's length
+// advances, and the number of keys that the last row sees
+constexpr int kGposAdv = kWideRows / kMaxRows;
+constexpr int kGposKeys = kGposAdv + 1;
 // cache slot of row m (negative: not cached)
 __device__ inline int row_slot(const RowMap& r, int m) {
   if (r.gpos) {
@@ -263,10 +267,26 @@ struct AttnArgs {
 constexpr int kAttnWaves = 8;                       // waves per attention workgroup (default)
 hipError_t launch_attention(int kv_bf16, int hd, const AttnArgs& a, hipStream_t s);
 // causal attention of one window's prompt rows (rows.gpos) over the cache
-// (prefill.hip), the keys in n_chunks chunks of `chunk` (a multiple of 64);
-// several chunks leave partials [n_kv][units][chunks][16][hd] in part_o and
-// part_ml.  Rows from 16 * rb0 on only (part_o's units count from there).
-// n_qtiles, waves unused.
+// (prefill.hip), the keys in at most n_chunks chunks; several chunks leave
+// partials [n_kv][units][n_chunks][16][hd] in part_o and part_ml.  Rows from
+// 16 * rb0 on only (part_o's units count from there).  n_qtiles, chunk, waves
+// unused.  The kernel takes the chunk size from the window's length on the
+// device (prefill_chunk): the host has only an upper bound, which committed
+// verifications leave above the length (the sums would depend on when it was
+// last corrected), and below it where a captured prompt is replayed to append
+// (the keys past the last chunk would be lost).
+// prefill_chunks: chunks of at least 128 keys, at most `most`; prefill_chunk:
+// keys per chunk, a multiple of 64.  Both are the same for any `most` not below
+// the number of chunks, so a bound on the keys can size the launch.
+__host__ __device__ inline int prefill_chunks(int keys, int most) {
+  const int c = (keys + 127) / 128;
+  return c < 1 ? 1 : c < most ? c : most;
+}
+__host__ __device__ inline int prefill_chunk(int keys, int most) {
+  const int want = prefill_chunks(keys, most);
+  const int size = ((keys + want - 1) / want + 63) & ~63;
+  return size < 64 ? 64 : size;
+}
 int prefill_units(int rows, int group);   // 16-row units of one KV head
 hipError_t launch_attention_prefill(int kv_bf16, int hd, const AttnArgs& a, int rb0, hipStream_t s);
 
@@ -359,13 +379,12 @@ hipError_t launch_kv_rollback(int* lens, int window, int new_len, int* err, hipS
 hipError_t launch_kv_set(int* lens, int window, int new_len, hipStream_t s);
 hipError_t launch_kv_add_checked(int* lens, int window, const int* tokens, int n, int V, int* err,
                                  hipStream_t s);
-// Prompt rows of one forward (n tokens): gpos[g] of every group of kMaxRows
-// rows and *adv, the rows the window's length advances by: the rows of the
-// groups without an invalid id.  A group with one is not cached unless it is
+// Prompt rows of one forward (n tokens): gpos (RowMap).  The window's length
+// advances by the rows of the groups without an invalid id.  A group with one is not cached unless it is
 // the last of the call (`last`), and is reported in err.
 hipError_t launch_prefill_rows(const int* lens, int window, const int* tokens, int n, int V, int last, int* gpos,
-                               int* adv, int* err, hipStream_t s);
-hipError_t launch_prefill_commit(int* lens, int window, const int* adv, hipStream_t s);
+                               int* err, hipStream_t s);
+hipError_t launch_prefill_commit(int* lens, int window, const int* gpos, hipStream_t s);
 hipError_t launch_kv_copy(int to_cache, int kv_bf16, void* kc, void* vc, int n_kv, int hd,
                           int maxlen, int len, void* dk, void* dv, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);

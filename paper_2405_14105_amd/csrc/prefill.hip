@@ -338,7 +338,10 @@ __global__ __launch_bounds__(512) void k_attn_prefill(AttnArgs a, int rb0, int n
   const int kw = live ? block_keys(rb) : 0;             // keys of this wave
   int kwg = 0;                                          // and of the workgroup
   for (int b = rb0 + (ub * 8) / G; b <= rb0 + ul / G; ++b) kwg = max(kwg, block_keys(b));
-  const int st0 = c * (a.chunk >> 6), st1 = min((kwg + 63) >> 6, st0 + (a.chunk >> 6));   // stages of 64 keys
+  const int keys = a.rows.gpos[kGposKeys];
+  const int per = a.n_chunks > 1 ? prefill_chunk(keys, a.n_chunks) >> 6 : 1 << 20;
+  if (a.n_chunks > 1 && c * per * 64 >= keys && c > 0) return;   // no such chunk
+  const int st0 = c * per, st1 = min((kwg + 63) >> 6, st0 + per);   // stages of 64 keys
   const int r16 = lane & 15, kgrp = (lane >> 4) * 8;
   const int row = rb * 16 + r16;
   const int qpos = pos0 + r16;
@@ -544,13 +547,15 @@ __global__ __launch_bounds__(HD * 4) void k_attn_prefill_combine(AttnArgs a, int
   const size_t part = ((size_t)kvh * n_units + u) * a.n_chunks;
   const float2* ml = a.part_ml + part * 16 + q;
   const float* po = a.part_o + (part * 16 + q) * HD + d;
+  const int keys = a.rows.gpos[kGposKeys], per = prefill_chunk(keys, a.n_chunks);
+  const int n_chunks = max(1, (keys + per - 1) / per);
   float M = -INFINITY;
-  for (int c = 0; c < a.n_chunks; ++c) M = fmaxf(M, ml[c * 16].x);
+  for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, ml[c * 16].x);
   const float b = M == -INFINITY ? 0.f : M;
   float L = 0.f;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-  for (int c = 0; c < a.n_chunks; ++c) {
+  for (int c = 0; c < n_chunks; ++c) {
     const float2 v = ml[c * 16];
     const float f = __builtin_amdgcn_exp2f(v.x - b);
     L += v.y * f;
@@ -637,7 +642,7 @@ hipError_t launch_attn_prefill_hd(const AttnArgs& a, int rb0, int units, hipStre
 hipError_t launch_attention_prefill(int kv_bf16, int hd, const AttnArgs& a, int rb0, hipStream_t s) {
   const int units = prefill_units(a.rows.rows_per_window - 16 * rb0, a.n_heads / a.n_kv);
   if (rb0 < 0 || units < 1) return hipErrorInvalidValue;
-  if (a.n_chunks < 1 || a.chunk < 64 || a.chunk % 64 || !a.rows.gpos) return hipErrorInvalidValue;
+  if (a.n_chunks < 1 || !a.rows.gpos) return hipErrorInvalidValue;
   if (kv_bf16) {
     switch (hd) {
       case 32: return launch_attn_prefill_hd<1, 32>(a, rb0, units, s);

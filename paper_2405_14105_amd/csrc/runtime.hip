@@ -104,7 +104,7 @@ struct WideWs {
   float* attn_o = nullptr;      // [kChunkParts][hd] partials of chunked attention
   float2* attn_ml = nullptr;
   float2* rope = nullptr;
-  int* gpos = nullptr;          // [rows / kMaxRows], then the advance
+  int* gpos = nullptr;          // [kGposKeys + 1]
 };
 
 struct dsi_model {
@@ -258,7 +258,7 @@ void wide_reserve(dsi_model* m, int max_len) {
   part((void**)&w.attn_o, kChunkParts * m->hd * sizeof(float));
   part((void**)&w.attn_ml, kChunkParts * sizeof(float2));
   part((void**)&w.rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
-  part((void**)&w.gpos, (size_t)(kWideRows / kMaxRows + 1) * sizeof(int));
+  part((void**)&w.gpos, (size_t)(kGposKeys + 1) * sizeof(int));
   char* slab = nullptr;
   if (hipMalloc((void**)&slab, total) != hipSuccess) {
     hipGetLastError();
@@ -726,18 +726,11 @@ dsi_status wide_gemm(dsi_model* m, const WidePlan& p, GemmArgs g, int M, int* sp
   return DSI_OK;
 }
 
-// Key chunks of the attention of rows 16 rb0 .. M - 1 over `keys` keys (see
-// run_prefill).
-struct Chunks {
-  int n, size;
-};
-Chunks key_chunks(const dsi_model* m, int M, int rb0, int keys) {
+// Key chunks launched for the attention of rows 16 rb0 .. M - 1 over at most
+// `keys` keys: chunks (prefill_chunk) when the row blocks alone leave CUs idle.
+int key_chunks(const dsi_model* m, int M, int rb0, int keys) {
   const int units = prefill_units(M - 16 * rb0, m->hq / m->hkv);
-  const int want = std::max(1, std::min(cdiv(keys, 128), 256 / (cdiv(units, 8) * m->hkv)));
-  Chunks c;
-  c.size = (int)round_up((size_t)cdiv(keys, want), 64);
-  c.n = cdiv(keys, c.size);
-  return c;
+  return prefill_chunks(keys, std::max(1, 256 / (cdiv(units, 8) * m->hkv)));
 }
 
 // Prompts of more rows than this run in wide forwards.  A model whose layer
@@ -774,8 +767,7 @@ int wide_rows(dsi_model* m, const dsi_kv* kv, int n) {
 dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d_tokens, float* logits, int last) {
   hipStream_t s = m->stream;
   WideWs& w = m->wide;
-  int* adv = w.gpos + kWideRows / kMaxRows;
-  HIP_TRY(launch_prefill_rows(kv->lens, window, d_tokens, M, m->V, last, w.gpos, adv, m->err, s));
+  HIP_TRY(launch_prefill_rows(kv->lens, window, d_tokens, M, m->V, last, w.gpos, m->err, s));
   RowMap rows{kv->lens, window, M, nullptr, w.gpos};
 
   EmbedArgs ea{};
@@ -796,11 +788,10 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
   ea.err = m->err;
   HIP_TRY(launch_embed_norm(ea, s));
 
-  // attention: key chunks (of at least 128 keys) when the row blocks alone
-  // leave CUs idle; of the last layer the last row block only
+  // attention of the last layer: the last row block only
   const int keys = (int)(kv->hi[window] + M);
   const int rb_last = (M - 1) / 16;
-  const Chunks ch_all = key_chunks(m, M, 0, keys), ch_last = key_chunks(m, M, rb_last, keys);
+  const int chunks_all = key_chunks(m, M, 0, keys), chunks_last = key_chunks(m, M, rb_last, keys);
   const WidePlan pl_qkv = wide_plan(m, M, m->Nb_qkv, m->Kb_d, true), pl_o = wide_plan(m, M, m->Nb_o, m->Kb_q, false);
   const WidePlan pl_gu = wide_plan(m, M, m->Nb_gu, m->Kb_d, true);
   const WidePlan pl_down = wide_plan(m, M, m->Nb_down, m->Kb_ff, false);
@@ -823,7 +814,6 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     // caller wants no logits (8B, 2048 rows: 1.3 ms of a 1.6 ms layer)
     const bool tail = l + 1 == m->L;
     if (tail && !logits) break;
-    const Chunks ch = tail ? ch_last : ch_all;
     AttnArgs aa{};
     aa.q = w.qbuf;
     aa.kc = kv_ptr(kv, kv->k, l, 0);
@@ -833,8 +823,7 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
     aa.n_heads = m->hq;
     aa.n_kv = m->hkv;
     aa.maxlen = kv->maxlen_pad;
-    aa.chunk = ch.size;
-    aa.n_chunks = ch.n;
+    aa.n_chunks = tail ? chunks_last : chunks_all;
     aa.part_o = w.attn_o;
     aa.part_ml = w.attn_ml;
     aa.scale = (float)(1.0 / sqrt((double)m->hd));
@@ -901,7 +890,7 @@ dsi_status run_prefill(dsi_model* m, dsi_kv* kv, int window, int M, const int* d
                                   m->wtype, w.pk_d, nullptr, s));
     }
   }
-  HIP_TRY(launch_prefill_commit(kv->lens, window, adv, s));
+  HIP_TRY(launch_prefill_commit(kv->lens, window, w.gpos, s));
   return DSI_OK;
 }
 

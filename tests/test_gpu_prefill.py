@@ -204,6 +204,49 @@ def test_captured_prompt():
     assert np.abs(narrow - wide).max() <= 2e-3
 
 
+@pytest.mark.parametrize("name,prefix", [("many_kv", 700), ("tiny", 500)])
+def test_bits_do_not_depend_on_the_hosts_bound(name, prefix):
+    """A window whose length the host only knows a bound of (dropped chunks, uncorrected) takes the same bits as one whose
+    length it knows: the key chunks come from the length."""
+    shape = S.SHAPES[name]
+    toks = S.prefix_tokens(shape, SEED, 0, prefix + 100)
+    with _rig(shape, SEED, 2, prefix + 400) as rig:
+        for w in (0, 1):
+            rig.prefill(w, toks[:prefix])
+        for _ in range(4):
+            rig.prefill(0, np.full(64, -1))          # not cached: the bound grows, the length stays
+        z = [rig.prefill(w, toks[prefix:], want_logits=True) for w in (0, 1)]
+        with pytest.raises(dsi.DsiError):
+            rig.length(0)                            # the dropped chunks' report
+        assert rig.length(0) == rig.length(1) == prefix + 100
+        kv = [[rig.export_kv(w, l, prefix + 100) for l in range(shape.n_layers)] for w in (0, 1)]
+    assert np.array_equal(*z)
+    assert all(np.array_equal(a, b) for x, y in zip(*kv) for a, b in zip(x, y))
+
+
+@pytest.mark.parametrize("name,n", [("gqa_hd64", 100), ("many_kv", 130)])
+def test_captured_prompt_appends_on_every_replay(name, n):
+    """A captured prompt that is replayed without a rollback attends to everything before it, past the length it was captured at."""
+    import torch
+    shape = S.SHAPES[name]
+    toks = S.prefix_tokens(shape, SEED, 0, n)
+    with torch.cuda.stream(torch.cuda.Stream()), _rig(shape, SEED, 2, 6 * n) as rig:
+        rig.prefill(1, toks)                         # reserves what a capture needs
+        dsi.dsi_kv_rollback(rig.kv, 1, 0)
+        t = rig.dev_i32(toks)
+        z = torch.zeros(shape.vocab, device="cuda")
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=torch.cuda.current_stream()):
+            dsi.dsi_prefill(rig.model, rig.kv, 0, t, n, z)
+        for i in range(5):
+            g.replay()
+            torch.cuda.synchronize()
+            assert rig.length(0) == (i + 1) * n
+            want = rig.prefill(1, toks, want_logits=True)
+            assert np.abs(z.cpu().numpy() - want).max() <= 2e-3
+
+
 def test_captured_launches_outlive_later_prompts():
     """Launches captured before the first wide prompt, replayed after it: it frees nothing that they use."""
     import torch
