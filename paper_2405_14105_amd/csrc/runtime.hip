@@ -144,7 +144,13 @@ struct dsi_model {
   int* tbad = nullptr;
   int4* tdec = nullptr;
   int* err = nullptr;
-  DevBuf attn_o, attn_ml;
+  // partials of chunked attention, attn_parts (row, chunk) rows of them, in one
+  // allocation, and the outgrown ones (ensure_attention)
+  size_t attn_parts = 0;
+  float* attn_o = nullptr;
+  float2* attn_ml = nullptr;
+  void* attn_slab[64] = {};
+  int attn_slabs = 0;
   WideWs wide;
   int wide_refused = 0;         // rows there was no memory for
   int live_kv = 0;
@@ -456,9 +462,38 @@ struct AttnPlan {
   int n_qtiles = 0, chunk = 0, n_chunks = 0, waves = kAttnWaves;
 };
 
-dsi_status plan_attention(dsi_model* m, dsi_kv* kv, int window0, int B, int R, AttnPlan* p) {
-  long long kmax = 0;
-  for (int b = 0; b < B; ++b) kmax = std::max(kmax, kv->hi[window0 + b] + R);
+// Partial buffers for `parts` rows.  Outgrown ones stay until the model is
+// destroyed: launches of them may be in flight or in a graph of the caller's.
+// The sizes at least double, so all of them hold less than twice the last.
+dsi_status ensure_attention(dsi_model* m, size_t parts) {
+  if (m->attn_parts >= parts) return DSI_OK;
+  const size_t each = m->hd * sizeof(float) + sizeof(float2);
+  size_t take = std::max(parts, 2 * m->attn_parts);
+  void* p = nullptr;
+  hipError_t e = hipMalloc(&p, take * each);
+  if (e != hipSuccess && take > parts) {
+    hipGetLastError();
+    take = parts;
+    e = hipMalloc(&p, take * each);
+  }
+  if (e != hipSuccess) {
+    hipGetLastError();
+    return fail(DSI_ENOMEM, "hipMalloc(%zu) failed: %s", take * each, hipGetErrorString(e));
+  }
+  if (m->attn_slabs == (int)(sizeof(m->attn_slab) / sizeof(m->attn_slab[0]))) {
+    hipFree(p);
+    return fail(DSI_ENOMEM, "attention buffers grown too often");
+  }
+  m->attn_slab[m->attn_slabs++] = p;
+  m->attn_parts = take;
+  m->attn_o = (float*)p;
+  m->attn_ml = (float2*)(m->attn_o + take * m->hd);
+  return DSI_OK;
+}
+
+// The partition for R rows of each of B windows over at most kmax keys, and
+// the partial rows it needs.
+size_t attention_plan(const dsi_model* m, const dsi_kv* kv, long long kmax, int B, int R, AttnPlan* p) {
   // The chunk size depends only on the model, R and the cache capacity --
   // never on B or the current lengths -- so a window's partial sums and
   // therefore its results are identical alone or inside a batch.
@@ -508,10 +543,13 @@ dsi_status plan_attention(dsi_model* m, dsi_kv* kv, int window0, int B, int R, A
     p->chunk = chunk_of(1, q8);
   }
   p->n_chunks = (int)((kmax + p->chunk - 1) / p->chunk);
-  const size_t nparts = (size_t)B * m->hkv * p->n_qtiles * p->n_chunks * 16;
-  DSI_TRY(ensure(m->attn_o, nparts * m->hd * sizeof(float)));
-  DSI_TRY(ensure(m->attn_ml, nparts * sizeof(float2)));
-  return DSI_OK;
+  return (size_t)B * m->hkv * p->n_qtiles * p->n_chunks * 16;
+}
+
+dsi_status plan_attention(dsi_model* m, dsi_kv* kv, int window0, int B, int R, AttnPlan* p) {
+  long long kmax = 0;
+  for (int b = 0; b < B; ++b) kmax = std::max(kmax, kv->hi[window0 + b] + R);
+  return ensure_attention(m, attention_plan(m, kv, kmax, B, R, p));
 }
 
 // Whether a forward runs its layer GEMMs on the ring layouts: every bf16
@@ -579,8 +617,8 @@ dsi_status run_forward(dsi_model* m, dsi_kv* kv, const AttnPlan& ap, int window0
     aa.chunk = ap.chunk;
     aa.n_chunks = ap.n_chunks;
     aa.scale = (float)(1.0 / sqrt((double)m->hd));
-    aa.part_o = (float*)m->attn_o.p;
-    aa.part_ml = (float2*)m->attn_ml.p;
+    aa.part_o = m->attn_o;
+    aa.part_ml = m->attn_ml;
     aa.out = m->pk_q;
     aa.wtype = m->wtype;
     aa.anc = anc;
@@ -749,14 +787,27 @@ int wide_above(const dsi_model* m) {
 // instead.  Reserves what the forwards need, so that they allocate nothing and
 // free nothing that a captured launch may use; a capturing stream cannot
 // reserve, and takes wide forwards only where an earlier prompt has.
-int wide_rows(dsi_model* m, const dsi_kv* kv, int n) {
+int wide_rows(dsi_model* m, const dsi_kv* kv, int window, int n) {
   if (n <= wide_above(m)) return 0;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (m->stream && hipStreamIsCapturing(m->stream, &cap) != hipSuccess) {
     hipGetLastError();
     return 0;
   }
-  if (cap == hipStreamCaptureStatusNone) wide_reserve(m, kv->max_len);
+  if (cap == hipStreamCaptureStatusNone) {
+    wide_reserve(m, kv->max_len);
+    // and what the forwards of one chunk would have needed: short prompts and
+    // drafts on this cache may be captured next.  Nothing here uses it, so a
+    // failure is the later call's
+    if (m->wide.rows) {
+      AttnPlan p;
+      const long long len = kv->hi[window];
+      const int whole = n / kMaxRows * kMaxRows;
+      size_t parts = whole ? attention_plan(m, kv, len + whole, 1, kMaxRows, &p) : 0;
+      if (n > whole) parts = std::max(parts, attention_plan(m, kv, len + n, 1, n - whole, &p));
+      (void)ensure_attention(m, parts);
+    }
+  }
   if (!m->wide.rows) return 0;
   const int forwards = cdiv(n, m->wide.rows);
   return (int)round_up((size_t)cdiv(n, forwards), kMaxRows);
@@ -1124,8 +1175,7 @@ dsi_status dsi_model_destroy(dsi_model* m) {
   for (auto& g : m->graphs) hipGraphExecDestroy(g.exec);
   for (hipEvent_t e : m->prof_ev) hipEventDestroy(e);
   free_list(m->allocs);
-  if (m->attn_o.p) hipFree(m->attn_o.p);
-  if (m->attn_ml.p) hipFree(m->attn_ml.p);
+  for (int i = 0; i < m->attn_slabs; ++i) hipFree(m->attn_slab[i]);
   delete m;
   return DSI_OK;
 }
@@ -1297,7 +1347,7 @@ dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* 
   if (kv->hi[window] + n > kv->max_len)
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window,
                 kv->hi[window], n, kv->max_len);
-  if (const int each = wide_rows(m, kv, n)) {
+  if (const int each = wide_rows(m, kv, window, n)) {
     for (int off = 0; off < n; off += each) {
       const int rows = std::min(each, n - off);
       const bool last = off + rows == n;
@@ -1375,7 +1425,7 @@ dsi_status dsi_verify(dsi_model* m, dsi_kv* kv, const dsi_verify_args* a, int32_
         (uint64_t)(uintptr_t)kv->k, (uint64_t)(uintptr_t)kv->v, (uint64_t)(uintptr_t)kv->lens,
         (uint64_t)kv->n_windows, (uint64_t)kv->max_len, (uint64_t)kv->maxlen_pad,
         (uint64_t)ap.n_qtiles, (uint64_t)ap.chunk, (uint64_t)ap.n_chunks, (uint64_t)ap.waves,
-        (uint64_t)(uintptr_t)m->attn_o.p, (uint64_t)(uintptr_t)m->attn_ml.p};
+        (uint64_t)(uintptr_t)m->attn_o, (uint64_t)(uintptr_t)m->attn_ml};
     DSI_TRY(replay_or_capture(m, key, launches));
   } else {
     DSI_TRY(launches());
@@ -1457,7 +1507,7 @@ dsi_status dsi_verify_tree(dsi_model* m, dsi_kv* kv, const dsi_tree_args* a, int
         (uint64_t)(uintptr_t)kv->k, (uint64_t)(uintptr_t)kv->v, (uint64_t)(uintptr_t)kv->lens,
         (uint64_t)kv->n_windows, (uint64_t)kv->max_len, (uint64_t)kv->maxlen_pad,
         (uint64_t)ap.n_qtiles, (uint64_t)ap.chunk, (uint64_t)ap.n_chunks, (uint64_t)ap.waves,
-        (uint64_t)(uintptr_t)m->attn_o.p, (uint64_t)(uintptr_t)m->attn_ml.p};
+        (uint64_t)(uintptr_t)m->attn_o, (uint64_t)(uintptr_t)m->attn_ml};
     DSI_TRY(replay_or_capture(m, key, launches));
   } else {
     DSI_TRY(launches());

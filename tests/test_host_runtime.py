@@ -1,0 +1,109 @@
+"""Decisions of the library's host code -- what is allocated when, what is
+launched -- against a HIP runtime that runs nothing (host_hip_stub.c), without
+a GPU.  Each test is a program of its own, in a process of its own."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+from paper_2405_14105_amd import dsi
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None or not os.path.exists(dsi.LIB_PATH),
+                                reason="needs gcc and the built library")
+
+PRELUDE = '''
+import ctypes, re, sys
+hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+hip.stub_budget.argtypes = [ctypes.c_size_t]
+hip.stub_in_use.restype = ctypes.c_size_t
+hip.stub_log.restype = ctypes.c_char_p
+import dsi_synth as S
+from paper_2405_14105_amd import dsi
+STREAM, P = 1, 4096                     # any addresses: nothing reads them
+
+def model(shape, layers=None):
+    kind = {"bf16": dsi.DSI_BF16, "f32": dsi.DSI_F32}
+    L = layers or shape.n_layers
+    m = dsi.dsi_model_create(dsi.make_config(L, shape.d_model, shape.n_heads, shape.n_kv_heads, shape.head_dim, shape.d_ff,
+                             shape.vocab, wdtype=kind[shape.wdtype], kvdtype=kind[shape.kvdtype]), STREAM)
+    e = 4 if shape.wdtype == "f32" else 2
+    for l in range(-1, L):
+        for name in (S.GLOBAL_TENSORS if l < 0 else S.LAYER_TENSORS):
+            n = 1
+            for x in S.tensor_shape(shape, name):
+                n *= x
+            dsi.dsi_model_set_tensor(m, l, dsi.TENSOR_IDS[name], P, n * e, True)
+    hip.stub_clear()
+    return m
+
+def launches():
+    """(kernel, its template arguments, grid) of the launches since the last stub_clear()."""
+    out = []
+    for line in hip.stub_log().decode().splitlines():
+        name, x, y, z, b = line.rsplit(" ", 4)
+        k = re.search(r"\\d+(k_[a-z0-9_]+?)(I(?:L[ij]\\d+E)+E)?Ev", name)
+        assert k, name
+        out.append((k[1], tuple(int(v) for v in re.findall(r"L[ij](\\d+)E", k[2] or "")), (int(x), int(y), int(z))))
+    return out
+'''
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip") / "libstub.so")
+    r = subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", os.path.join(HERE, "host_hip_stub.c"), "-o", so],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return so
+
+
+def run(stub, program):
+    env = dict(os.environ, PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(program), stub], capture_output=True, text=True,
+                       env=env, cwd=ROOT, timeout=120)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
+
+
+def test_short_forwards_can_be_captured_after_a_long_prompt(stub):
+    """A long prompt leaves the buffers that captured short prompts and drafts on the same cache need."""
+    run(stub, '''
+    for name in ("gqa_hd64", "tiny", "mha_hd128"):
+        for n in (65, 100, 130, 900):
+            m = model(S.SHAPES[name])
+            kv = dsi.dsi_kv_create(m, 1, 4000)
+            dsi.dsi_prefill(m, kv, 0, P, n, P)
+            dsi.dsi_kv_rollback(kv, 0, n - 64)
+            hip.stub_capture(1)
+            dsi.dsi_prefill(m, kv, 0, P, 40, P)
+            dsi.dsi_kv_rollback(kv, 0, n - 64)
+            dsi.dsi_draft(m, kv, 0, P, 2, 5, P, P, P)
+            hip.stub_capture(0)
+            assert hip.stub_refused() == 0
+            dsi.dsi_kv_destroy(kv)
+            dsi.dsi_model_destroy(m)
+    ''')
+
+
+def test_growing_buffers_free_nothing(stub):
+    """Buffers that captured launches may use are kept when longer calls need larger ones, and all are freed with the model."""
+    run(stub, '''
+    m = model(S.SHAPES["many_kv"])
+    kv = dsi.dsi_kv_create(m, 4, 30000)
+    hip.stub_clear()
+    sizes = []
+    for n in (10, 40, 64, 65, 300, 2000, 5000, 9000, 13000):
+        dsi.dsi_prefill(m, kv, 0, P, n, P)
+        sizes.append(hip.stub_mallocs())
+    dsi.dsi_verify(m, kv, 0, 4, 5, P, P, P, P, P)
+    assert hip.stub_frees() == 0
+    assert hip.stub_mallocs() <= 12                    # sizes double
+    dsi.dsi_kv_destroy(kv)
+    dsi.dsi_model_destroy(m)
+    assert hip.stub_in_use() == 0
+    ''')
