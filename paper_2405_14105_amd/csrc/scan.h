@@ -4,6 +4,7 @@
 #pragma once
 
 #include <limits.h>
+#include <math.h>
 
 #include "device_util.h"
 
@@ -143,6 +144,16 @@ __device__ __forceinline__ int block_first_or_last(int first, int last, int* sf,
 __device__ __forceinline__ double over_t(double z, double t, double inv) {
   const double q = z * inv;
   return __builtin_isfinite(q) ? fma(fma(-q, t, z), inv, q) : q;
+}
+
+// exp(z / T - m) of a softmax whose largest exponent is m; a masked entry (z =
+// -inf) adds nothing, also where all of them are masked and m is -inf too
+__device__ __forceinline__ double exp_term(float z, double t, double inv, double m) {
+  return z == -INFINITY ? 0.0 : exp(over_t((double)z, t, inv) - m);
+}
+// a chunk's sum `sum` of those over its maximum m, relative to the row's M
+__device__ __forceinline__ double chunk_term(double sum, double m, double M) {
+  return sum == 0.0 ? 0.0 : sum * exp(m - M);
 }
 
 // Entries v .. v + 3 of a row of n values, all in flight together: one

@@ -81,8 +81,7 @@ __global__ __launch_bounds__(THR) void k_vrow(VerifyArgs a) {
       double sum = 0.0;
 #pragma unroll
       for (int i = 0; i < PER; ++i)
-        if (v0 + g * THR * PER + i < a.V)
-          sum += exp(over_t((double)vals[g][i], a.temperature, a.inv_temperature) - m);
+        if (v0 + g * THR * PER + i < a.V) sum += exp_term(vals[g][i], a.temperature, a.inv_temperature, m);
       sum = wave_scan_incl(sum);
       if (lane == 63) shd[g * (THR / 64) + w] = sum;
     }
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(VT) void k_vdecide(VerifyArgs a) {
       m = wave_max(m);
       for (int c = lane; c < a.C; c += 64) {
         const double2 pc = a.part[(size_t)r * a.C + c];
-        sum += pc.y * exp(pc.x - m);
+        sum += chunk_term(pc.y, pc.x, m);
       }
       sum = wave_sum(sum);
     }

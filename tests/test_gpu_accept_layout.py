@@ -48,3 +48,28 @@ def test_layouts(V, B, k, zoff, qoff, T):
                        qp + 4 * b * k * V if k else None, du[b], n1, t1, T, dsi.DSI_SAMPLE)
         torch.cuda.synchronize()
         assert (int(n1), int(t1)) == (int(n[b]), int(tok[b]))
+
+
+@pytest.mark.parametrize("V,keep", [(4100, (0, 4096)), (40000, (4096, 40000)), (40000, (20000, 20050)), (12288, (0, 8192)),
+                                    (128256, (100000, 128000))])
+@pytest.mark.parametrize("B,k", [(2, 3), (16, 3)])
+def test_whole_chunks_masked(V, keep, B, k):
+    """Only the entries of [keep) are not -inf: first, middle and last chunks, all but one of them, a tail of four entries."""
+    z, tokens, q, u = _inputs(V, k, B, seed=V + keep[0] + k)
+    rng = np.random.default_rng(V)
+    tokens[:, 1:] = rng.integers(*keep, size=(B, k))
+    z[:, :keep[0]] = -np.inf
+    z[:, keep[1]:] = -np.inf
+    for b in range(B):                         # every draft at the target's own probability: accepted with ratio > u
+        for i in range(k):
+            p = z[b * (k + 1) + i, tokens[b, i + 1]] - np.log(np.exp(z[b * (k + 1) + i, keep[0]:keep[1]].astype(np.float64)).sum())
+            q[b, i, tokens[b, i + 1]] = np.exp(p) * (0.5 if (b + i) % 3 else 4.0)
+    n = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    tok = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    dev = [torch.from_numpy(np.ascontiguousarray(x, dtype=d)).cuda() for x, d in
+           ((z, np.float32), (tokens, np.int32), (q, np.float32), (u, np.float32))]
+    dsi.dsi_accept(torch.cuda.current_stream().cuda_stream, B, k, V, *dev, n, tok, 1.0, dsi.DSI_SAMPLE)
+    torch.cuda.synchronize()
+    n, tok = n.cpu().numpy(), tok.cpu().numpy()
+    assert np.all((tok >= keep[0]) & (tok < keep[1])) and n.max() > 0
+    assert compare(z, tokens, q, u, n, tok) <= max(1, B // 10)

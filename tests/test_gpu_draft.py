@@ -192,3 +192,28 @@ def test_si_loop_self_drafting_accepts_every_draft():
         if r.draw_margin < 1e-6:
             break
         assert np.array_equal(tok, r.window) and (n, t) == (r.n, r.token), it
+
+
+def test_masked_vocabulary_chunks():
+    """A head whose logits are -inf over whole chunks (first, last): the stored row is the softmax of the rest."""
+    shape = S.Shape("masked_head", 1, 64, 2, 2, 32, 128, 13000, wdtype="f32", kvdtype="f32")
+    rng = np.random.default_rng(3)
+    with Rig(shape, SEED, 2, 64) as rig:
+        E = S.weight(shape, SEED, -1, "embed").astype(np.float32).copy()
+        E[:, 0] = 5.0                            # the first feature is large and positive whatever the tokens
+        gain = np.zeros(64, np.float32)
+        gain[0] = 1.0                            # and the only one that the head sees
+        head = np.zeros((13000, 64), np.float32)
+        head[:, 0] = rng.standard_normal(13000) * 0.3
+        head[:4096, 0] = head[12288:, 0] = -3e38     # times about 8: -inf
+        for name, a in (("embed", E), ("final_norm", gain), ("lm_head", head)):
+            dsi.dsi_model_set_tensor(rig.model, -1, dsi.TENSOR_IDS[name], a.ctypes.data, a.nbytes, False)
+        feed = [17]
+        z = rig.prefill(1, feed, want_logits=True).astype(np.float64)
+        assert np.all(np.isneginf(z[:4096])) and np.all(np.isneginf(z[12288:])) and np.all(np.isfinite(z[4096:12288]))
+        tok, q = run_draft(rig, 0, feed, 1, np.array([0.6], np.float32))
+    want = np.exp(z - z.max())
+    want /= want.sum()
+    assert np.all(q[0][:4096] == 0) and np.all(q[0][12288:] == 0)
+    assert np.allclose(q[0][4096:12288], want[4096:12288], rtol=1e-6, atol=0)
+    assert int(tok[1]) == draw_inverse_cdf(q[0], float(np.float32(0.6)))[0]
