@@ -132,8 +132,9 @@ dsi_status dsi_kv_destroy(dsi_kv* kv);
  * advance the length and is reported by the next synchronising call
  * (DSI_EINVAL).  The same prompt on the same cache gives the same bits,
  * whatever ran before.  They differ in rounding between ways of cutting a
- * prompt into calls, and between a call captured into a graph before the
- * workspace was reserved (forwards of one chunk) and one captured after.
+ * prompt into calls, and where the workspace could not be reserved (a call
+ * captured into a graph before any long prompt ran, no memory) and prompts run
+ * in shorter forwards.
  * Stream-ordered; d_tokens is caller-owned and only read by the call's stream
  * work. */
 dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* d_tokens,

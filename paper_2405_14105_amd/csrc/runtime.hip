@@ -13,6 +13,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/dsi.h"
@@ -107,6 +108,8 @@ struct WideWs {
   int* gpos = nullptr;          // [kGposKeys + 1]
 };
 
+constexpr int kWideRetry = 16;
+
 struct dsi_model {
   dsi_config cfg;
   hipStream_t stream = nullptr;
@@ -152,7 +155,9 @@ struct dsi_model {
   void* attn_slab[64] = {};
   int attn_slabs = 0;
   WideWs wide;
-  int wide_refused = 0;         // rows there was no memory for
+  void* wide_slab[8] = {};      // at most one of every size
+  int wide_slabs = 0;
+  int wide_wait = 0;            // long prompts until a refused size is asked for again
   int live_kv = 0;
   // diagnostics: event pairs around one kernel class
   int prof_class = 0;
@@ -225,26 +230,12 @@ PackRef make_pack(dsi_model* m, int Kb, dsi_status* st) {
   return p;
 }
 
-// The workspace of wide prefill forwards (see wide_above), reserved by
-// the first prompt that needs it, for the cache's max_len (kWideRows rows at
-// most), in one allocation.  A model that has no memory for it keeps the one
-// it has, or none: prompts then run in narrower forwards.  An outgrown
-// workspace stays until the model is destroyed (launches of it may be in
-// flight or captured); the sizes are powers of two, so all of them together
-// hold less than twice the last.
-void wide_reserve(dsi_model* m, int max_len) {
-  int rows = 2 * kMaxRows;
-  while (rows < max_len && rows < kWideRows) rows *= 2;
-  if (rows <= m->wide.rows || rows <= m->wide_refused) return;
-  WideWs w;
-  w.rows = rows;
-  // one partial of the widest launch, or several of a launch with fewer rows
-  w.delta_bytes = std::max((size_t)rows * m->d * 4, (size_t)64 << 20);
-  if (m->wtype != W_BF16) w.delta_bytes = (size_t)rows * m->d * 4;   // fp32 GEMMs do not split
+// Lays out the workspace of `rows` prompt rows from `base` on (null: for its
+// size only) and returns its size; [*zero, *zero_end) is to be cleared.
+size_t wide_layout(const dsi_model* m, int rows, char* base, WideWs* w, size_t* zero, size_t* zero_end) {
   size_t total = 0;
-  std::vector<std::pair<void**, size_t>> parts;
-  auto part = [&](void** p, size_t bytes) {
-    parts.push_back({p, total});
+  auto part = [&](auto** p, size_t bytes) {
+    *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>((uintptr_t)base + total);
     total += round_up(bytes, 256);
   };
   auto pack = [&](PackRef& p, int Kb) {
@@ -253,34 +244,67 @@ void wide_reserve(dsi_model* m, int max_len) {
     part(&p.hi, elems * m->esz);
     if (m->wtype == W_BF16) part(&p.lo, elems * 2);
   };
-  part((void**)&w.x, (size_t)rows * m->d * 4);
-  part((void**)&w.delta, w.delta_bytes);
-  pack(w.pk_d, m->Kb_d);
-  pack(w.pk_q, m->Kb_q);
-  const size_t ff0 = total;
-  pack(w.pk_ff, m->Kb_ff);
-  const size_t ff1 = total;
-  part((void**)&w.qbuf, (size_t)rows * m->qdim * 4);
-  part((void**)&w.attn_o, kChunkParts * m->hd * sizeof(float));
-  part((void**)&w.attn_ml, kChunkParts * sizeof(float2));
-  part((void**)&w.rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
-  part((void**)&w.gpos, (size_t)(kGposKeys + 1) * sizeof(int));
+  w->rows = rows;
+  // one partial of the widest launch, or several of a launch with fewer rows
+  w->delta_bytes = std::max((size_t)rows * m->d * 4, (size_t)64 << 20);
+  if (m->wtype != W_BF16) w->delta_bytes = (size_t)rows * m->d * 4;   // fp32 GEMMs do not split
+  part(&w->x, (size_t)rows * m->d * 4);
+  part(&w->delta, w->delta_bytes);
+  pack(w->pk_d, m->Kb_d);
+  pack(w->pk_q, m->Kb_q);
+  *zero = total;
+  pack(w->pk_ff, m->Kb_ff);
+  *zero_end = total;
+  part(&w->qbuf, (size_t)rows * m->qdim * 4);
+  part(&w->attn_o, kChunkParts * m->hd * sizeof(float));
+  part(&w->attn_ml, kChunkParts * sizeof(float2));
+  part(&w->rope, (size_t)rows * (m->hd / 2) * sizeof(float2));
+  part(&w->gpos, (size_t)(kGposKeys + 1) * sizeof(int));
+  return total;
+}
+
+bool wide_alloc(dsi_model* m, int rows) {
+  WideWs w;
+  size_t z0 = 0, z1 = 0;
+  const size_t total = wide_layout(m, rows, nullptr, &w, &z0, &z1);
   char* slab = nullptr;
   if (hipMalloc((void**)&slab, total) != hipSuccess) {
     hipGetLastError();
-    m->wide_refused = rows;
-    return;
+    return false;
   }
-  for (auto& p : parts) *p.first = slab + p.second;
   // the FFN pack's columns past d_ff are multiplied (by zero weights) and
   // never written
-  if (m->ff % 32 && launch_fill_zero(slab + ff0, ff1 - ff0, m->stream) != hipSuccess) {
+  if (m->ff % 32 && launch_fill_zero(slab + z0, z1 - z0, m->stream) != hipSuccess) {
+    hipGetLastError();
     hipFree(slab);
-    m->wide_refused = rows;
+    return false;
+  }
+  wide_layout(m, rows, slab, &w, &z0, &z1);
+  m->wide = w;
+  m->wide_slab[m->wide_slabs++] = slab;
+  return true;
+}
+
+// The workspace of wide prefill forwards (see wide_above), reserved by
+// the first prompt that needs it, for the cache's max_len (kWideRows rows at
+// most), in one allocation.  Where there is no memory for that it takes the
+// largest half, quarter, ... there is (prompts run in more forwards, or in
+// those of 64 rows) and asks for the whole again kWideRetry long prompts later
+// or when a cache has been destroyed.  An outgrown workspace stays until the
+// model is destroyed (launches of it may be in flight or captured); the sizes
+// are powers of two, so all of them together hold less than twice the last.
+void wide_reserve(dsi_model* m, int max_len) {
+  int rows = 2 * kMaxRows;
+  while (rows < max_len && rows < kWideRows) rows *= 2;
+  if (rows <= m->wide.rows) return;
+  if (m->wide_wait > 0) {
+    --m->wide_wait;
     return;
   }
-  m->allocs.push_back(slab);
-  m->wide = w;
+  if (wide_alloc(m, rows)) return;
+  m->wide_wait = kWideRetry;
+  for (rows /= 2; rows >= 2 * kMaxRows && rows > m->wide.rows; rows /= 2)
+    if (wide_alloc(m, rows)) return;
 }
 
 // event pair around the launches of one kernel class (diagnostics only)
@@ -1176,6 +1200,7 @@ dsi_status dsi_model_destroy(dsi_model* m) {
   for (hipEvent_t e : m->prof_ev) hipEventDestroy(e);
   free_list(m->allocs);
   for (int i = 0; i < m->attn_slabs; ++i) hipFree(m->attn_slab[i]);
+  for (int i = 0; i < m->wide_slabs; ++i) hipFree(m->wide_slab[i]);
   delete m;
   return DSI_OK;
 }
@@ -1334,6 +1359,7 @@ dsi_status dsi_kv_destroy(dsi_kv* kv) {
   hipFree(kv->v);
   hipFree(kv->lens);
   kv->m->live_kv--;
+  kv->m->wide_wait = 0;
   delete kv;
   return DSI_OK;
 }

@@ -47,9 +47,9 @@ def launches():
     out = []
     for line in hip.stub_log().decode().splitlines():
         name, x, y, z, b = line.rsplit(" ", 4)
-        k = re.search(r"\\d+(k_[a-z0-9_]+?)(I(?:L[ij]\\d+E)+E)?Ev", name)
+        k = re.search(r"\\d(k_[a-z0-9_]+)", name)
         assert k, name
-        out.append((k[1], tuple(int(v) for v in re.findall(r"L[ij](\\d+)E", k[2] or "")), (int(x), int(y), int(z))))
+        out.append((k[1], tuple(int(v) for v in re.findall(r"L[ij](\\d+)E", name)), (int(x), int(y), int(z))))
     return out
 '''
 
@@ -106,4 +106,41 @@ def test_growing_buffers_free_nothing(stub):
     dsi.dsi_kv_destroy(kv)
     dsi.dsi_model_destroy(m)
     assert hip.stub_in_use() == 0
+    ''')
+
+
+def test_prompt_workspace_under_memory_pressure(stub):
+    """Where the whole workspace does not fit, a smaller one is taken; a refusal ends with the shortage."""
+    run(stub, '''
+    shape = S.SHAPES["llama1b"]
+    def forwards(n=2000):
+        hip.stub_clear()
+        dsi.dsi_prefill(m, kv, 0, P, n, P)
+        dsi.dsi_kv_rollback(kv, 0, 0)
+        return sum(k == "k_prefill_rows" for k, _, _ in launches())    # of wide forwards; 0: 64-row ones
+    m = model(shape, layers=1)
+    kv, other = (dsi.dsi_kv_create(m, 1, 2048) for _ in range(2))
+    dsi.dsi_prefill(m, other, 0, P, 10, P)
+    dsi.dsi_prefill(m, kv, 0, P, 64, P)                 # the 64-row forwards' buffers
+    dsi.dsi_kv_rollback(kv, 0, 0)
+    base = hip.stub_in_use()
+    assert forwards() == 1
+    whole = hip.stub_in_use() - base
+    m = model(shape, layers=1)
+    kv = dsi.dsi_kv_create(m, 1, 2048)
+    other = dsi.dsi_kv_create(m, 1, 2048)
+    hip.stub_budget(whole * 3 // 4)
+    assert forwards() == 2                              # half the rows
+    hip.stub_budget(1 << 40)
+    counts = [forwards() for _ in range(20)]
+    assert counts[0] == 2 and counts[-1] == 1           # the whole, some prompts later
+    m = model(shape, layers=1)
+    kv = dsi.dsi_kv_create(m, 1, 2048)
+    other = dsi.dsi_kv_create(m, 1, 2048)
+    hip.stub_budget(32 << 20)
+    assert forwards() == 0
+    hip.stub_budget(1 << 40)
+    assert forwards() == 0
+    dsi.dsi_kv_destroy(other)                           # memory came back
+    assert forwards() == 1
     ''')
