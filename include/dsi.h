@@ -99,7 +99,11 @@ enum {
  * the first time it sees a combination of arguments (pointers, sizes, mode,
  * cache) and replays that graph on later calls with the same combination
  * (up to 16 are cached per model; the environment variable DSI_GRAPHS=0
- * read here disables this).  Results are identical either way. */
+ * read here disables this).  Results are identical either way.
+ * bf16 layer and head weights are stored a second time in the order that
+ * forwards of up to DSI_MAX_ROWS rows stream them, where the device has the
+ * memory (about 16 GB at an 8B shape, 26 GB at 13B; d_model up to 5120).
+ * DSI_RING=0, read here, does without. */
 dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out);
 
 /* Upload one tensor (host memory if src_on_device == 0, else device memory).
@@ -114,7 +118,11 @@ dsi_status dsi_model_destroy(dsi_model* m);
 
 /* KV cache for n_windows independent windows of up to max_len positions each
  * (the per-server cache of Section 3.1, one per concurrent verification
- * task).  Lengths start at 0 and live on the device. */
+ * task).  Lengths start at 0 and live on the device.  A cache for which there
+ * is no memory otherwise takes that of the weights' second copy and of the
+ * model's prompt workspace, after the work enqueued so far: later calls are
+ * slower and may round differently.  Not once the caller has captured calls on
+ * the model, whose launches use them (DSI_ENOMEM then). */
 dsi_status dsi_kv_create(dsi_model* m, int32_t n_windows, int32_t max_len, dsi_kv** out);
 dsi_status dsi_kv_destroy(dsi_kv* kv);
 

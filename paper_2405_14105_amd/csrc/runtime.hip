@@ -129,6 +129,8 @@ struct dsi_model {
   std::vector<LayerW> layers;
   std::vector<unsigned> set_mask;   // [L+1]: bit per tensor id (index 0: globals)
   std::vector<void*> allocs;
+  std::vector<void*> ring_allocs;   // the ring layouts: copies the model can do without (give_back)
+  bool captured = false;        // a caller has captured calls: their launches hold every buffer
   // forward workspace for up to kMaxRows rows
   float* x = nullptr;
   float* delta = nullptr;       // [kMaxSplits][kMaxRows][d] K-split partial outputs
@@ -282,6 +284,49 @@ bool wide_alloc(dsi_model* m, int rows) {
   wide_layout(m, rows, slab, &w, &z0, &z1);
   m->wide = w;
   m->wide_slab[m->wide_slabs++] = slab;
+  return true;
+}
+
+void drop_rings(dsi_model* m) {
+  free_list(m->ring_allocs);
+  m->lm_head_s = nullptr;
+  for (LayerW& w : m->layers) w.wqkv_s = w.wo_s = w.wgu_s = w.wdown_s = nullptr;
+  m->use_ring = false;
+}
+
+// Whether the model's stream is being captured, and a note that it was.
+bool capturing(dsi_model* m) {
+  if (!m->stream) return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(m->stream, &cap) != hipSuccess) {
+    hipGetLastError();
+    cap = hipStreamCaptureStatusActive;
+  }
+  if (cap != hipStreamCaptureStatusNone) m->captured = true;
+  return cap != hipStreamCaptureStatusNone;
+}
+
+// Gives back what the model can do without: the ring layouts, the prompt
+// workspaces (the next long prompt asks again) and outgrown attention buffers.
+// Not where a graph of the caller's may use them.  False: nothing to give.
+bool give_back(dsi_model* m) {
+  if (capturing(m) || m->captured) return false;
+  if (m->ring_allocs.empty() && !m->wide_slabs && m->attn_slabs < 2) return false;
+  if (hipStreamSynchronize(m->stream) != hipSuccess) {
+    hipGetLastError();
+    return false;
+  }
+  for (auto& g : m->graphs) hipGraphExecDestroy(g.exec);
+  m->graphs.clear();
+  drop_rings(m);
+  for (int i = 0; i < m->wide_slabs; ++i) hipFree(m->wide_slab[i]);
+  m->wide = WideWs{};
+  m->wide_slabs = m->wide_wait = 0;
+  for (int i = 0; i + 1 < m->attn_slabs; ++i) hipFree(m->attn_slab[i]);
+  if (m->attn_slabs > 1) {
+    m->attn_slab[0] = m->attn_slab[m->attn_slabs - 1];
+    m->attn_slabs = 1;
+  }
   return true;
 }
 
@@ -803,7 +848,8 @@ int key_chunks(const dsi_model* m, int M, int rb0, int keys) {
 // ones at four (tiny, 48 rows after 900: 89 and 88; 64: 103 and 91).
 int wide_above(const dsi_model* m) {
   if (m->wtype != W_BF16) return 48;
-  return m->use_ring && m->rc_qkv.nbw && m->rc_o.nbw && m->rc_gu.nbw && m->rc_down.nbw ? kMaxRows : 32;
+  const LayerW& w = m->layers[0];
+  return m->use_ring && w.wqkv_s && w.wo_s && w.wgu_s && w.wdown_s ? kMaxRows : 32;
 }
 
 // Rows per wide forward of a prompt of n tokens: forwards of about equal size,
@@ -811,14 +857,9 @@ int wide_above(const dsi_model* m) {
 // instead.  Reserves what the forwards need, so that they allocate nothing and
 // free nothing that a captured launch may use; a capturing stream cannot
 // reserve, and takes wide forwards only where an earlier prompt has.
-int wide_rows(dsi_model* m, const dsi_kv* kv, int window, int n) {
+int wide_rows(dsi_model* m, const dsi_kv* kv, int window, int n, bool capture) {
   if (n <= wide_above(m)) return 0;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (m->stream && hipStreamIsCapturing(m->stream, &cap) != hipSuccess) {
-    hipGetLastError();
-    return 0;
-  }
-  if (cap == hipStreamCaptureStatusNone) {
+  if (!capture) {
     wide_reserve(m, kv->max_len);
     // and what the forwards of one chunk would have needed: short prompts and
     // drafts on this cache may be captured next.  Nothing here uses it, so a
@@ -1148,7 +1189,6 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
   A(&m->embed, (size_t)m->V * m->d * m->esz);
   A((void**)&m->final_norm, (size_t)m->d * 4);
   A(&m->lm_head, (size_t)m->Nb_head * m->Kb_d * tile * m->esz);
-  if (m->use_ring && m->rc_head.nbw) A(&m->lm_head_s, m->rc_head.tiles() * tile * m->esz);
   for (int l = 0; l < m->L && st == DSI_OK; ++l) {
     LayerW& w = m->layers[l];
     A((void**)&w.attn_norm, (size_t)m->d * 4);
@@ -1157,12 +1197,6 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
     A(&w.wo, (size_t)m->Nb_o * m->Kb_q * tile * m->esz);
     A(&w.wgu, (size_t)m->Nb_gu * m->Kb_d * tile * m->esz);
     A(&w.wdown, (size_t)m->Nb_down * m->Kb_ff * tile * m->esz);
-    if (m->use_ring) {
-      if (m->rc_qkv.nbw) A(&w.wqkv_s, m->rc_qkv.tiles() * tile * m->esz);
-      if (m->rc_o.nbw) A(&w.wo_s, m->rc_o.tiles() * tile * m->esz);
-      if (m->rc_gu.nbw) A(&w.wgu_s, m->rc_gu.tiles() * tile * m->esz);
-      if (m->rc_down.nbw) A(&w.wdown_s, m->rc_down.tiles() * tile * m->esz);
-    }
   }
   A((void**)&m->x, (size_t)kMaxRows * m->d * 4);
   A((void**)&m->delta, (size_t)kMaxSplits * kMaxRows * m->d * 4);
@@ -1188,6 +1222,18 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
     delete m;
     return st;
   }
+  // the ring layouts last: a model that has no memory for all of them runs on
+  // the packed ones
+  auto ring = [&](void** p, const RingCfg& c) {
+    if (m->use_ring && c.nbw && dev_alloc(m->ring_allocs, p, c.tiles() * tile * m->esz) != DSI_OK) drop_rings(m);
+  };
+  ring(&m->lm_head_s, m->rc_head);
+  for (LayerW& w : m->layers) {
+    ring(&w.wqkv_s, m->rc_qkv);
+    ring(&w.wo_s, m->rc_o);
+    ring(&w.wgu_s, m->rc_gu);
+    ring(&w.wdown_s, m->rc_down);
+  }
   *out = m;
   return DSI_OK;
 }
@@ -1199,6 +1245,7 @@ dsi_status dsi_model_destroy(dsi_model* m) {
   for (auto& g : m->graphs) hipGraphExecDestroy(g.exec);
   for (hipEvent_t e : m->prof_ev) hipEventDestroy(e);
   free_list(m->allocs);
+  free_list(m->ring_allocs);
   for (int i = 0; i < m->attn_slabs; ++i) hipFree(m->attn_slab[i]);
   for (int i = 0; i < m->wide_slabs; ++i) hipFree(m->wide_slab[i]);
   delete m;
@@ -1251,6 +1298,10 @@ dsi_status dsi_model_set_tensor(dsi_model* m, int32_t layer, int32_t id, const v
     void* staging = nullptr;
     if (!src_on_device) {
       hipError_t e = hipMalloc(&staging, nbytes);
+      if (e == hipErrorOutOfMemory && give_back(m)) {
+        hipGetLastError();
+        e = hipMalloc(&staging, nbytes);
+      }
       if (e != hipSuccess) {
         hipGetLastError();
         return fail(DSI_ENOMEM, "staging hipMalloc(%zu) failed", nbytes);
@@ -1339,11 +1390,16 @@ dsi_status dsi_kv_create(dsi_model* m, int32_t n_windows, int32_t max_len, dsi_k
   kv->lo.assign(n_windows, 0);
   const size_t bytes = (size_t)m->L * n_windows * kv->win_elems * m->kvesz;
   std::vector<void*> list;
-  dsi_status st = dev_alloc(list, &kv->k, bytes);
-  if (st == DSI_OK) st = dev_alloc(list, &kv->v, bytes);
-  if (st == DSI_OK) st = dev_alloc(list, (void**)&kv->lens, (size_t)n_windows * sizeof(int));
+  auto alloc = [&]() {
+    dsi_status st = dev_alloc(list, &kv->k, bytes);
+    if (st == DSI_OK) st = dev_alloc(list, &kv->v, bytes);
+    if (st == DSI_OK) st = dev_alloc(list, (void**)&kv->lens, (size_t)n_windows * sizeof(int));
+    if (st != DSI_OK) free_list(list);
+    return st;
+  };
+  dsi_status st = alloc();
+  if (st == DSI_ENOMEM && give_back(m)) st = alloc();   // a cache that fits without the copies is not refused
   if (st != DSI_OK) {
-    free_list(list);
     delete kv;
     return st;
   }
@@ -1373,7 +1429,7 @@ dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* 
   if (kv->hi[window] + n > kv->max_len)
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window,
                 kv->hi[window], n, kv->max_len);
-  if (const int each = wide_rows(m, kv, window, n)) {
+  if (const int each = wide_rows(m, kv, window, n, capturing(m))) {
     for (int off = 0; off < n; off += each) {
       const int rows = std::min(each, n - off);
       const bool last = off + rows == n;
@@ -1405,6 +1461,7 @@ dsi_status dsi_verify(dsi_model* m, dsi_kv* kv, const dsi_verify_args* a, int32_
     return fail(DSI_EINVAL, "windows [%d, %d) outside the cache's %d", a->window0, a->window0 + B,
                 kv->n_windows);
   if (!all_set(m)) return fail(DSI_ESTATE, "not every model tensor has been set");
+  (void)capturing(m);
   for (int b = 0; b < B; ++b)
     if (kv->hi[a->window0 + b] + k + 1 > kv->max_len)
       return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", a->window0 + b,
@@ -1475,6 +1532,7 @@ dsi_status dsi_verify_tree(dsi_model* m, dsi_kv* kv, const dsi_tree_args* a, int
     return fail(DSI_EINVAL, "windows [%d, %d) outside the cache's %d", a->window0, a->window0 + B,
                 kv->n_windows);
   if (!all_set(m)) return fail(DSI_ESTATE, "not every model tensor has been set");
+  (void)capturing(m);
   for (int b = 0; b < B; ++b)
     if (kv->hi[a->window0 + b] + R > kv->max_len)
       return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", a->window0 + b,
@@ -1553,6 +1611,7 @@ dsi_status dsi_draft(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* d_
   if (!d_u || !d_tokens || !d_q) return fail(DSI_EINVAL, "null uniforms / output pointer");
   if (!(temperature > 0.f) || !std::isfinite(temperature)) return fail(DSI_EINVAL, "temperature must be > 0");
   if (!all_set(m)) return fail(DSI_ESTATE, "not every model tensor has been set");
+  (void)capturing(m);
   if (kv->hi[window] + n_feed + k - 1 > kv->max_len)
     return fail(DSI_ECAPACITY, "window %d: length (<= %lld) + %d exceeds max_len %d", window, kv->hi[window],
                 n_feed + k - 1, kv->max_len);

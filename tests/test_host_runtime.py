@@ -144,3 +144,67 @@ def test_prompt_workspace_under_memory_pressure(stub):
     dsi.dsi_kv_destroy(other)                           # memory came back
     assert forwards() == 1
     ''')
+
+
+def test_weight_copies_give_way(stub):
+    """A model and a cache that fit without the second copy of the weights are not refused for it."""
+    run(stub, '''
+    shape = S.SHAPES["llama13b"]
+    GB = 1 << 30
+    def rings(kv, rows=11):
+        hip.stub_clear()
+        dsi.dsi_verify(m, kv, 0, 1, rows - 1, P, P, P, P, P, commit=False)
+        n = [k for k, _, _ in launches()]
+        return sum(k == "k_gemm_ring" for k in n), sum(k == "k_gemm_bf16" for k in n)
+    # room for everything
+    m = model(shape, 4)
+    used = hip.stub_in_use()
+    kv = dsi.dsi_kv_create(m, 1, 32768)
+    cache = hip.stub_in_use() - used
+    assert rings(kv) == (17, 0)
+    dsi.dsi_kv_destroy(kv)
+    dsi.dsi_model_destroy(m)
+    assert hip.stub_in_use() == 0
+    # the model alone has no room for the copies
+    hip.stub_budget(used * 6 // 10)
+    m = model(shape, 4)
+    hip.stub_budget(cache + (1 << 28))
+    kv = dsi.dsi_kv_create(m, 1, 32768)
+    assert rings(kv) == (0, 17)
+    dsi.dsi_kv_destroy(kv)
+    dsi.dsi_model_destroy(m)
+    assert hip.stub_in_use() == 0
+    # a cache comes later and needs their room; calls go on, in graphs of the library's too
+    for late in (False, True):
+        hip.stub_budget(used + 2 * cache)
+        m = model(shape, 4)
+        a = dsi.dsi_kv_create(m, 1, 32768)
+        if late:
+            assert rings(a) == (17, 0)
+            dsi.dsi_prefill(m, a, 0, P, 300, P)
+        hip.stub_budget(cache)
+        b = dsi.dsi_kv_create(m, 1, 32768 + 4096)
+        assert rings(a) == (0, 17) and rings(b) == (0, 17)
+        dsi.dsi_prefill(m, b, 0, P, 300, P)
+        dsi.dsi_kv_destroy(a)
+        dsi.dsi_kv_destroy(b)
+        dsi.dsi_model_destroy(m)
+        assert hip.stub_in_use() == 0
+    # a graph of the caller's may hold them: then they stay
+    hip.stub_budget(used + 2 * cache)
+    m = model(shape, 4)
+    a = dsi.dsi_kv_create(m, 1, 32768)
+    dsi.dsi_prefill(m, a, 0, P, 60, P)
+    hip.stub_capture(1)
+    dsi.dsi_prefill(m, a, 0, P, 60, P)
+    hip.stub_capture(0)
+    hip.stub_budget(cache)
+    hip.stub_clear()
+    try:
+        dsi.dsi_kv_create(m, 1, 32768 + 4096)
+    except dsi.DsiError as e:
+        assert e.status == dsi.DSI_ENOMEM
+    else:
+        raise AssertionError("a cache larger than the memory")
+    assert hip.stub_frees() <= 2 and rings(a) == (17, 0)     # of the failed attempt
+    ''')
