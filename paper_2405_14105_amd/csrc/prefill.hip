@@ -568,13 +568,17 @@ __global__ __launch_bounds__(HD * 4) void k_attn_prefill_combine(AttnArgs a, int
 
 }  // namespace
 
+// NT variants of launches that no plan makes with one row tile are not built:
+// eight waves along the features of O and down (at most 512 n-blocks, 16
+// workgroups), four and eight of an unsplit QKV
 template <int MT, int NWN, int NT>
 hipError_t launch_wide_epi(const GemmArgs& a, const WideGrid& g, hipStream_t s) {
   const dim3 gd(g.per_xcd * 8), bd(kWideWaves * 64);
+  constexpr int NT_PART = NWN == 8 ? 0 : NT, NT_QKV = NWN == 2 ? NT : 0;
   switch (a.epi.kind) {
-    case EPI_PART: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_PART, NT>), gd, bd, 0, s, a, g); break;
+    case EPI_PART: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_PART, NT_PART>), gd, bd, 0, s, a, g); break;
     case EPI_TILE: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_TILE, NT>), gd, bd, 0, s, a, g); break;
-    case EPI_QKV: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_QKV, NT>), gd, bd, 0, s, a, g); break;
+    case EPI_QKV: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_QKV, NT_QKV>), gd, bd, 0, s, a, g); break;
     case EPI_SILU: hipLaunchKernelGGL((k_gemm_wide<MT, NWN, EPI_SILU, NT>), gd, bd, 0, s, a, g); break;
     default: return hipErrorInvalidValue;
   }

@@ -33,6 +33,8 @@ int stub_mallocs(void) { return mallocs; }
 int stub_frees(void) { return frees; }
 int stub_refused(void) { return refused; }
 const char* stub_log(void) { return text ? text : ""; }
+int stub_kernels(void) { return n_kernels; }
+const char* stub_kernel(int i) { return kernels[i].name; }
 void stub_clear(void) {
   mallocs = frees = refused = 0;
   text_len = 0;

@@ -8,6 +8,7 @@ from oracle import forward64
 from oracle.model import embed64, layer64
 from paper_2405_14105_amd import dsi
 from parity import reg_of
+from wide_cases import WIDE_CASES
 
 pytestmark = pytest.mark.gpu
 SEED = 5
@@ -22,15 +23,16 @@ def _weights(shape):
     return lambda l, n: S.weight(shape, SEED, l, n).astype(np.float64)
 
 
-# one row past a chunk, row tiles of 4-8 blocks, one row past a tile, two and
-# three row tiles; prefixes that end off the 16-, 32- and 64-row grids; group
-# sizes 1, 3, 4 and 16; ragged FFN and K splits; several key chunks
+# one row past a chunk, one row past a tile, two and three row tiles of four and
+# five blocks (every GEMM variant: test_every_gemm_variant); prefixes that end
+# off the 16-, 32- and 64-row grids; group sizes 1, 3, 4 and 16; ragged FFN, K
+# splits of O and down; several key chunks
 @pytest.mark.parametrize("name,prefix,n", [
     ("ragged_bf16", 0, 65), ("ragged_bf16", 5, 129), ("gqa_hd64", 0, 97), ("gqa_hd64", 37, 257),
     ("mha_hd128", 63, 112), ("mha_hd128", 700, 66), ("many_kv", 0, 200), ("o_ring_hd128", 64, 300),
     ("ring_wide_ff", 31, 81),
     # fp32 weights and / or cache
-    ("tiny", 0, 65), ("tiny", 40, 300), ("ragged_f32", 7, 130), ("hd96_kvf32", 33, 129), ("f32w_bf16kv", 0, 200)])
+    ("tiny", 0, 65), ("tiny", 40, 300), ("tiny", 33, 49), ("tiny", 9, 64), ("ragged_f32", 7, 130), ("hd96_kvf32", 33, 129), ("f32w_bf16kv", 0, 200)])
 def test_matches_oracle(name, prefix, n):
     shape = S.SHAPES[name]
     toks = S.prefix_tokens(shape, SEED, 0, prefix + n)
@@ -88,6 +90,51 @@ def test_sums_are_no_less_exact_than_in_32_token_calls(name, prefix, n, limit):
         ea, eb = (float(np.linalg.norm(y[prefix:] - want) / np.linalg.norm(want)) for y in (a, b))
         print(f"{name} {prefix}+{n}: {ea:.4g} against {eb:.4g}, {ea / eb:.4f}")
         assert ea <= limit * eb
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,ff,n", WIDE_CASES)
+def test_every_gemm_variant(d, hq, hkv, hd, ff, n):
+    """Every tile, split, epilogue and fold of the prefill GEMM, against the window kernels (calls of at most 32 rows, which
+    other tests hold to the oracle): last row's logits, keys and values of both layers, in an fp32 cache.  The bound is the
+    one of test_matches_oracle for bf16 hi + lo activations."""
+    import torch
+    V, prefix = 256, 21
+    g = torch.Generator(device="cuda").manual_seed(n)
+    m = dsi.dsi_model_create(dsi.make_config(2, d, hq, hkv, hd, ff, V, kvdtype=dsi.DSI_F32), torch.cuda.current_stream().cuda_stream)
+    kv = None
+    try:
+        def put(layer, name, *shape):
+            w = torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16).mul_(0.02)
+            if name.endswith("norm"):
+                w.mul_(5).add_(1)
+            torch.cuda.synchronize()
+            dsi.dsi_model_set_tensor(m, layer, dsi.TENSOR_IDS[name], w.data_ptr(), w.numel() * 2, True)
+        put(-1, "embed", V, d), put(-1, "final_norm", d), put(-1, "lm_head", V, d)
+        for l in range(2):
+            put(l, "attn_norm", d), put(l, "ffn_norm", d)
+            put(l, "wq", hq * hd, d), put(l, "wk", hkv * hd, d), put(l, "wv", hkv * hd, d), put(l, "wo", d, hq * hd)
+            put(l, "w_gate", ff, d), put(l, "w_up", ff, d), put(l, "w_down", d, ff)
+        kv = dsi.dsi_kv_create(m, 2, prefix + n)
+        toks = torch.randint(0, V, (prefix + n,), generator=g, device="cuda", dtype=torch.int32)
+        z = torch.full((2, V), float("nan"), device="cuda")
+        dsi.dsi_prefill(m, kv, 0, toks, prefix)
+        dsi.dsi_prefill(m, kv, 0, toks[prefix:], n, z[0])
+        for i in range(0, prefix + n, 32):
+            dsi.dsi_prefill(m, kv, 1, toks[i:], min(32, prefix + n - i), z[1])
+        out = [[torch.full((hkv, prefix + n, hd), float("nan"), device="cuda") for _ in range(4)] for _ in range(2)]
+        for w in range(2):
+            for l in range(2):
+                dsi.dsi_kv_export(kv, w, l, prefix + n, out[w][2 * l], out[w][2 * l + 1])
+        assert dsi.dsi_kv_length(kv, 0) == dsi.dsi_kv_length(kv, 1) == prefix + n
+        worst = [float(((a - b).abs() / b.abs().amax(-1, keepdim=True)).max()) for a, b in zip(*out)]
+        dz = float((z[0] - z[1]).abs().max() / z[1].abs().max())
+        print(f"{(d, hq, hkv, hd, ff, n)}: {dz:.2g}, keys and values {max(worst):.2g}")
+        assert dz <= 1e-4 and max(worst) <= 1e-4
+    finally:
+        torch.cuda.synchronize()
+        if kv:
+            dsi.dsi_kv_destroy(kv)
+        dsi.dsi_model_destroy(m)
 
 
 def test_more_than_one_forward():

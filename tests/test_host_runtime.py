@@ -22,7 +22,7 @@ import ctypes, re, sys
 hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 hip.stub_budget.argtypes = [ctypes.c_size_t]
 hip.stub_in_use.restype = ctypes.c_size_t
-hip.stub_log.restype = ctypes.c_char_p
+hip.stub_log.restype = hip.stub_kernel.restype = ctypes.c_char_p
 import dsi_synth as S
 from paper_2405_14105_amd import dsi
 STREAM, P = 1, 4096                     # any addresses: nothing reads them
@@ -42,15 +42,22 @@ def model(shape, layers=None):
     hip.stub_clear()
     return m
 
+def kernel(name):
+    """(kernel, its template arguments)"""
+    k = re.search(r"\\d(k_[a-z0-9_]+)", name)
+    assert k, name
+    return k[1], tuple(int(v) for v in re.findall(r"L[ij](\\d+)E", name))
+
 def launches():
     """(kernel, its template arguments, grid) of the launches since the last stub_clear()."""
     out = []
     for line in hip.stub_log().decode().splitlines():
         name, x, y, z, b = line.rsplit(" ", 4)
-        k = re.search(r"\\d(k_[a-z0-9_]+)", name)
-        assert k, name
-        out.append((k[1], tuple(int(v) for v in re.findall(r"L[ij](\\d+)E", name)), (int(x), int(y), int(z))))
+        out.append(kernel(name) + ((int(x), int(y), int(z)),))
     return out
+
+def built():
+    return {kernel(hip.stub_kernel(i).decode()) for i in range(hip.stub_kernels())}
 '''
 
 
@@ -143,6 +150,26 @@ def test_prompt_workspace_under_memory_pressure(stub):
     assert forwards() == 0
     dsi.dsi_kv_destroy(other)                           # memory came back
     assert forwards() == 1
+    ''')
+
+
+def test_prompt_cases_launch_every_variant(stub):
+    """Every variant of the prefill GEMM that is built is one that a prompt of wide_cases.py launches."""
+    run(stub, '''
+    sys.path.insert(0, "tests")
+    from wide_cases import WIDE_CASES
+    seen = set()
+    for d, hq, hkv, hd, ff, n in WIDE_CASES:
+        m = model(S.Shape("case", 2, d, hq, hkv, hd, ff, 256, kvdtype="f32"))
+        kv = dsi.dsi_kv_create(m, 2, 21 + n)
+        dsi.dsi_prefill(m, kv, 0, P, n, P)
+        here = {l[:2] for l in launches() if l[0] in ("k_gemm_wide", "k_wide_fold")}
+        assert here, (d, ff, n)
+        seen |= here
+        dsi.dsi_kv_destroy(kv)
+        dsi.dsi_model_destroy(m)
+    want = {k for k in built() if k[0] in ("k_gemm_wide", "k_wide_fold")}
+    assert len(want) > 20 and seen == want, (sorted(want - seen), sorted(seen - want))
     ''')
 
 
