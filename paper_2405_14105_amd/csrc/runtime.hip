@@ -1182,13 +1182,25 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
   m->set_mask.assign(m->L + 1, 0u);
 
   dsi_status st = DSI_OK;
+  // the ring layouts give way to what the model cannot do without
   auto A = [&](void** p, size_t bytes) {
-    if (st == DSI_OK) st = dev_alloc(m->allocs, p, bytes);
+    if (st != DSI_OK) return;
+    st = dev_alloc(m->allocs, p, bytes);
+    if (st == DSI_ENOMEM && !m->ring_allocs.empty()) {
+      drop_rings(m);
+      st = dev_alloc(m->allocs, p, bytes);
+    }
   };
   const size_t tile = 512;
+  auto ring = [&](void** p, const RingCfg& c) {
+    if (st == DSI_OK && m->use_ring && c.nbw &&
+        dev_alloc(m->ring_allocs, p, c.tiles() * tile * m->esz) != DSI_OK)
+      drop_rings(m);
+  };
   A(&m->embed, (size_t)m->V * m->d * m->esz);
   A((void**)&m->final_norm, (size_t)m->d * 4);
   A(&m->lm_head, (size_t)m->Nb_head * m->Kb_d * tile * m->esz);
+  ring(&m->lm_head_s, m->rc_head);
   for (int l = 0; l < m->L && st == DSI_OK; ++l) {
     LayerW& w = m->layers[l];
     A((void**)&w.attn_norm, (size_t)m->d * 4);
@@ -1197,6 +1209,10 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
     A(&w.wo, (size_t)m->Nb_o * m->Kb_q * tile * m->esz);
     A(&w.wgu, (size_t)m->Nb_gu * m->Kb_d * tile * m->esz);
     A(&w.wdown, (size_t)m->Nb_down * m->Kb_ff * tile * m->esz);
+    ring(&w.wqkv_s, m->rc_qkv);
+    ring(&w.wo_s, m->rc_o);
+    ring(&w.wgu_s, m->rc_gu);
+    ring(&w.wdown_s, m->rc_down);
   }
   A((void**)&m->x, (size_t)kMaxRows * m->d * 4);
   A((void**)&m->delta, (size_t)kMaxSplits * kMaxRows * m->d * 4);
@@ -1219,20 +1235,9 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
   A((void**)&m->err, 64);
   if (st != DSI_OK) {
     free_list(m->allocs);
+    free_list(m->ring_allocs);
     delete m;
     return st;
-  }
-  // the ring layouts last: a model that has no memory for all of them runs on
-  // the packed ones
-  auto ring = [&](void** p, const RingCfg& c) {
-    if (m->use_ring && c.nbw && dev_alloc(m->ring_allocs, p, c.tiles() * tile * m->esz) != DSI_OK) drop_rings(m);
-  };
-  ring(&m->lm_head_s, m->rc_head);
-  for (LayerW& w : m->layers) {
-    ring(&w.wqkv_s, m->rc_qkv);
-    ring(&w.wo_s, m->rc_o);
-    ring(&w.wgu_s, m->rc_gu);
-    ring(&w.wdown_s, m->rc_down);
   }
   *out = m;
   return DSI_OK;
