@@ -52,7 +52,7 @@ __global__ __launch_bounds__(ST) void k_dstat(DraftArgs a) {
   double sum = 0.0;
 #pragma unroll
   for (int i = 0; i < SPER; ++i)
-    if (v0 + i < a.V) sum += exp_term(vals[i], a.temperature, a.inv_temperature, m);
+    if (v0 + i < a.V) sum += exp(over_t((double)vals[i], a.temperature, a.inv_temperature) - exp_base(m));
   sum = wave_sum(sum);
   if ((threadIdx.x & 63) == 0) shd[w] = sum;
   __syncthreads();
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(ST) void k_dstat(DraftArgs a) {
 }
 
 // the row's max and normaliser from the chunk statistics: wave 0, chunks
-// lane, lane + 64, ... then a butterfly (every block computes the same)
+// lane, lane + 64, ... then a wave scan (every block computes the same)
 __device__ __forceinline__ void row_stats(const DraftArgs& a, double* sM, double* sS) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
@@ -73,7 +73,7 @@ __device__ __forceinline__ void row_stats(const DraftArgs& a, double* sM, double
     for (int c = lane; c < a.C; c += 64) m = fmax(m, a.part[c].x);
     m = wave_max(m);
     double s = 0.0;
-    for (int c = lane; c < a.C; c += 64) s += chunk_term(a.part[c].y, a.part[c].x, m);
+    for (int c = lane; c < a.C; c += 64) s += a.part[c].y * exp(a.part[c].x - m);
     s = wave_sum(s);
     if (lane == 0) {
       *sM = m;

@@ -146,15 +146,10 @@ __device__ __forceinline__ double over_t(double z, double t, double inv) {
   return __builtin_isfinite(q) ? fma(fma(-q, t, z), inv, q) : q;
 }
 
-// exp(z / T - m) of a softmax whose largest exponent is m; a masked entry (z =
-// -inf) adds nothing, also where all of them are masked and m is -inf too
-__device__ __forceinline__ double exp_term(float z, double t, double inv, double m) {
-  return z == -INFINITY ? 0.0 : exp(over_t((double)z, t, inv) - m);
-}
-// a chunk's sum `sum` of those over its maximum m, relative to the row's M
-__device__ __forceinline__ double chunk_term(double sum, double m, double M) {
-  return sum == 0.0 ? 0.0 : sum * exp(m - M);
-}
+// What is subtracted from a chunk's exponents, the largest of which is m: in a
+// chunk of masked entries (all -inf) not -inf itself, so that each adds exp(-inf)
+// = 0 and not exp(-inf + inf)
+__device__ __forceinline__ double exp_base(double m) { return m == -INFINITY ? 0.0 : m; }
 
 // Entries v .. v + 3 of a row of n values, all in flight together: one
 // 16-byte load where `vec` says that rows are 16-byte aligned and n a multiple

@@ -14,9 +14,9 @@
 //
 // Four launches:
 //   1. row statistics: per (row, 4096-entry chunk) max, sum exp, argmax;
-//   2. decide: one wavefront per window combines chunk statistics, tests the
-//      k drafts in parallel and finds the first rejection with a ballot;
-//      greedy windows finish here;
+//   2. decide: one workgroup per window, a wave per row combines the chunk
+//      statistics, then one wave tests the k drafts in parallel and finds the
+//      first rejection with a ballot; greedy windows finish here;
 //   3. per (window, chunk): fp64 sums of the residual (and of p) over the
 //      chunk, via the same block scan used in step 4;
 //   4. sample: one workgroup per window locates the chunk that holds
@@ -76,12 +76,14 @@ __global__ __launch_bounds__(THR) void k_vrow(VerifyArgs a) {
   double m = 0.0;
   if (!a.greedy) {   // the exact-match rules read the argmax only
     m = over_t((double)zmax, a.temperature, a.inv_temperature);
+    const double mb = exp_base(m);
 #pragma unroll
     for (int g = 0; g < NV; ++g) {
       double sum = 0.0;
 #pragma unroll
       for (int i = 0; i < PER; ++i)
-        if (v0 + g * THR * PER + i < a.V) sum += exp_term(vals[g][i], a.temperature, a.inv_temperature, m);
+        if (v0 + g * THR * PER + i < a.V)
+          sum += exp(over_t((double)vals[g][i], a.temperature, a.inv_temperature) - mb);
       sum = wave_scan_incl(sum);
       if (lane == 63) shd[g * (THR / 64) + w] = sum;
     }
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(THR) void k_vrow(VerifyArgs a) {
 }
 
 // one workgroup per window: each wave combines the chunk statistics of a
-// row (lanes over chunks, butterfly in fixed order), then wave 0 decides; its
+// row (lanes over chunks, a wave scan in fixed order), then wave 0 decides; its
 // drafts' q and logits are requested before the statistics
 __global__ __launch_bounds__(VT) void k_vdecide(VerifyArgs a) {
   __shared__ double sM[kMaxRows], sS[kMaxRows];
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(VT) void k_vdecide(VerifyArgs a) {
       m = wave_max(m);
       for (int c = lane; c < a.C; c += 64) {
         const double2 pc = a.part[(size_t)r * a.C + c];
-        sum += chunk_term(pc.y, pc.x, m);
+        sum += pc.y * exp(pc.x - m);
       }
       sum = wave_sum(sum);
     }
