@@ -790,9 +790,11 @@ struct RingRole<EPI_STORE> {   // the LM head: many rounds of workgroups
 };
 
 // k-blocks per wave the ring kernel is built for (a shape's k-range per wave
-// is rounded up to one of them; the extra tiles are zero).  18 and 20 are the
-// 13B shape's (d_ff 13824 split three ways, d 5120), against its packed
-// kernels per launch at 11 / 17 / 55 rows: QKV 28.3 / 30.7 / 45.0 against 29.8
+// is rounded up to one of them; the extra tiles are zero and streamed, 40 %
+// more bytes at the worst, ten k-blocks in runs of 14).  K ranges of more than
+// 160 k-blocks (d_model above 5120) have none and take the packed kernels.  18
+// and 20 against those per launch at d_model 5120 and d_ff 13824 (K split three
+// ways), 11 / 17 / 55 rows: QKV 28.3 / 30.7 / 45.0 against 29.8
 // / 44.4 / 54.7 us, O 18.5 / 19.9 / 28.6 against 18.5 / 28.2 / 34.6, gate/up
 // 47.2 / 49.0 / 61.7 against 47.1 / 64.2 / 82.7, down 26.4 / 28.6 / 41.6
 // against 27.3 / 31.5 / 42.1, head 53 / 54 / 65 against 58 / 60 / 73.

@@ -315,7 +315,7 @@ struct VerifyArgs {
   double2* csum;        // [B][C]: (sum r, sum p)
   int C;                // chunks per row
 };
-constexpr int kVerifyChunk = 4096;  // vocabulary entries per chunk (256 thr x 16)
+constexpr int kVerifyChunk = 4096;  // vocabulary entries per chunk (1024 threads x 4, or 256 x 16)
 
 // drafter sampling (draft.hip): q = softmax(z / T) stored fp32 and one draft
 // drawn from it by inverse CDF
