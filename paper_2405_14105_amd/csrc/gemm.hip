@@ -593,11 +593,18 @@ constexpr int kRingMinTiles = 4;
 // registers would not hold 8 -- the narrow roles (one or two n-blocks per
 // workgroup) with several row tiles, whose activation slots (hi and lo of MT
 // tiles per k-block in flight) grow with MT, and gate/up's 7 x 4 accumulator
-// tiles at four row tiles.  The depth does not change any sum.
-constexpr int ring_depth(int nbw, int mt, int tiles) {
-  const int d = ((mt > 1 && nbw <= 2) || (mt >= 4 && nbw >= 7)) ? 4 : kRingDepth;
-  return tiles < d ? tiles : d;
+// tiles at four row tiles, and the two sets of accumulators of ring_halves.  The
+// depth does not change any sum.
+constexpr int ring_depth(int nk, int nbw, int mt) {
+  const int d = ((mt > 1 && nbw <= 2) || (mt >= 4 && (nbw >= 7 || nk > 16))) ? 4 : kRingDepth;
+  return nk * nbw < d ? nk * nbw : d;
 }
+// The two halves of a run longer than 16 k-blocks are summed by themselves: in
+// one chain the 13B shape's second-layer keys and values were 0.6-0.8 % less
+// exact than with the packed kernels (11 and 31 rows, fp32 cache).  Not with
+// seven or eight n-blocks, whose accumulators leave no registers for a second
+// set; the choice holds for every row count, so sums stay the same for all.
+constexpr bool ring_halves(int nk, int nbw) { return nk > 16 && nbw <= 4; }
 // n-blocks per LDS reduction round: kRingWaves x NBR x MT tiles of 1 KB
 // within 128 KB
 constexpr int ring_red_nb(int nbw, int mt) { return 16 / mt < nbw ? 16 / mt : nbw; }
@@ -660,7 +667,7 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&&
 // how many rows share the launch.
 template <int NK, int NBW, int EPI, int MT>
 __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
-  constexpr int NW = kRingWaves, N = NK * NBW, D = ring_depth(NBW, MT, N);
+  constexpr int NW = kRingWaves, N = NK * NBW, D = ring_depth(NK, NBW, MT), H = ring_halves(NK, NBW) ? 2 : 1;
   // activation slots: k-block i's fragments are requested together with its
   // first weight tile (D tiles ahead of use) and live until its last tile;
   // when one is requested, tile u has just been consumed and tiles
@@ -716,18 +723,20 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
     if (a.ssq) ring_row_scales<MT>(a, spre, rs);
     __builtin_amdgcn_sched_barrier(0);
   }
-  f32x4 acc[NBW][MT];
+  f32x4 acc[H][NBW][MT];
 #pragma unroll
-  for (int j = 0; j < NBW; ++j)
+  for (int h = 0; h < H; ++h)
 #pragma unroll
-    for (int t = 0; t < MT; ++t) acc[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NBW; ++j)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) acc[h][j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   static_for(std::make_integer_sequence<int, N>{}, [&](auto step) {
-    constexpr int u = decltype(step)::value, i = u / NBW;
+    constexpr int u = decltype(step)::value, i = u / NBW, h = i * H / NK;
     const bf16x8 wv = as_bf16x8(ring[u % D]);
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      acc[u % NBW][t] = mfma_bf16(wv, as_bf16x8(xh[i % A][t]), acc[u % NBW][t]);
-      acc[u % NBW][t] = mfma_bf16(wv, as_bf16x8(xl[i % A][t]), acc[u % NBW][t]);
+      acc[h][u % NBW][t] = mfma_bf16(wv, as_bf16x8(xh[i % A][t]), acc[h][u % NBW][t]);
+      acc[h][u % NBW][t] = mfma_bf16(wv, as_bf16x8(xl[i % A][t]), acc[h][u % NBW][t]);
     }
     if constexpr (u + D < N) issue(u + D);
     __builtin_amdgcn_sched_barrier(0);   // consume tile u, then refill its slot
@@ -739,7 +748,9 @@ __global__ __launch_bounds__(kRingWaves * 64) void k_gemm_ring(GemmArgs a) {
     for (int jj = 0; jj < NBR; ++jj)
 #pragma unroll
       for (int t = 0; t < MT; ++t)
-        if (j0 + jj < NBW) red[((w * NBR + jj) * MT + t) * 64 + lane] = acc[j0 + jj][t];
+        if (j0 + jj < NBW)
+          red[((w * NBR + jj) * MT + t) * 64 + lane] =
+              H == 2 ? acc[0][j0 + jj][t] + acc[H - 1][j0 + jj][t] : acc[0][j0 + jj][t];
     __syncthreads();
     finish<W_BF16, EPI, MT, NBR, NW>(a, red, a.ssq ? rs : nullptr, nb0 + j0, min(NBR, NBW - j0), split, pre);
   }

@@ -387,3 +387,41 @@ def test_verify_at_the_row_maximum():
         zo = oracle_logits(shape, prefixes[b], wi["tokens"][b])
         assert np.abs(z[b] - zo).max() <= min(TOL["f32"], reg_of(shape)), b
         split_check(z[b], wi["tokens"][b], wi["q"][b], wi["u"][b], out["n"][b], out["token"][b])
+
+
+# limits between one chain over a wave's run of 18 or 20 k-blocks (1.04e-7 and up;
+# 9.9e-8 and up) and its halves (8.9e-8; 7.8e-8 and 8.5e-8)
+@pytest.mark.parametrize("d,limit", [(4608, 1.0e-7), (5120, 9.2e-8)])
+@pytest.mark.parametrize("n", [11, 40])
+def test_long_runs_are_summed_in_halves(d, limit, n):
+    """Values of a layer whose weights and inputs are all positive, in an fp32 cache: there the summation's rounding is most
+    of the error against 64 bits."""
+    import torch
+    V, hq, hkv, hd = 64, 36, 36, 128
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    m = dsi.dsi_model_create(dsi.make_config(1, d, hq, hkv, hd, 64, V, kvdtype=dsi.DSI_F32), torch.cuda.current_stream().cuda_stream)
+    kv = dsi.dsi_kv_create(m, 1, 64)
+    try:
+        w = {}
+        for name, shape in (("embed", (V, d)), ("final_norm", (d,)), ("lm_head", (V, d)), ("attn_norm", (d,)), ("ffn_norm", (d,)),
+                            ("wq", (hq * hd, d)), ("wk", (hkv * hd, d)), ("wv", (hkv * hd, d)), ("wo", (d, hq * hd)),
+                            ("w_gate", (64, d)), ("w_up", (64, d)), ("w_down", (d, 64))):
+            t = torch.rand(shape, generator=g, device="cuda").add_(0.5).bfloat16()
+            w[name] = t
+            torch.cuda.synchronize()
+            layer = -1 if name in ("embed", "final_norm", "lm_head") else 0
+            dsi.dsi_model_set_tensor(m, layer, dsi.TENSOR_IDS[name], t.data_ptr(), t.numel() * 2, True)
+        toks = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+        dsi.dsi_prefill(m, kv, 0, toks, n)
+        k, v = (torch.empty((hkv, n, hd), device="cuda") for _ in range(2))
+        dsi.dsi_kv_export(kv, 0, 0, n, k, v)
+        x = w["embed"][toks.long()].double()
+        h = x / (x.square().mean(-1, keepdim=True) + 1e-5).sqrt() * w["attn_norm"].double()
+        want = (h @ w["wv"].double().t()).view(n, hkv, hd).transpose(0, 1)
+        err = float((v.double() - want).norm() / want.norm())
+        print(f"d {d} n {n}: {err:.4g}")
+        assert err <= limit
+    finally:
+        torch.cuda.synchronize()
+        dsi.dsi_kv_destroy(kv)
+        dsi.dsi_model_destroy(m)

@@ -30,7 +30,7 @@ def _weights(shape):
 @pytest.mark.parametrize("name,prefix,n", [
     ("ragged_bf16", 0, 65), ("ragged_bf16", 5, 129), ("gqa_hd64", 0, 97), ("gqa_hd64", 37, 257),
     ("mha_hd128", 63, 112), ("mha_hd128", 700, 66), ("many_kv", 0, 200), ("o_ring_hd128", 64, 300),
-    ("ring_wide_ff", 31, 81),
+    ("ring_wide_ff", 31, 81), ("ring_wide_d", 0, 70),
     # fp32 weights and / or cache
     ("tiny", 0, 65), ("tiny", 40, 300), ("tiny", 33, 49), ("tiny", 9, 64), ("ragged_f32", 7, 130), ("hd96_kvf32", 33, 129), ("f32w_bf16kv", 0, 200)])
 def test_matches_oracle(name, prefix, n):
