@@ -135,10 +135,12 @@ dsi_status dsi_kv_destroy(dsi_kv* kv);
  * drafts a task builds on).  d_last_logits (nullable, device [V] fp32)
  * receives the logits of the last token.  Fails with DSI_ECAPACITY if
  * length + n may exceed max_len, with no side effects.  The tokens run in
- * chunks of DSI_MAX_ROWS, many of them in one forward (the first prompt longer
- * than one chunk reserves the model's workspace for it); a chunk holding an id outside [0, V) does not
- * advance the length and is reported by the next synchronising call
- * (DSI_EINVAL).  The same prompt on the same cache gives the same bits,
+ * chunks of DSI_MAX_ROWS, many of them in one forward.  The first prompt of
+ * more than 64 rows (48 for fp32 weights, 32 for bf16 ones without the second
+ * copy) reserves the model's workspace for it, sized for the cache's max_len
+ * or 2048 rows (8B: about 0.5 GB), which stays with the model.  A chunk holding
+ * an id outside [0, V) does not advance the length and is reported by the next
+ * synchronising call (DSI_EINVAL).  The same prompt on the same cache gives the same bits,
  * whatever ran before.  They differ in rounding between ways of cutting a
  * prompt into calls, and where the workspace could not be reserved (a call
  * captured into a graph before any long prompt ran, no memory) and prompts run

@@ -5,12 +5,13 @@
 // hundreds of rows is bound by the matrix cores, if the weights are read once
 // for all of them.  In forwards of 64 rows the weights were read n / 64 times:
 // 2048 tokens through one 8B layer took 5.1 ms (gate/up 2.00, down 1.24, QKV
-// 0.85, O 0.65, attention 0.4); in one forward they take 1.6 ms (0.81, 0.36,
-// 0.24, 0.12, 0.11).
+// 0.85, O 0.65, attention 0.4); in one forward they take 1.6 ms (gate/up 0.76,
+// O and down 0.48 together, QKV 0.21, attention 0.08, the residual and norm
+// passes 0.09).
 //
-// GEMM (bf16 weights).  Same products as the window GEMMs: pre-tiled weights against the
-// hi/lo activation packs, two 16x16x32 MFMAs per product, fp32 sums.  A
-// workgroup of 8 waves makes a tile of NWN * 64 features x MT * 16 rows:
+// GEMM (bf16 weights).  Same products as the window GEMMs: pre-tiled weights
+// against the hi/lo activation packs, two 16x16x32 MFMAs per product, fp32
+// sums.  A workgroup of 8 waves makes a tile of NWN * 64 features x MT * 16 rows:
 //  * NWN (2, 4 or 8) waves lie along the features, four n-blocks each, and 8 /
 //    NWN groups of them split the tile's k-blocks, so two waves share each
 //    SIMD whatever the tile; the groups' sums meet in LDS at the end, in group
@@ -306,8 +307,9 @@ __global__ __launch_bounds__(256) void k_wide_fold(GemmArgs a, const float* part
 // row block by row block), so the keys and values of a 64-key stage are
 // loaded once per workgroup into LDS, in fragment order, while the stage
 // before is worked on, and a workgroup stops at its last row's position.
-// 8B, 2048 rows: 108 us (114 with a maximum and a rescale per 32 keys), against
-// 32 x 15 us of the window kernel, which reads the keys once per 16 queries.
+// 8B, 2048 rows: 97 us (5 % more with a maximum and a rescale per 32 keys),
+// against 32 x 15 us of the window kernel, which reads the keys once per 16
+// queries.
 // With few row blocks the keys are cut into chunks as well (13B, 77 rows over
 // 900 keys: 51 us whole, 19 + 5 in 256-key and 13 + 6 in 128-key chunks).
 template <int KVB, int HD>

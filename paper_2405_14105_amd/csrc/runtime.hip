@@ -842,10 +842,13 @@ int key_chunks(const dsi_model* m, int M, int rb0, int keys) {
 
 // Prompts of more rows than this run in wide forwards.  A model whose layer
 // GEMMs have ring layouts gains from 65 rows on, where 64-row forwards read
-// the weights twice (8B, 64 rows after 900: 770 us narrow, 791 wide; 65: 1201
-// and 815, 4 layers).  The packed kernels of the others are overtaken at three
-// row tiles (the 13B shape on them, 3 layers, 32 rows: 611 and 603; 33: 706 and 620), the fp32
-// ones at four (tiny, 48 rows after 900: 89 and 88; 64: 103 and 91).
+// the weights twice (rows after 900 keys, narrow and wide: 8B, 4 layers, 64
+// rows 751 and 753 us, 65 rows 985 and 787; 1B, 8 layers, 678 and 729, 949 and
+// 745).  The packed kernels of the others are overtaken at three row tiles (d
+// 6144, 3 layers, 32 rows: 677 and 626; 33: 779 and 640; from 17 rows on the
+// gain is 7 %, and those prompts keep the verification's kernels and bits), the
+// fp32 ones at four (tiny, 48 rows: 87 and 82; 49: 95 and 81; d 1024, two
+// layers, 48: 194 and 207; 49: 243 and 212).
 int wide_above(const dsi_model* m) {
   if (m->wtype != W_BF16) return 48;
   const LayerW& w = m->layers[0];
