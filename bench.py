@@ -33,7 +33,7 @@ METRIC = "verify-step latency (ms) + verified draft tokens/s, 8B-shape k=10; % H
 # scales from a 512 MiB copy).  Reported only while the GEMM sources are the
 # ones the counters were taken with.
 TRAFFIC_MEASURED = {"workload": "llama8b_L2048_k10", "bytes": 237.90e6,
-                    "sources_sha256": "72f217d1c092606206afc6ed2e745ecf896408877acd391ffbda88f6b27ac3d2"}
+                    "sources_sha256": "5054f5a451bf31879c3622e20acb36eaa74e482568a014019c6dab770d71c3d2"}
 # Matrix-core work of the same kernel from the counter run in
 # profiles/verify_8b_mfma_counters.md: SQ_INSTS_VALU_MFMA_MOPS_BF16 x 512 flops
 # per launch (what the MFMAs execute: 16-row tiles, both hi/lo halves) and

@@ -138,13 +138,13 @@ dsi_status dsi_kv_destroy(dsi_kv* kv);
  * chunks of DSI_MAX_ROWS, many of them in one forward.  The first prompt of
  * more than 64 rows (48 for fp32 weights, 32 for bf16 ones without the second
  * copy) reserves the model's workspace for it, sized for the cache's max_len
- * or 2048 rows (8B: about 0.5 GB), which stays with the model.  A chunk holding
+ * or 2048 rows (8B: 0.34 GB), which stays with the model.  A chunk holding
  * an id outside [0, V) does not advance the length and is reported by the next
- * synchronising call (DSI_EINVAL).  The same prompt on the same cache gives the same bits,
- * whatever ran before.  They differ in rounding between ways of cutting a
- * prompt into calls, and where the workspace could not be reserved (a call
- * captured into a graph before any long prompt ran, no memory) and prompts run
- * in shorter forwards.
+ * synchronising call (DSI_EINVAL).  The same prompt on the same cache gives the
+ * same bits, whatever ran before.  They differ in rounding between ways of
+ * cutting a prompt into calls, and where memory did not allow the workspace or
+ * the second copy, or a call was captured into a graph before a long prompt
+ * had reserved the workspace: prompts then run in shorter forwards.
  * Stream-ordered; d_tokens is caller-owned and only read by the call's stream
  * work. */
 dsi_status dsi_prefill(dsi_model* m, dsi_kv* kv, int32_t window, const int32_t* d_tokens,
