@@ -294,6 +294,38 @@ def test_captured_prompt_appends_on_every_replay(name, n):
             assert np.abs(z.cpu().numpy() - want).max() <= 2e-3
 
 
+@pytest.mark.parametrize("name", ["gqa_hd64", "tiny"])
+def test_short_calls_captured_after_a_long_prompt(name):
+    """A model whose first call is a long prompt: a short prompt and a draft can be captured next, and replay as they run eagerly."""
+    import torch
+    shape = S.SHAPES[name]
+    toks = S.prefix_tokens(shape, SEED, 0, 340)
+    with torch.cuda.stream(torch.cuda.Stream()), _rig(shape, SEED, 1, 2000) as rig:
+        t = rig.dev_i32(toks)
+        u = torch.full((4,), 0.4, device="cuda")
+        rig.prefill(0, toks[:300])
+        z = torch.zeros(shape.vocab, device="cuda")
+        tok, q = torch.zeros(5, dtype=torch.int32, device="cuda"), torch.zeros((4, shape.vocab), device="cuda")
+
+        def calls():
+            dsi.dsi_kv_rollback(rig.kv, 0, 240)
+            dsi.dsi_prefill(rig.model, rig.kv, 0, t[240:], 40, z)
+            dsi.dsi_draft(rig.model, rig.kv, 0, t[280:], 2, 4, u, tok, q)
+
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=torch.cuda.current_stream()):
+            calls()
+        out = []
+        for replay in (True, True, False, True):
+            for x in (z, tok, q):
+                x.zero_()
+            g.replay() if replay else calls()
+            torch.cuda.synchronize()
+            out.append([x.clone() for x in (z, tok, q)])
+    assert bool(out[0][0].any()) and all(torch.equal(a, b) for o in out[1:] for a, b in zip(out[0], o))
+
+
 def test_captured_launches_outlive_later_prompts():
     """Launches captured before the first wide prompt, replayed after it: it frees nothing that they use."""
     import torch
