@@ -130,6 +130,7 @@ struct dsi_model {
   std::vector<unsigned> set_mask;   // [L+1]: bit per tensor id (index 0: globals)
   std::vector<void*> allocs;
   std::vector<void*> ring_allocs;   // the ring layouts: copies the model can do without (give_back)
+  size_t spare_bytes = 0;       // what give_back would free
   bool captured = false;        // a caller has captured calls: their launches hold every buffer
   // forward workspace for up to kMaxRows rows
   float* x = nullptr;
@@ -283,12 +284,15 @@ bool wide_alloc(dsi_model* m, int rows) {
   }
   wide_layout(m, rows, slab, &w, &z0, &z1);
   m->wide = w;
+  m->spare_bytes += total;
   m->wide_slab[m->wide_slabs++] = slab;
   return true;
 }
 
+// while the model is created (nothing else is spare yet) or by give_back
 void drop_rings(dsi_model* m) {
   free_list(m->ring_allocs);
+  m->spare_bytes = 0;
   m->lm_head_s = nullptr;
   for (LayerW& w : m->layers) w.wqkv_s = w.wo_s = w.wgu_s = w.wdown_s = nullptr;
   m->use_ring = false;
@@ -308,10 +312,16 @@ bool capturing(dsi_model* m) {
 
 // Gives back what the model can do without: the ring layouts, the prompt
 // workspaces (the next long prompt asks again) and outgrown attention buffers.
-// Not where a graph of the caller's may use them.  False: nothing to give.
-bool give_back(dsi_model* m) {
-  if (capturing(m) || m->captured) return false;
-  if (m->ring_allocs.empty() && !m->wide_slabs && m->attn_slabs < 2) return false;
+// Not where a graph of the caller's may use them, nor where `need` bytes would
+// not fit all the same (the call fails then, and has no side effects).
+bool give_back(dsi_model* m, size_t need) {
+  if (capturing(m) || m->captured || !m->spare_bytes) return false;
+  size_t avail = 0, total = 0;
+  if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+    hipGetLastError();
+    return false;
+  }
+  if (avail + m->spare_bytes < need) return false;
   if (hipStreamSynchronize(m->stream) != hipSuccess) {
     hipGetLastError();
     return false;
@@ -327,6 +337,7 @@ bool give_back(dsi_model* m) {
     m->attn_slab[0] = m->attn_slab[m->attn_slabs - 1];
     m->attn_slabs = 1;
   }
+  m->spare_bytes = 0;
   return true;
 }
 
@@ -554,6 +565,7 @@ dsi_status ensure_attention(dsi_model* m, size_t parts) {
     return fail(DSI_ENOMEM, "attention buffers grown too often");
   }
   m->attn_slab[m->attn_slabs++] = p;
+  m->spare_bytes += m->attn_parts * each;   // the outgrown one
   m->attn_parts = take;
   m->attn_o = (float*)p;
   m->attn_ml = (float2*)(m->attn_o + take * m->hd);
@@ -1196,9 +1208,10 @@ dsi_status dsi_model_create(const dsi_config* cfg, void* stream, dsi_model** out
   };
   const size_t tile = 512;
   auto ring = [&](void** p, const RingCfg& c) {
-    if (st == DSI_OK && m->use_ring && c.nbw &&
-        dev_alloc(m->ring_allocs, p, c.tiles() * tile * m->esz) != DSI_OK)
-      drop_rings(m);
+    if (st != DSI_OK || !m->use_ring || !c.nbw) return;
+    const size_t bytes = c.tiles() * tile * m->esz;
+    if (dev_alloc(m->ring_allocs, p, bytes) == DSI_OK) m->spare_bytes += bytes;
+    else drop_rings(m);
   };
   A(&m->embed, (size_t)m->V * m->d * m->esz);
   A((void**)&m->final_norm, (size_t)m->d * 4);
@@ -1306,7 +1319,7 @@ dsi_status dsi_model_set_tensor(dsi_model* m, int32_t layer, int32_t id, const v
     void* staging = nullptr;
     if (!src_on_device) {
       hipError_t e = hipMalloc(&staging, nbytes);
-      if (e == hipErrorOutOfMemory && give_back(m)) {
+      if (e == hipErrorOutOfMemory && give_back(m, nbytes)) {
         hipGetLastError();
         e = hipMalloc(&staging, nbytes);
       }
@@ -1406,7 +1419,7 @@ dsi_status dsi_kv_create(dsi_model* m, int32_t n_windows, int32_t max_len, dsi_k
     return st;
   };
   dsi_status st = alloc();
-  if (st == DSI_ENOMEM && give_back(m)) st = alloc();   // a cache that fits without the copies is not refused
+  if (st == DSI_ENOMEM && give_back(m, 2 * bytes)) st = alloc();   // a cache that fits without the copies is not refused
   if (st != DSI_OK) {
     delete kv;
     return st;

@@ -217,6 +217,22 @@ def test_weight_copies_give_way(stub):
         dsi.dsi_kv_destroy(b)
         dsi.dsi_model_destroy(m)
         assert hip.stub_in_use() == 0
+    # a cache that would not fit without them either takes nothing
+    hip.stub_budget(used + 2 * cache)
+    m = model(shape, 4)
+    a = dsi.dsi_kv_create(m, 1, 32768)
+    dsi.dsi_prefill(m, a, 0, P, 300, P)
+    hip.stub_budget(cache)
+    before = hip.stub_in_use()
+    try:
+        dsi.dsi_kv_create(m, 4, 32768)
+    except dsi.DsiError as e:
+        assert e.status == dsi.DSI_ENOMEM
+    else:
+        raise AssertionError("a cache larger than the memory")
+    assert hip.stub_in_use() == before and rings(a) == (17, 0)
+    dsi.dsi_kv_destroy(a)
+    dsi.dsi_model_destroy(m)
     # a graph of the caller's may hold them: then they stay
     hip.stub_budget(used + 2 * cache)
     m = model(shape, 4)
